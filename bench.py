@@ -27,12 +27,7 @@ SALU_PEAK_GINST_S = 256 * 2.4            # 614.4 G scalar instructions / s: one 
 # (FETCH_SIZE + WRITE_SIZE scaled by a copy kernel of known size; SQ_INSTS_VALU; SQ_INSTS_SALU), keyed by
 # (workload, candidates per call).  Each entry names the SHA-256 (first 16 hex digits) of the kernel sources it
 # was taken on; the line below prints it only while the sources in the tree still hash to that, else null.
-PROFILED = {
-    ("W4", 65536): {"csrc_sha16": "3f0eef93ac58c684", "traffic_bytes": 1.65695e13, "valu_insts": 4.43262e12, "salu_insts": 4.74188e12,
-                    "source": "profiles/est_sim_kernel_W4.md"},
-    ("W5", 262144): {"csrc_sha16": "3f0eef93ac58c684", "traffic_bytes": 1.38932e14, "valu_insts": 3.55471e13, "salu_insts": 4.16431e13,
-                    "source": "profiles/est_sim_kernel_W5.md"},
-}
+PROFILED = {}
 
 
 def csrc_sha16():

@@ -62,12 +62,12 @@ struct Ctx {
     const uint64_t *cap_rings;
 };
 
-// Diagnostics record of candidate t and stage s: EST_DBG_WORDS words (general steps, ticks in the stage's scan,
-// shortcut steps, queries in shortcut steps, of which: lean light-load, light-load, one-per-batch, block of batches;
-// then ticks spent in steps that ended as: lean light-load, light-load, one-per-batch, block, backlog or horizon, general;
-// then ticks in the recurrence of the block steps and the batches those ran ahead).
+// Diagnostics record of candidate t and stage s: EST_DBG_WORDS words (unused, ticks in the stage's scan, steps,
+// queries in steps, of which: unused, unused, one-per-batch, batch by batch; then ticks spent in steps that ended as:
+// unused, unused, one-per-batch, batch by batch, backlog or horizon, unused; then ticks in the batch-by-batch recurrence
+// and the batches it formed).
 // The record of stage EST_MAX_STAGES-1 holds what belongs to no stage: ticks in merges, in the sink, in the
-// selection, merge rounds, merge output elements, merge calls, scan calls, queries in general steps.
+// selection, merge rounds, merge output elements, merge calls, scan calls.
 EST_DEV uint64_t *est_dbg_rec(const EstSimArgs *a, uint32_t t, uint32_t s) {
     return a->dbg_ticks + a->n_cfg + ((uint64_t)t * EST_MAX_STAGES + s) * EST_DBG_WORDS;
 }
@@ -200,239 +200,131 @@ EST_DEV uint64_t sort_lanes64(uint64_t v) {
     return sort_merge64<64>(v);
 }
 
-// Keys (e << 32 | q) of the lanes in VM, ascending, in lanes 0 .. popcount(VM)-1 (2^64-1 elsewhere).
-// Every e is at least base.  While the times span less than 2^26 the sort runs on 32-bit
-// (time - base, lane) pairs; equal times keep their lane order, and if that is not the order of the
-// query indices the full 64-bit sort is used after all.
-EST_DEV uint64_t sort_time_query(uint32_t e, uint32_t q, uint64_t VM, uint32_t base) {
-    const uint32_t ln = wv::lane();
-    const bool valid = wv::lane_in(VM);
-    const uint32_t d = e - base;
-    if ((VM & wv::ballot(d >= (1u << 26))) == 0) {
-        const uint32_t k = sort_lanes(valid ? ((d << 6) | ln) : 0xFFFFFFFFu, 64);
-        const uint32_t qs = wv::shfl(q, k & 63u);
-        const uint32_t ds = k >> 6;
-        const uint32_t dp = wv::shr1(ds), qp = wv::shr1(qs);
-        const uint32_t n = popc64(VM);
-        if ((lanes_below(n) & ~1ull & wv::ballot(dp == ds) & wv::ballot(qp > qs)) == 0)
-            return ln < n ? (((uint64_t)(base + ds) << 32) | qs) : ~0ull;
-    }
-    return sort_lanes64(valid ? (((uint64_t)e << 32) | q) : ~0ull);
-}
-
 // ------------------------------------------------------------------------------------------ SCAN
 //
-// Per-wavefront working set of a scan, in LDS:
-//   in-ring   128 or 256 keys (EstPlan::scan_ring: the smaller one where it lets one more wavefront share a SIMD):
-//             the next elements of the stage's input stream,
-//             refilled from the source ring in chunks (and filtered on the way, when only some
-//             elements of the source visit the stage);
-//   slots     one per replica: the members of the replica's last batch, sorted by query index,
-//             waiting to be emitted when the batch completes.
-// The replica table lives in registers, lane r holding the r-th replica in order of the time it is
-// free again, so the earliest free replica is lane 0 and batches complete in lane order.
+// Per-wavefront working set of a scan.  In registers, one entry per lane:
+//   F       the time every replica is free again, ascending (2^32-1 beyond the last replica); which replica is which
+//           does not matter, so a free time is all there is to a replica;
+//   gend, ginfo   the pending batches -- dispatched, not yet passed on -- ascending by completion time: lane l < nG
+//           holds the completion time, and the number of members << 8 | the member slot.  The lanes from nG on hold
+//           the numbers of the free slots.
+// In LDS:
+//   in-ring   128 or 256 keys (EstPlan::scan_ring): the next elements of the stage's input stream, refilled from the
+//             source ring in chunks (and filtered on the way, when only some elements of the source visit the stage);
+//   slots     EstPlan::slot_words words cut into slots of B (the candidate's maximum batch size at the stage): the
+//             query indices of the members of the pending batches.
+// A step looks at a window of up to 64 input elements.  First whatever is pending and certain to finish before anything
+// dispatched from here on leaves: everything that completes before lim = T0 + Lmin, T0 the start of the next batch, Lmin
+// the shortest latency of the stage.  Then the next batches are formed -- all of them become pending; only steps in
+// which every query is a batch of its own write their results directly.
 
-
-// Number of lanes whose value is below x (<= x with incl), for values that ascend with the lane: a binary search
-// over the lanes, the same for every lane's own x.  Only the first width lanes are searched (a power of two, the
-// same in every lane): no lane from there on may pass the test.
-EST_DEV uint32_t lanes_less(uint32_t v, uint32_t x, bool incl, uint32_t width = 64u) {
-    uint32_t pos = 0;
-    for (uint32_t step = width >> 1; step >= 1; step >>= 1) {
-        const uint32_t y = wv::shfl(v, pos + step - 1u);
-        if (incl ? y <= x : y < x) pos += step;
+// Query indices of the lanes in M (a prefix), which are in consecutive groups gid, each group's sorted ascending.
+// Indices that span less than 2^26 around the first one are sorted as 32-bit (group, index) pairs.
+EST_DEV uint32_t sort_groups(uint32_t gid, uint32_t q, uint64_t M) {
+    const bool valid = wv::lane_in(M);
+    const uint32_t base = wv::uniform(q) - (1u << 25), d = q - base;
+    if ((M & wv::ballot(d >= (1u << 26))) == 0) {
+        const uint32_t k = sort_lanes(valid ? ((gid << 26) | d) : 0xFFFFFFFFu, 64);
+        return (k & ((1u << 26) - 1u)) + base;
     }
-    const uint32_t y = wv::shfl(v, width - 1u);  // (pos is width-1 only when the lanes before that one all pass)
-    if (pos == width - 1u && (incl ? y <= x : y < x)) pos = width;
-    return pos;
+    return (uint32_t)sort_lanes64(valid ? (((uint64_t)gid << 32) | q) : ~0ull);
 }
 
 // The smallest power of two that is at least n (n from 1 to 64), at least 2
 EST_DEV uint32_t pow2_at_least(uint32_t n) { return n <= 2u ? 2u : 1u << (32u - (uint32_t)__builtin_clz(n - 1u)); }
 
-// Write the members of the batches in the table lanes of tie, which all complete at time mv, merged by
-// query index, to out[base ...]; returns their number.  (Times clamped at the horizon need no order:
-// everything downstream of a clamped time is clamped too, so those are concatenated.)  tw: lanes of the table.
-EST_DEV uint32_t emit_tied(const EstOp &op, const uint32_t *lslots, uint64_t tie, uint32_t mv, uint32_t rcnt, uint32_t rslot,
-                           uint64_t *out, uint32_t omask, uint32_t base, uint32_t tw) {
+// Pending batches k0 .. k1-1, which all complete at the same time mv and have more than 64 members in all, written to
+// out[wr ...] merged by query index: every batch is sorted in its slot, then every member finds its place among all of
+// them by binary searches.
+EST_DEV void emit_big_tie(uint32_t B, uint32_t *lslots, uint32_t k0, uint32_t k1, uint32_t mv, uint32_t ginfo, uint64_t *out,
+                          uint32_t omask, uint32_t wr) {
     const uint32_t ln = wv::lane();
-    const uint32_t bm = wv::uniform(op.b_max);
+    for (uint32_t k = k0; k < k1; ++k) {
+        const uint32_t gi = wv::bcast(ginfo, k), cr = gi >> 8, at = (gi & 0xFFu) * B + ln;
+        const uint32_t x = ln < cr ? lslots[at] : 0xFFFFFFFFu;  // (query indices stay below 2^31)
+        const uint32_t xs = sort_lanes(x, pow2_at_least(cr));
+        wv::sync_lds();
+        if (ln < cr) lslots[at] = xs;
+    }
+    wv::sync_lds();
     const uint64_t tkey = (uint64_t)mv << 32;
-    uint32_t total = 0;
-    if (mv == 0xFFFFFFFFu) {
-        for (uint64_t m = tie; m; m &= m - 1) {
-            const uint32_t r = ctz64(m);
-            const uint32_t cr = wv::bcast(rcnt, r), sl = wv::bcast(rslot, r);
-            if (ln < cr) out[(base + total + ln) & omask] = tkey | lslots[sl * bm + ln];
-            total += cr;
-        }
-        return total;
-    }
-    for (uint64_t m = tie; m; m &= m - 1) total += wv::bcast(rcnt, ctz64(m));
-    if (total <= 64u) {
-        // all members fit one per lane (a group that arrived together and was cut into many small batches, say): lane i
-        // takes the i-th member in table order, and one sorting network over the query indices does the merge
-        const uint32_t c = wv::lane_in(tie) ? rcnt : 0u;
-        const uint32_t off = wv::prefix_excl_u32(c);
-        const uint32_t l = lanes_less(off, ln, true, tw) - 1u;  // the last table lane whose batch starts at or before position ln
-        const uint32_t o = wv::shfl(off, l), sl = wv::shfl(rslot, l);
-        const uint32_t x = ln < total ? lslots[sl * bm + (ln - o)] : 0xFFFFFFFFu;  // (query indices stay below 2^31)
-        const uint32_t sorted = sort_lanes(x, pow2_at_least(total));
-        if (ln < total) out[(base + ln) & omask] = tkey | sorted;
-        return total;
-    }
-    // rank every member among all of them
-    total = 0;
-    for (uint64_t m = tie; m; m &= m - 1) {
-        const uint32_t r = ctz64(m);
-        const uint32_t cr = wv::bcast(rcnt, r), sl = wv::bcast(rslot, r);
-        const uint32_t x = ln < cr ? lslots[sl * bm + ln] : 0u;
+    for (uint32_t k = k0; k < k1; ++k) {
+        const uint32_t gi = wv::bcast(ginfo, k), cr = gi >> 8;
+        const uint32_t x = ln < cr ? lslots[(gi & 0xFFu) * B + ln] : 0u;
         uint32_t rank = ln;
-        for (uint64_t m2 = tie; m2; m2 &= m2 - 1) {
-            const uint32_t r2 = ctz64(m2);
-            const uint32_t c2 = wv::bcast(rcnt, r2), sl2 = wv::bcast(rslot, r2);
-            if (r2 == r || ln >= cr) continue;
-            const uint32_t *s2 = lslots + sl2 * bm;
-            uint32_t lo = 0, hi = c2;
+        for (uint32_t k2 = k0; k2 < k1; ++k2) {
+            const uint32_t g2 = wv::bcast(ginfo, k2);
+            if (k2 == k || ln >= cr) continue;
+            const uint32_t *s2 = lslots + (g2 & 0xFFu) * B;
+            uint32_t lo = 0, hi = g2 >> 8;
             while (lo < hi) {
                 const uint32_t mid = (lo + hi) >> 1;
                 if (s2[mid] < x) lo = mid + 1; else hi = mid;
             }
             rank += lo;
         }
-        if (ln < cr) out[(base + rank) & omask] = tkey | x;
-        total += cr;
-    }
-    return total;
-}
-
-// The batches in the table lanes of E (ascending completion times, no two of them equal) written out in table
-// order in one sweep: off (the members of the lanes of E before mine, e.g. from emit_offsets) turns an output
-// position into a batch and a member.  Every member goes to out[base + its position + extra of its batch], where
-// extra is a per-batch displacement (lane = table lane; 0 to write them back to back).
-EST_DEV void emit_many(const EstOp &op, const uint32_t *lslots, uint32_t total, uint32_t off, uint32_t extra, uint32_t rend,
-                       uint32_t rslot, uint64_t *out, uint32_t omask, uint32_t base, uint32_t tw) {
-    const uint32_t ln = wv::lane();
-    const uint32_t bm = wv::uniform(op.b_max);
-    for (uint32_t i0 = 0; i0 < total; i0 += 64) {
-        const uint32_t i = i0 + ln;
-        const uint32_t l = lanes_less(off, i, true, tw) - 1u;  // the last lane whose batch starts at or before position i
-        const uint32_t o = wv::shfl(off, l), e = wv::shfl(rend, l), sl = wv::shfl(rslot, l), x = wv::shfl(extra, l);
-        if (i < total) out[(base + i + x) & omask] = ((uint64_t)e << 32) | lslots[sl * bm + (i - o)];
+        if (ln < cr) out[(wr + rank) & omask] = tkey | x;
     }
 }
 
-// Older waiting batches (table lanes in woven, ascending completion times, all different from the new
-// ones) leave together with new queries: the new ones, whose completion times are ke in the lanes of emitm,
-// have been placed already, each shifted by the members of the older batches that finish before it; here the
-// older batches are written into the gaps, those that complete together merged by query index.
-EST_DEV void weave_out(const EstOp &op, const uint32_t *lslots, uint64_t woven, uint64_t emitm, uint32_t ke, uint32_t rend,
-                       uint32_t rcnt, uint32_t rslot, uint64_t *out, uint32_t omask, uint32_t wr, uint32_t tw) {
+// Pass on, in (completion time, query index) order, the members of the first nE pending batches (at least one; no
+// batch that stays completes at the same time as one of them), as far as the output ring has room; returns the number
+// of batches passed on.  Output positions are handled 64 at a time: a position finds its batch by counting the set bits
+// of a mask of the batches' first positions, and members that leave at the same time are put in query order only where
+// they are not in it already.  (Times clamped at the horizon need no order: everything downstream of a clamped time is
+// clamped too.)
+EST_DEV uint32_t emit_pending(uint32_t B, uint32_t *lslots, uint32_t nE, uint32_t gend, uint32_t ginfo, uint64_t *out,
+                              uint32_t omask, uint32_t &wr, uint32_t &space) {
     const uint32_t ln = wv::lane();
-    const uint32_t bm = wv::uniform(op.b_max);
-    uint32_t before = 0;
-    for (uint64_t pm = woven; pm;) {
-        const uint32_t j = ctz64(pm);
-        const uint32_t ej = wv::bcast(rend, j);
-        const uint64_t tie = pm & wv::ballot(rend == ej);
-        const uint32_t pos = wr + before + popc64(emitm & wv::ballot(ke < ej));
-        if ((tie & (tie - 1)) == 0) {
-            const uint32_t cj = wv::bcast(rcnt, j), sj = wv::bcast(rslot, j);
-            if (ln < cj) out[(pos + ln) & omask] = ((uint64_t)ej << 32) | lslots[sj * bm + ln];
-            before += cj;
-        } else {
-            before += emit_tied(op, lslots, tie, ej, rcnt, rslot, out, omask, pos, tw);
+    const uint32_t cnt = ln < nE ? ginfo >> 8 : 0u;
+    const uint32_t off = wv::prefix_excl_u32(cnt);
+    uint32_t total = wv::bcast(off, nE - 1u) + wv::bcast(cnt, nE - 1u);
+    const uint64_t tied = lanes_below(nE) & ~1ull & wv::ballot(gend == wv::shr1(gend)) & wv::ballot(gend != 0xFFFFFFFFu);
+    if (total > space) {
+        nE = popc64(lanes_below(nE) & wv::ballot(off + cnt <= space));  // (a prefix; batches that tie leave together)
+        while (nE > 0 && ((tied >> nE) & 1ull)) --nE;
+        if (nE == 0) return 0;
+        total = wv::bcast(off, nE - 1u) + wv::bcast(cnt, nE - 1u);
+    }
+    const uint32_t pk = (ginfo & 0xFFu) | (off << 8);
+    for (uint32_t k0 = 0, o0 = 0; k0 < nE;) {
+        uint32_t k1 = nE, o1 = total;
+        if (total - o0 > 64u) {
+            k1 = popc64(lanes_below(nE) & wv::ballot(off + cnt <= o0 + 64u));
+            while (k1 > k0 && ((tied >> k1) & 1ull)) --k1;  // (k1 < nE)
+            if (k1 == k0) {
+                for (k1 = k0 + 1u; k1 < nE && ((tied >> k1) & 1ull);) ++k1;
+                emit_big_tie(B, lslots, k0, k1, wv::bcast(gend, k0), ginfo, out, omask, wr + o0);
+                o0 = k1 < nE ? wv::bcast(off, k1) : total;
+                k0 = k1;
+                continue;
+            }
+            o1 = wv::bcast(off, k1);
         }
-        pm &= ~tie;
-    }
-}
-
-// New queries (their keys in the lanes of emit_me, rank orank among them, ns in all, ascending by rank) leave
-// together with the older waiting batches in the table lanes of woven (extra members in all, completion times
-// different from every new one): everything is written to out[wr ...] in (time, query) order.  With many older
-// batches and no two of them completing together, both sides find their places by binary searches over the
-// other side (lscr: 64 words of LDS scratch); otherwise batch by batch.
-EST_DEV void weave_all(const EstOp &op, const uint32_t *lslots, uint32_t *lscr, uint64_t woven, uint32_t extra, bool emit_me, uint64_t emitm,
-                       uint32_t orank, uint32_t ns, uint64_t key, uint32_t rend, uint32_t rcnt, uint32_t rslot, uint64_t *out,
-                       uint32_t omask, uint32_t wr, uint32_t tw) {
-    const uint32_t ln = wv::lane();
-    const uint32_t ke = (uint32_t)(key >> 32);
-    const uint64_t tied = woven & ~1ull & wv::ballot(rend == wv::shr1(rend));
-    if (popc64(woven) >= 6 && tied == 0) {
-        const uint32_t c = wv::lane_in(woven) ? rcnt : 0u;
-        const uint32_t off = wv::prefix_excl_u32(c);
-        const uint32_t pos = lanes_less(rend, ke, false, tw);        // table lanes that are free before my completion time
-        const uint32_t before = wv::shfl(off, pos);                  // members of the woven batches among them
-        if (emit_me) out[(wr + orank + (pos < 64u ? before : extra)) & omask] = key;
-        wv::sync_lds();
-        if (emit_me) lscr[orank] = ke;
-        wv::sync_lds();
-        const uint32_t kc = ln < ns ? lscr[ln] : 0xFFFFFFFFu;        // the new completion times in rank order
-        const uint32_t nb = lanes_less(kc, rend, false, pow2_at_least(ns));  // new queries that leave before my batch
-        emit_many(op, lslots, extra, off, nb, rend, rslot, out, omask, wr, tw);
-        wv::sync_lds();
-        return;
-    }
-    uint32_t shift = 0;
-    for (uint64_t pm = woven; pm; pm &= pm - 1) {
-        const uint32_t j = ctz64(pm);
-        const uint32_t ej = wv::bcast(rend, j), cj = wv::bcast(rcnt, j);
-        if (ej < ke) shift += cj;
-    }
-    if (emit_me) out[(wr + orank + shift) & omask] = key;
-    weave_out(op, lslots, woven, emitm, ke, rend, rcnt, rslot, out, omask, wr, tw);
-}
-
-// Emit, in (completion time, query index) order, the batches whose replica-table lanes are in E
-// (ascending lanes = ascending completion time).  Batches that complete at the same time are
-// merged by query index.  Stops early (returns false) when the output ring cannot take the next
-// group.
-EST_DEV bool scan_emit(const EstOp &op, const uint32_t *lslots, uint64_t E, uint32_t rend, uint32_t &rcnt,
-                       uint32_t rslot, uint64_t *out, uint32_t omask, uint32_t &wr, uint32_t &space, bool &progress, uint32_t tw) {
-    const uint32_t ln = wv::lane();
-    const uint32_t bm = wv::uniform(op.b_max);
-    if (popc64(E) >= 3) {
-        // several batches, no two completing together, and room for all of them: one sweep.  (The table is in
-        // order of time, so two batches of E with the same time have only lanes of that time between them: a lane
-        // of E whose time equals its left neighbour's is taken as a tie, whatever that neighbour holds.)
-        const uint64_t tied = E & ~1ull & wv::ballot(rend == wv::shr1(rend));
-        const uint32_t c = wv::lane_in(E) ? rcnt : 0u;
-        const uint32_t off = wv::prefix_excl_u32(c);
-        const uint32_t total = wv::bcast(off, 63) + wv::bcast(c, 63);
-        if (tied == 0 && total <= space) {
-            emit_many(op, lslots, total, off, 0u, rend, rslot, out, omask, wr, tw);
-            wr += total;
-            space -= total;
-            if (wv::lane_in(E)) rcnt = 0;
-            progress = true;
-            return true;
+        const uint32_t n = o1 - o0;
+        const uint64_t KM = lanes_below(k1) & ~lanes_below(k0);
+        const bool mine = wv::lane_in(KM);
+        const uint32_t pos = off - o0;  // first position of my batch in this chunk
+        const uint32_t bit = 1u << (pos & 31u);
+        const uint32_t hlo = wv::sum_u32(mine && pos < 32u ? bit : 0u), hhi = wv::sum_u32(mine && pos >= 32u ? bit : 0u);
+        const uint64_t H = ((uint64_t)hhi << 32) | hlo;
+        const uint32_t kl = k0 + wv::rank_below(H >> 1);  // my batch (bit 0 of H is set)
+        const uint32_t e = wv::shfl(gend, kl), y = wv::shfl(pk, kl);
+        uint32_t q = ln < n ? lslots[(y & 0xFFu) * B + (o0 + ln - (y >> 8))] : 0u;
+        const uint32_t qp = wv::shr1(q);
+        uint64_t Hg = H;  // first positions of the groups that leave at the same time
+        if (tied & KM) {
+            const uint32_t ep = wv::shr1(e);
+            Hg = wv::ballot(e != ep) | 1ull;
         }
+        if (lanes_below(n) & ~Hg & wv::ballot(qp > q)) q = sort_groups(wv::rank_below(Hg >> 1), q, lanes_below(n));
+        if (ln < n) out[(wr + o0 + ln) & omask] = ((uint64_t)e << 32) | q;
+        k0 = k1;
+        o0 = o1;
     }
-    while (E) {
-        const uint32_t l0 = ctz64(E);
-        const uint32_t mv = wv::bcast(rend, l0);
-        const uint64_t tie = E & wv::ballot(rend == mv);
-        const uint64_t tkey = (uint64_t)mv << 32;
-        if ((tie & (tie - 1)) == 0) {  // the common case: one batch
-            const uint32_t cr = wv::bcast(rcnt, l0), sl = wv::bcast(rslot, l0);
-            EST_CHECK(cr >= 1 && cr <= bm);
-            if (cr > space) return false;
-            if (ln < cr) out[(wr + ln) & omask] = tkey | lslots[sl * bm + ln];
-            wr += cr;
-            space -= cr;
-        } else {
-            uint32_t total = 0;
-            for (uint64_t m = tie; m; m &= m - 1) total += wv::bcast(rcnt, ctz64(m));
-            if (total > space) return false;
-            emit_tied(op, lslots, tie, mv, rcnt, rslot, out, omask, wr, tw);
-            wr += total;
-            space -= total;
-        }
-        if ((tie >> ln) & 1ull) rcnt = 0;
-        E &= ~tie;
-        progress = true;
-    }
-    return true;
+    wr += total;
+    space -= total;
+    return nE;
 }
 
 template <bool DIAG, bool MEMO>
@@ -443,37 +335,32 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op, uint32_t opi) {
     const EstStageCfg sc = c.cfg[s];
     // (values read from memory are the same in every lane; saying so keeps what is computed from them in
     // scalar registers, off the vector unit)
-    const uint32_t B = wv::uniform(sc.batch), R = wv::uniform(sc.replicas), bm = wv::uniform(op.b_max);
+    const uint32_t B = wv::uniform(sc.batch), R = wv::uniform(sc.replicas);
     EST_CHECK(B >= 1 && B <= op.b_max && R >= 1 && R <= op.r_max);
     const uint32_t *Ltab = c.a->lat_us + ((uint64_t)s * c.a->dag->H + sc.hw) * c.a->dag->Bmax;
     const uint32_t Lmine = ln < B ? Ltab[ln] : 0u;  // lane l holds L(l+1)
+    const uint32_t Lrot = wv::shfl(Lmine, ln - 1u);  // lane l holds L(l), lane 0 L(64)
     const uint32_t L1 = wv::bcast(Lmine, 0);
-    // the light-load shortcut below needs: no batch is faster than a single query
-    const bool mono = (lanes_below(B) & wv::ballot(Lmine < L1)) == 0;
-    uint32_t *g_end = c.rep + op.rep_off, *g_cnt = g_end + op.r_max, *g_slot = g_cnt + op.r_max;
+    const uint32_t Lmin = wv::min_u32(ln < B ? Lmine : 0xFFFFFFFFu);
+    const bool mono = Lmin == L1;  // no batch is faster than a single query
+    const uint32_t SW = wv::uniform(P.slot_words);
+    const uint32_t nslots = umin(64u, SW / B);  // (at least R)
+    EST_CHECK(nslots >= R);
+    uint32_t *g_free = c.rep + op.rep_off, *g_end = g_free + 64, *g_info = g_free + 128, *g_n = g_free + 192;
     uint32_t *g_slots = c.slots + op.slot_off;
     uint64_t *lkey = c.lds;
     const uint32_t RING = wv::uniform(P.scan_ring), rmask = RING - 1u;
-    uint32_t *ltab = (uint32_t *)(c.lds + RING);  // 4 x 64 words of per-group values (reused as staging by the rare table re-sort)
-    uint32_t *lstart = ltab + 256;         // 65 (of 72): first lane of each group of a window (+ the end)
-    uint16_t *linv = (uint16_t *)(ltab + 328);  // 64 half words: linv[d-1] = ceil(65536 / d) - 1, so that floor(x / d) = x * (linv[d-1] + 1) >> 16 for x <= 64
-    uint32_t *lslots = ltab + 360;
+    uint32_t *lslots = (uint32_t *)(c.lds + RING);
     const uint8_t *acc = c.a->acc + (uint64_t)op.acc_idx * c.a->acc_stride;
-    linv[ln] = (uint16_t)((65536u + ln) / (ln + 1u) - 1u);
+    const uint32_t filtered = wv::uniform(op.filtered);
     const uint32_t inv_b = (65536u + B - 1u) / B, inv_r = (65536u + R - 1u) / R;
 
-    // replica table, sorted by the time the replica is free again
     const bool isrep = ln < R;
-    const uint64_t REP = lanes_below(R);  // (lanes beyond the table hold end = 2^32-1, count 0)
-    const uint32_t tw = pow2_at_least(R);  // searches over the table look at this many lanes
-    uint32_t rend = isrep ? g_end[ln] : 0xFFFFFFFFu;
-    uint32_t rcnt = isrep ? g_cnt[ln] : 0u;
-    uint32_t rslot = isrep ? g_slot[ln] : 0u;
-    for (uint64_t m = wv::ballot(rcnt > 0); m; m &= m - 1) {  // members still waiting: back into LDS
-        const uint32_t l = ctz64(m);
-        const uint32_t cn = wv::bcast(rcnt, l), sl = wv::bcast(rslot, l);
-        if (ln < cn) lslots[sl * bm + ln] = g_slots[sl * bm + ln];
-    }
+    uint32_t F = isrep ? g_free[ln] : 0xFFFFFFFFu;
+    uint32_t gend = g_end[ln], ginfo = g_info[ln];
+    uint32_t nG = wv::uniform(*g_n);
+    if (nG)  // members still pending: back into LDS
+        for (uint32_t i = ln; i < SW; i += 64) lslots[i] = g_slots[i];
     wv::sync_lds();
 
     View in = view_of<MEMO>(c, op.src_ring[0]);
@@ -490,15 +377,12 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op, uint32_t opi) {
     uint32_t space = wv::uniform(ring_space(c, op.out_ring, wr));
     bool progress = false, finished = false;
     EST_CHK_ORDER_INIT();  // (host-side emulation only: everything written from here on is verified to be in order, step by step)
-    uint32_t fp_skip = 0;   // general batches still to do before the light-load shortcut is tried again
-    uint32_t sat_skip = 0;  // the same for the backlog shortcut
-    uint32_t single_skip = 0;  // and for the one-query-per-batch shortcut
-    uint32_t blk_skip = 0;     // and for the block of batches
-    uint32_t lean_skip = 0;    // and for the light-load step on large groups
-    uint32_t cf_skip = 0;      // and for the closed forms of one query per batch
-    uint64_t d_blkl = 0, d_blkk = 0;  // diagnostics: ticks in the recurrence of the block step, batches it ran ahead
+    uint32_t sat_skip = 0;     // steps to go before the backlog front end is tried again
+    uint32_t single_skip = 0;  // the same for one query per batch
+    uint32_t cf_skip = 0;      // and for its closed forms
+    uint64_t d_blkl = 0, d_blkk = 0;  // diagnostics: ticks in the batch-by-batch recurrence, batches it formed
     uint64_t d_tk[6] = {0, 0, 0, 0, 0, 0}, tk0 = 0;  // diagnostics: ticks by the kind of step that ended the iteration
-    uint32_t d_gen = 0, d_gene = 0, d_fp = 0, d_fpe = 0, d_b1 = 0, d_b1e = 0, d_sat = 0, d_sate = 0, d_hz = 0, d_blk = 0, d_blke = 0, d_lean = 0, d_leane = 0;  // diagnostics
+    uint32_t d_b1 = 0, d_b1e = 0, d_sat = 0, d_sate = 0, d_hz = 0, d_blk = 0, d_blke = 0;  // diagnostics
 
     for (;;) {
         uint32_t staged = ltail - lhead;
@@ -514,7 +398,7 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op, uint32_t opi) {
             // (lane masks are combined as scalars: one vector compare per term)
             uint64_t A0 = lanes_below(w0), A1 = lanes_below(w1), A2 = lanes_below(w2);
             bool a0 = ln < w0, a1 = ln < w1, a2 = ln < w2;
-            if (op.filtered) {  // (lanes beyond a window hold key 0: query 0 exists)
+            if (filtered) {  // (lanes beyond a window hold key 0: query 0 exists)
                 const bool f0 = (acc[(uint32_t)k0] & 1u) != 0u, f1 = (acc[(uint32_t)k1] & 1u) != 0u, f2 = (acc[(uint32_t)k2] & 1u) != 0u;
                 A0 &= wv::ballot(f0); A1 &= wv::ballot(f1); A2 &= wv::ballot(f2);
                 a0 = a0 && f0; a1 = a1 && f1; a2 = a2 && f2;
@@ -533,28 +417,45 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op, uint32_t opi) {
             wv::sync_lds();
             continue;
         }
-        if (staged == 0) {
-            if (in.fin) {  // input exhausted for good: flush what is still in flight
-                const uint64_t E = wv::ballot(rcnt > 0);
-                if (!E || scan_emit(op, lslots, E, rend, rcnt, rslot, out, omask, wr, space, progress, tw)) finished = true;
-            }
-            break;
-        }
-        // every step below works on a window of up to 64 queries and may emit as many: with less room
-        // than that in the output ring, let the reader run first rather than squeeze batches through
-        if (space < 64u) break;
+        if (staged == 0 && !in.fin) break;
+        // a step may pass on a window of 64 queries: with less room than that in the output ring, let the reader run
+        // first rather than squeeze batches through
+        if (staged != 0 && space < 64u) break;
         if (DIAG) tk0 = wv::ticks();
         const uint32_t w = umin(staged, 64u);
         const uint64_t key = ln < w ? lkey[(lhead + ln) & rmask] : ~0ull;
         const uint32_t rdy = (uint32_t)(key >> 32);
-        uint32_t q = (uint32_t)key;
+        const uint32_t q = (uint32_t)key;
         EST_CHECK(ln == 0 || ln >= w || rdy == 0xFFFFFFFFu || key > lkey[(lhead + ln - 1) & rmask]);  // input is ordered
-        const uint32_t f0 = wv::uniform(rend);  // earliest free replica = lane 0
-        if (f0 == 0xFFFFFFFFu) {
-            // Every replica is busy up to the horizon: whatever is still queued starts and ends at the
-            // horizon, where order no longer matters.  Waiting batches leave first, then the window.
-            const uint64_t E = wv::ballot(rcnt > 0);
-            if (E && !scan_emit(op, lslots, E, rend, rcnt, rslot, out, omask, wr, space, progress, tw)) break;
+        const uint32_t f0 = wv::uniform(F), r0 = wv::uniform(rdy);
+        const uint32_t T0 = umax(f0, r0);  // the next batch starts here (the horizon when the input has ended)
+        // ---- what nothing dispatched from here on can overtake leaves
+        {
+            const uint32_t lim = wv::sat_add_uniform(T0, Lmin);
+            const uint64_t late = ~lanes_below(nG) | (T0 == 0xFFFFFFFFu ? 0ull : wv::ballot(gend >= lim));
+            const uint32_t nE = late ? ctz64(late) : 64u;
+            if (nE > 0) {
+                const uint32_t d = emit_pending(B, lslots, nE, gend, ginfo, out, omask, wr, space);
+                EST_CHK_ORDER(4);
+                if (d) {
+                    progress = true;
+                    nG -= d;
+                    // the batches passed on go to the end of the lanes: their slots are free
+                    const uint32_t src = ln + d < nslots ? ln + d : ln + d - nslots;
+                    gend = wv::shfl(gend, src);
+                    ginfo = wv::shfl(ginfo, src);
+                    wv::sync_lds();
+                }
+                if (d < nE) break;  // wait for the consumer
+            }
+        }
+        if (staged == 0) {  // input exhausted for good, and nothing is in flight any more
+            finished = true;
+            break;
+        }
+        if (T0 == 0xFFFFFFFFu) {
+            // Every replica is busy up to the horizon, or the input is clamped there: whatever is still queued starts and
+            // ends at the horizon, where order no longer matters.
             const uint32_t m = umin(w, space);
             if (m == 0) break;
             if (ln < m) out[(wr + ln) & omask] = 0xFFFFFFFF00000000ull | q;
@@ -566,638 +467,223 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op, uint32_t opi) {
             progress = true;
             continue;
         }
-        if (B >= 2) {
-            if (sat_skip == 0 && B <= 32 && w >= 2 * B && wv::bcast(rdy, B - 1) <= f0) {
-                // Backlog: while the queue holds a full batch whenever a replica frees, the replicas take
-                // full batches in rotation.  With the free times f_0 <= ... <= f_{R-1} < f_0 + L(B), batch k
-                // (queries kB .. kB+B-1 of the window) starts at f_k, where f_k = f_{k-R} + L(B) for k >= R,
-                // provided its last member is ready by then.  The leading batches that satisfy this are all
-                // dispatched at once; as in the general step, everything that completes by the last of
-                // these dispatch times leaves, the rest waits in the slots of the replicas.
-                const uint32_t LB = wv::bcast(Lmine, B - 1);
-                const uint32_t tl = wv::bcast(rend, R - 1);
-                uint32_t nacc = 0;
-                if (tl < wv::sat_add_uniform(f0, LB)) {
+        const uint32_t last = wv::flag_ge(64u, staged) & wv::flag_eq(rraw, in.wr) & in.fin;  // the window holds the end of the input
+        if (nG == 0 && L1 > 0 && mono) {
+            if (space < 64u) break;
+            if (cf_skip == 0 && w >= 32 && R <= 31) {
+                // Closed forms for a whole window of queries that are each a batch of their own, checked with one
+                // vote and left to the steps below when they do not hold.  Query i runs on the replica that served
+                // query i-R (the table's entry i for the first R).
+                //   Nobody waits: every query finds that replica free again by the time it is ready, ready[i] >=
+                //   ready[i-R] + L(1) (for B > 1 no two queries may become ready together): end[i] = ready[i] + L(1).
+                //   Everybody waits (B = 1): ready[i] <= end[i-R], so end[i] = free[i mod R] + (i div R + 1) L(1), as
+                //   long as these ascend strictly (they do while the free times lie within one L(1) of each other;
+                //   equal completion times would have to be put in query order).
+                const uint64_t WM = lanes_below(w);
+                const uint32_t back = ln >= R && ln < w ? (uint32_t)(lkey[(lhead + ln - R) & rmask] >> 32) : 0u;
+                const uint32_t prev1 = ln < R ? F : sat_add(back, L1);
+                uint64_t ok1 = WM & wv::ballot(prev1 <= rdy);
+                if (B > 1) ok1 &= wv::ballot(rdy != wv::shl1(rdy)) | ~lanes_below(w - 1u);
+                uint32_t m = 0, x = 0;
+                if (ok1 == WM) {
+                    m = (B > 1 && !last) ? w - 1u : w;  // (for B > 1 the last query may yet be joined by the next)
+                    x = sat_add(rdy, L1);
+                } else if (B == 1) {
                     const uint32_t lo = wv::opaque(ln);
-                    const uint32_t kb = (lo * inv_b) >> 16;        // my batch
-                    const uint32_t kd = (kb * inv_r) >> 16, km = kb - kd * R;
-                    const uint64_t ft = (uint64_t)wv::shfl(rend, km) + (uint64_t)kd * LB;
-                    const uint32_t fk = ft >= 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)ft;
-                    const uint32_t e = sat_add(fk, LB);
-                    const uint32_t nfull = (w * inv_b) >> 16;
-                    const uint32_t lastr = wv::shfl(rdy, kb * B + B - 1u);
-                    const uint64_t okm = lanes_below(nfull * B) & wv::ballot(lastr <= fk) & wv::ballot(e != 0xFFFFFFFFu);
-                    const uint32_t nl = okm == ~0ull ? 64u : ctz64(~okm);  // a multiple of B: the test is per batch
-                    nacc = (nl * inv_b) >> 16;
-                    if (nacc >= 2) {
-                        const uint32_t na = nacc * B;
-                        const uint32_t Tlast = wv::bcast(fk, na - 1u);
-                        const uint64_t E = wv::ballot(rcnt > 0) & wv::ballot(rend <= Tlast);
-                        const uint64_t D = lanes_below(na) & wv::ballot(e <= Tlast);  // replaced again inside this step: never wait
-                        const bool direct = ln < na && e <= Tlast;
-                        const uint32_t nd = popc64(D);
-                        if (popc64(E) * B + nd > space) {
-                            nacc = 0;  // tight output ring: batch by batch
-                        } else {
-                            scan_emit(op, lslots, E, rend, rcnt, rslot, out, omask, wr, space, progress, tw);
-                            const uint32_t eprev = wv::shr1(e), qprev = wv::shr1(q), kprev = wv::shr1(kb);
-                            uint64_t okey = direct ? (((uint64_t)e << 32) | q) : ~0ull;
-                            if (D & ~1ull & wv::ballot(eprev == e) & wv::ballot(qprev > q)) okey = sort_lanes64(okey);
-                            if (ln < nd) out[(wr + ln) & omask] = okey;  // (times ascend with the batch: a prefix)
-                            wr += nd;
-                            space -= nd;
-                            EST_CHK_ORDER(6);
-                            // members wait sorted by query index
-                            uint32_t qs = q;
-                            if (lanes_below(na) & ~lanes_below(umax(nd, 1u)) & wv::ballot(kprev == kb) & wv::ballot(qprev > q))
-                                qs = (uint32_t)sort_lanes64(ln < na ? (((uint64_t)kb << 32) | q) : ~0ull);
-                            const uint32_t myslot = wv::shfl(rslot, km);
-                            if (ln >= nd && ln < na) lslots[myslot * bm + (ln - kb * B)] = qs;
-                            // new table: the entries not replaced, then the last min(nacc, R) batches
-                            const uint32_t nn = umin(nacc, R);
-                            const uint32_t src = (nacc - R + ln) * B;  // first lane of the batch that lands in table lane ln
-                            const uint32_t oe = wv::shfl(rend, ln + nn), oc = wv::shfl(rcnt, ln + nn), os = wv::shfl(rslot, ln + nn);
-                            const uint32_t ne = wv::shfl(e, src), ns = wv::shfl(myslot, src);
-                            if (isrep) {
-                                if (ln + nn < R) {
-                                    rend = oe; rcnt = oc; rslot = os;
-                                } else {
-                                    rend = ne; rcnt = ne > Tlast ? B : 0u; rslot = ns;
-                                }
-                            }
-                            wv::sync_lds();
-                            lhead += na;
-                            ++d_sat; d_sate += na;
-                            if (DIAG) d_tk[4] += wv::ticks() - tk0;
-                            progress = true;
-                            continue;
-                        }
+                    const uint32_t kd = (lo * inv_r) >> 16, km = lo - kd * R;
+                    const uint64_t st = (uint64_t)wv::shfl(F, km) + (uint64_t)kd * L1;  // when my replica is free for me
+                    const uint64_t en = st + L1;
+                    x = en >= 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)en;
+                    const uint32_t xp = wv::shr1(x);
+                    if ((WM & ~(wv::ballot((uint64_t)rdy <= st) & wv::ballot(x != 0xFFFFFFFFu) & (wv::ballot(x > xp) | 1ull))) == 0) m = w;
+                }
+                if (m >= R && wv::bcast(x, m - 1u) != 0xFFFFFFFFu) {
+                    if (ln < m) out[(wr + ln) & omask] = ((uint64_t)x << 32) | q;
+                    wr += m;
+                    space -= m;
+                    EST_CHK_ORDER(9);
+                    const uint32_t tnew = wv::shfl(x, ln + m - R);  // the table becomes the last R completion times
+                    if (isrep) F = tnew;
+                    lhead += m;
+                    ++d_b1; d_b1e += m;
+                    if (DIAG) d_tk[2] += wv::ticks() - tk0;
+                    progress = true;
+                    continue;
+                }
+                cf_skip = 6;
+            } else if (cf_skip) {
+                --cf_skip;
+            }
+            // With larger batch sizes the same evaluation holds as long as no query waits and no two become
+            // ready together: then every query is a batch of its own, started on arrival.
+            const bool single = B > 1 && single_skip == 0 && w >= 16;
+            if (B == 1 || single) {
+                // Maximum batch size 1: every query is its own batch and the service time is the constant
+                // L(1), so completions keep the input order and query i runs on the replica that served
+                // query i-R:  end_i = max(ready_i, end_{i-R}) + L(1).  The sorted replica table is exactly
+                // (end_{i-R}, ..., end_{i-1}), so a whole window is evaluated at once with a max-plus
+                // scan of stride R.  Nothing is pending: results are written out immediately.
+                uint32_t x = sat_add(umax(rdy, isrep ? F : 0u), L1);
+                for (uint32_t d = R, mul = 1; d < 64; d <<= 1, mul <<= 1) {
+                    const uint32_t y = wv::shfl(x, ln - d);
+                    const uint32_t inc = (uint64_t)mul * L1 > 0xFFFFFFFFull ? 0xFFFFFFFFu : mul * L1;
+                    if (ln >= d) x = umax(x, sat_add(y, inc));
+                }
+                uint32_t m = w;
+                bool sorted = true;
+                if (single) {
+                    // the leading queries that start on arrival, each alone at its ready time (the one after
+                    // it must be seen to become ready later); completion times then ascend strictly, and
+                    // whatever is dispatched later finishes later still
+                    const uint32_t rnext = wv::shl1(rdy);
+                    const uint64_t gm = lanes_below(w) & wv::ballot(x == sat_add(rdy, L1)) & wv::ballot(x != 0xFFFFFFFFu) &
+                                        ((wv::ballot(rdy != rnext) & lanes_below(w - 1u)) | (last ? 1ull << (w - 1u) : 0ull));
+                    m = gm == ~0ull ? 64u : ctz64(~gm);
+                    if (m < 12) {
+                        single_skip = 6;  // not the regime: leave it alone for a few steps
+                        m = 0;
                     }
-                }
-                if (nacc < 2) sat_skip = 4;
-            }
-        }
-        if (cf_skip == 0 && L1 > 0 && (B == 1 || mono) && w >= 32 && R <= 31 && wv::ballot(rcnt > 0) == 0) {
-            // Closed forms for a whole window of queries that are each a batch of their own, checked with one
-            // vote and left to the steps below when they do not hold.  Query i runs on the replica that served
-            // query i-R (the table's entry i for the first R).
-            //   Nobody waits: every query finds that replica free again by the time it is ready, ready[i] >=
-            //   ready[i-R] + L(1) (for B > 1 no two queries may become ready together): end[i] = ready[i] + L(1).
-            //   Everybody waits (B = 1): ready[i] <= end[i-R], so end[i] = free[i mod R] + (i div R + 1) L(1), as
-            //   long as these ascend strictly (they do while the free times lie within one L(1) of each other;
-            //   equal completion times would have to be put in query order).
-            const bool final = staged <= 64 && rraw == in.wr && in.fin;
-            const uint64_t WM = lanes_below(w);
-            const uint32_t back = ln >= R && ln < w ? (uint32_t)(lkey[(lhead + ln - R) & rmask] >> 32) : 0u;
-            const uint32_t prev1 = ln < R ? rend : sat_add(back, L1);
-            uint64_t ok1 = WM & wv::ballot(prev1 <= rdy);
-            if (B > 1) ok1 &= wv::ballot(rdy != wv::shl1(rdy)) | ~lanes_below(w - 1u);
-            uint32_t m = 0, x = 0;
-            if (ok1 == WM) {
-                m = (B > 1 && !final) ? w - 1u : w;  // (for B > 1 the last query may yet be joined by the next)
-                x = sat_add(rdy, L1);
-            } else if (B == 1) {
-                const uint32_t lo = wv::opaque(ln);
-                const uint32_t kd = (lo * inv_r) >> 16, km = lo - kd * R;
-                const uint64_t st = (uint64_t)wv::shfl(rend, km) + (uint64_t)kd * L1;  // when my replica is free for me
-                const uint64_t en = st + L1;
-                x = en >= 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)en;
-                const uint32_t xp = wv::shr1(x);
-                if ((WM & ~(wv::ballot((uint64_t)rdy <= st) & wv::ballot(x != 0xFFFFFFFFu) & (wv::ballot(x > xp) | 1ull))) == 0) m = w;
-            }
-            if (m >= R && wv::bcast(x, m - 1u) != 0xFFFFFFFFu) {
-                if (ln < m) out[(wr + ln) & omask] = ((uint64_t)x << 32) | q;
-                wr += m;
-                space -= m;
-                EST_CHK_ORDER(9);
-                const uint32_t tnew = wv::shfl(x, ln + m - R);  // the table becomes the last R completion times
-                if (isrep) rend = tnew;
-                lhead += m;
-                ++d_b1; d_b1e += m;
-                if (DIAG) d_tk[2] += wv::ticks() - tk0;
-                progress = true;
-                continue;
-            }
-            cf_skip = 6;
-        } else if (cf_skip) {
-            --cf_skip;
-        }
-        const bool b1 = B == 1 && L1 > 0;
-        // With larger batch sizes the same evaluation holds as long as no query waits and no two become
-        // ready together: then every query is a batch of its own, started on arrival.
-        const bool single = !b1 && B > 1 && mono && L1 > 0 && single_skip == 0 && w >= 16 && wv::ballot(rcnt > 0) == 0;
-        if (b1 || single) {
-            // Maximum batch size 1: every query is its own batch and the service time is the constant
-            // L(1), so completions keep the input order and query i runs on the replica that served
-            // query i-R:  end_i = max(ready_i, end_{i-R}) + L(1).  The sorted replica table is exactly
-            // (end_{i-R}, ..., end_{i-1}), so a whole window is evaluated at once with a max-plus
-            // scan of stride R.  Nothing waits in slots: results are written out immediately.
-            EST_CHECK(wv::ballot(rcnt > 0) == 0);
-            uint32_t x = sat_add(umax(rdy, isrep ? rend : 0u), L1);
-            for (uint32_t d = R, mul = 1; d < 64; d <<= 1, mul <<= 1) {
-                const uint32_t y = wv::shfl(x, ln - d);
-                const uint32_t inc = (uint64_t)mul * L1 > 0xFFFFFFFFull ? 0xFFFFFFFFu : mul * L1;
-                if (ln >= d) x = umax(x, sat_add(y, inc));
-            }
-            const bool last = staged <= 64 && rraw == in.wr && in.fin;
-            uint32_t m = umin(w, space);
-            bool sorted = true;
-            if (single) {
-                // the leading queries that start on arrival, each alone at its ready time (the one after
-                // it must be seen to become ready later); completion times then ascend strictly, and
-                // whatever is dispatched later finishes later still
-                const uint32_t rnext = wv::shl1(rdy);
-                const uint64_t gm = lanes_below(w) & wv::ballot(x == sat_add(rdy, L1)) & wv::ballot(x != 0xFFFFFFFFu) &
-                                    ((wv::ballot(rdy != rnext) & lanes_below(w - 1u)) | (last ? 1ull << (w - 1u) : 0ull));
-                const uint32_t m1 = gm == ~0ull ? 64u : ctz64(~gm);
-                if (m1 < 12) {
-                    single_skip = 6;  // not the regime: leave it alone for a few steps
-                    m = 0;
                 } else {
-                    m = umin(m1, space);
-                    if (m == 0) break;  // wait for the consumer
-                }
-            } else {
-                // Queries that complete at the same time leave ordered by query index.  Since
-                // end_i > end_{i-R}, such a run has at most R members; a shorter run at the end of what
-                // can be written now may continue with the next query, and is kept back until that is
-                // known (times clamped at the horizon need no order).
-                const uint32_t xp = wv::shr1(x);
-                const uint32_t qp = wv::shr1(q);
-                const uint64_t bnd = (lanes_below(w) & wv::ballot(x != xp)) | 1ull;  // starts of runs
-                if (m > 0) {
+                    // Queries that complete at the same time leave ordered by query index.  Since
+                    // end_i > end_{i-R}, such a run has at most R members; a shorter run at the end of what
+                    // can be written now may continue with the next query, and is kept back until that is
+                    // known (times clamped at the horizon need no order).
+                    const uint32_t xp = wv::shr1(x);
+                    const uint32_t qp = wv::shr1(q);
+                    const uint64_t bnd = (lanes_below(w) & wv::ballot(x != xp)) | 1ull;  // starts of runs
                     const uint32_t s0 = 63u - (uint32_t)__builtin_clzll(bnd & lanes_below(m));  // start of the run of lane m-1
                     const uint32_t xl = wv::bcast(x, m - 1u);
-                    const bool complete = m < w ? wv::bcast(x, m) != xl : (last || xl == 0xFFFFFFFFu || m - s0 >= R);
-                    if (!complete) m = s0;
+                    if (!(last || xl == 0xFFFFFFFFu || m - s0 >= R)) m = s0;
+                    if (m == 0) break;  // wait for the rest of the run
+                    sorted = (lanes_below(m) & ~1ull & wv::ballot(x == xp) & wv::ballot(q < qp) & wv::ballot(x != 0xFFFFFFFFu)) == 0;
                 }
-                if (m == 0) break;  // wait for the consumer, or for the rest of the run
-                sorted = (lanes_below(m) & ~1ull & wv::ballot(x == xp) & wv::ballot(q < qp) & wv::ballot(x != 0xFFFFFFFFu)) == 0;
-            }
-            if (m > 0) {
-                uint64_t okey = ln < m ? (((uint64_t)x << 32) | q) : ~0ull;
-                if (!sorted) okey = sort_lanes64(okey);
-                if (ln < m) out[(wr + ln) & omask] = okey;
-                wr += m;
-                space -= m;
-                ++d_b1; d_b1e += m;
-                if (DIAG) d_tk[2] += wv::ticks() - tk0;
-                EST_CHK_ORDER(1);
-                // the table becomes the last R completion times
-                const uint32_t keep = R > m ? R - m : 0u;  // old entries that stay
-                const uint32_t told = wv::shfl(rend, ln + m);
-                const uint32_t tnew = wv::shfl(x, ln + m - R);
-                if (isrep) rend = ln < keep ? told : tnew;
-                // (old entries that stay hold no members, so they ended by some earlier start + L(1): no later than the new ends)
-                const uint32_t rbefore = wv::shr1(rend);
-                EST_CHECK(ln == 0 || !isrep || rend >= rbefore);
-                (void)rbefore;
-                lhead += m;
-                progress = true;
-                continue;
-            }
-        }
-        if (single_skip) --single_skip;
-        if (mono && L1 > 0 && lean_skip == 0 && w >= 16) {
-            // Light load, large groups: the queries of a run (same ready time, at most B of them) are one batch,
-            // started at that time on a replica that is idle when the window's first query becomes ready.  When
-            // the new completion times ascend from run to run and all lie after every completion time already in
-            // the table, the table stays sorted by appending them, and the output order is settled by the table
-            // alone: the members of the new batches wait in their replicas' slots, and what leaves now are the older
-            // batches that finish before tau = (ready time of the first query after the accepted runs) + L(1),
-            // before which nothing dispatched later can finish.  Work per run, not per query, apart from moving
-            // the query indices.
-            const uint32_t r0 = wv::uniform(rdy);
-            const uint64_t WM = lanes_below(w);
-            const uint32_t rprev = wv::shr1(rdy);
-            const uint64_t heads = WM & (wv::ballot(rdy != rprev) | 1ull);
-            const bool final = staged <= 64 && rraw == in.wr && in.fin;
-            const uint32_t p = popc64(REP & wv::ballot(rend <= r0));  // idle now: a prefix of the sorted table
-            const uint32_t gid = wv::rank_below(heads >> 1);           // my run (lane 0 starts run 0)
-            uint32_t m = final ? w : 63u - (uint32_t)__builtin_clzll(heads);  // the last run may go on beyond the window
-            {
-                const uint64_t fits = WM & wv::ballot(gid < p);               // one idle replica per run
-                m = umin(m, fits == ~0ull ? 64u : ctz64(~fits));
-            }
-            const uint64_t AM = lanes_below(m);
-            const uint64_t hA = heads & AM;
-            const uint32_t G = popc64(hA);
-            bool done = false;
-            if (m >= 16 && 4u * G <= m) {
-                // my run: lanes [start, nh)
-                const uint64_t upto = lanes_below(wv::opaque(ln) + 1u);
-                const uint32_t start = 63u - (uint32_t)__builtin_clzll((hA & upto) | 1ull);
-                const uint64_t later = ln == 63 ? 0ull : (hA >> (ln + 1));
-                const uint32_t nh = later ? ln + 1u + ctz64(later) : m;
-                const uint32_t g = nh - start;
-                const uint32_t e = sat_add(rdy, wv::shfl(Lmine, (g - 1u) & 63u));  // (L is 0 beyond B: rejected below)
-                const uint32_t eprev = wv::shr1(e);
-                const uint64_t bad = AM & (wv::ballot(g > B) | wv::ballot(e == 0xFFFFFFFFu) | (hA & ~1ull & wv::ballot(eprev >= e)));
-                const uint32_t e0 = wv::uniform(e), last_old = wv::bcast(rend, R - 1u);
-                if (bad == 0 && (G == R || e0 > last_old)) {
-                    const bool tau_inf = final && m >= w;
-                    const uint32_t tau = tau_inf ? 0xFFFFFFFFu : wv::sat_add_uniform(wv::bcast(rdy, umin(m, w - 1u)), L1);
-                    const uint64_t E = wv::ballot(rcnt > 0) & (tau_inf ? ~0ull : wv::ballot(rend < tau));
-                    if (E && !scan_emit(op, lslots, E, rend, rcnt, rslot, out, omask, wr, space, progress, tw)) break;  // wait for the consumer
-                    EST_CHK_ORDER(8);
-                    wv::sync_lds();  // the slots of batches just written out may be taken again
-                    const uint32_t myslot = wv::shfl(rslot, gid);
-                    if (ln < m) lslots[myslot * bm + (ln - start)] = q;
-                    if (ln < m && ln == start) { ltab[gid] = e; ltab[64 + gid] = g; }
-                    wv::sync_lds();
-                    // new table: the entries not taken move down, the new batches follow in run order
-                    const uint32_t keep = R - G;
-                    const uint32_t oe = wv::shfl(rend, ln + G), oc = wv::shfl(rcnt, ln + G), os = wv::shfl(rslot, ln + G);
-                    const uint32_t k = ln >= keep && ln < R ? ln - keep : 0u;
-                    const uint32_t ns = wv::shfl(rslot, k);
-                    const uint32_t ne = ltab[k], nc = ltab[64 + k];
-                    if (isrep) {
-                        if (ln < keep) {
-                            rend = oe; rcnt = oc; rslot = os;
-                        } else {
-                            rend = ne; rcnt = nc; rslot = ns;
-                        }
-                    }
-                    wv::sync_lds();
-                    lhead += m;
-                    ++d_lean; d_leane += m;
-                    if (DIAG) d_tk[0] += wv::ticks() - tk0;
-                    progress = true;
-                    done = true;
-                }
-            }
-            if (done) continue;
-            lean_skip = 4;
-        } else if (lean_skip) {
-            --lean_skip;
-        }
-        if (mono && fp_skip == 0) {
-            // Light load: as long as every group of queries that become ready at the same instant
-            // finds an idle replica at that instant and fits one batch, each group is one batch started
-            // at its ready time r and finished at r + L(group size).  A whole run of groups is
-            // evaluated at once.  Let tau = (ready time of the first query after the run) + L(1): no
-            // later batch can finish before tau.  Batches of the run that finish before tau are
-            // written out right away, ordered by (completion time, query index), together with older
-            // waiting batches that finish before tau; the others wait in their replica's slot like any
-            // dispatched batch.  The p replicas idle at the first ready time serve the groups in turn
-            // (group k takes the replica of group k-p, which must be free again by then); replicas
-            // still busy are left alone.
-            const uint32_t r0 = wv::uniform(rdy);
-            const uint64_t idle0 = REP & wv::ballot(rend <= r0);
-            const uint64_t E0 = idle0 & wv::ballot(rcnt > 0);
-            if (E0 && !scan_emit(op, lslots, E0, rend, rcnt, rslot, out, omask, wr, space, progress, tw)) break;
-            EST_CHK_ORDER(5);
-            const uint32_t pidle = popc64(idle0);  // idle now: a prefix of the sorted table
-            uint32_t m = 0;
-            if (pidle > 0) {
-                uint32_t *lend = ltab, *lg = ltab + 64, *luns = ltab + 128;  // per group: end, size, waits
-                // groups: queries with the same ready time, cut into pieces of B (a piece of B queries is
-                // a full batch; the queries of a run are in query-index order, so piece j holds its
-                // members j*B .. j*B+B-1, as the queue would hand them out)
-                const uint32_t rprev = wv::shr1(rdy);
-                const uint64_t WM = lanes_below(w);
-                const uint64_t runs = WM & (wv::ballot(rdy != rprev) | 1ull);
-                // first lane of every run through LDS (run r starts at lstart[r]; lstart[number of runs] = w)
-                const uint32_t nruns = popc64(runs);
-                const uint32_t rid = wv::rank_below(runs >> 1);  // my run (lane 0 always starts one)
-                if (ln < w && (ln == 0 || rdy != rprev)) lstart[rid] = ln;
-                if (ln == 0) lstart[nruns] = w;
-                wv::sync_lds();
-                uint64_t heads = runs;
-                uint32_t bid = rid, start = lstart[rid], nh = lstart[rid + 1u];
-                const uint32_t rlen = ln < nruns ? lstart[ln + 1u] - lstart[ln] : 0u;
-                if (wv::ballot(rlen > B)) {
-                    // some run is longer than a batch: cut the runs into pieces of B
-                    const uint64_t upto = lanes_below(wv::opaque(ln) + 1u);
-                    const uint32_t off = ln - start;
-                    heads = WM & wv::ballot(off == B * ((off * inv_b) >> 16));  // first query of each group
-                    bid = popc64(heads & upto) - 1u;                               // group index of this lane
-                    start = 63u - (uint32_t)__builtin_clzll(heads & upto);
-                    const uint64_t later = ln == 63 ? 0ull : (heads >> (ln + 1));
-                    nh = later ? ln + 1 + ctz64(later) : w;                        // where the next group starts
-                }
-                const uint32_t g = nh - start;
-                const bool final = staged <= 64 && rraw == in.wr && in.fin;
-                const uint32_t e = sat_add(rdy, wv::shfl(Lmine, g - 1));       // (L is 0 beyond B: rejected below)
-                uint32_t *lrdy = ltab + 192;                                   // per group: ready time
-                if (ln < w && ln == start) { lend[bid] = e; lg[bid] = g; lrdy[bid] = rdy; }
-                wv::sync_lds();
-                // replicas that serve the run: the table's first p entries, each free by the time its turn
-                // comes (group l takes entry l); later groups take the replica of the group p before them
-                const uint32_t ngroups = popc64(heads);
-                const uint64_t usable = REP & lanes_below(ngroups) & wv::ballot(rend <= lrdy[ln < ngroups ? ln : 0]);
-                const uint32_t p = usable == ~0ull ? 64u : ctz64(~usable);     // >= 1: entry 0 is idle now
-                // no new completion time may equal an older waiting one (older ones that tie with each other are
-                // merged by query index when they leave)
-                const uint64_t busyp = wv::ballot(rcnt > 0);  // all of these end after r0
-                uint64_t okm = WM & wv::ballot(e != 0xFFFFFFFFu) & wv::ballot(g <= B);  // (a clamped time never passes)
-                if (busyp) {
-                    // (one search over the table per lane; an entry that no longer holds members counts as well, which
-                    // only ends the run early)
-                    const uint32_t pos = lanes_less(rend, e, false, tw);  // the first table lane that is free no earlier than e
-                    okm &= ~wv::ballot(wv::shfl(rend, pos & 63u) == e && pos < 64u);
-                }
-                okm &= final ? ~0ull : (wv::ballot(nh < w) | wv::ballot(g == B));                    // the whole group is in view (or it is full)
-                okm &= wv::ballot(bid < p) | wv::ballot(lend[bid >= p ? bid - p : 0u] <= rdy);     // its replica is free again
-                m = okm == ~0ull ? 64u : ctz64(~okm);                    // (a group is accepted or rejected as a whole)
                 if (m > 0) {
-                    // the next batch starts no earlier than the next query's ready time; if the run took
-                    // the whole window, that is at least the window's last ready time
-                    bool tau_inf = m >= w && final;                      // nothing follows at all
-                    uint32_t tau = tau_inf ? 0xFFFFFFFFu : wv::sat_add_uniform(wv::bcast(rdy, umin(m, w - 1u)), L1);
-                    uint64_t safem = lanes_below(m) & (tau_inf ? ~0ull : wv::ballot(e < tau));
-                    if (safem != lanes_below(m)) {
-                        // Some batch of the run would have to wait.  Waiting batches cost slot traffic and
-                        // weaving in the steps that follow; if the run up to the first of them is long and
-                        // nothing in it has to wait once the run ends there, stop the run there: the rest is
-                        // looked at again with more of the input in view.
-                        const uint32_t m2 = ctz64(~safem);               // (the first query of its group)
-                        if (m2 >= 16) {
-                            const uint32_t tau2 = wv::sat_add_uniform(wv::bcast(rdy, m2), L1);
-                            if ((lanes_below(m2) & ~wv::ballot(e < tau2)) == 0) {
-                                m = m2;
-                                tau = tau2;
-                                tau_inf = false;
-                                safem = lanes_below(m2);
-                            }
-                        }
-                    }
-                    const bool safe = ln < m && (tau_inf || e < tau);
-                    const uint32_t ns = popc64(safem);
-                    // older waiting batches that finish before tau go out with the run (the table is in order of
-                    // time: the rest finish later and keep waiting)
-                    const uint64_t woven = tau_inf ? busyp : busyp & wv::ballot(rend < tau);
-                    const uint32_t extra = woven ? wv::sum_u32(wv::lane_in(woven) ? rcnt : 0u) : 0u;
-                    if (ns + extra > space) {
-                        m = 0;  // leave it to the general path (or to the consumer)
-                    } else {
-                        // order the run's own output: usually already ordered
-                        uint64_t key = safe ? (((uint64_t)e << 32) | q) : ~0ull;
-                        // completion times that never decrease along the run, with query indices ascending where they are
-                        // equal: already in output order.  (Measured: where this test fails, an exact test over the safe
-                        // queries alone fails as well, so none is made.)
-                        const uint32_t eprev1 = wv::shr1(e);
-                        const uint32_t qprev = wv::shr1(q);
-                        const uint64_t inv = lanes_below(m) & ~1ull & (wv::ballot(eprev1 > e) | (wv::ballot(eprev1 == e) & wv::ballot(qprev > q)));
-                        uint32_t orank = wv::rank_below(safem);
-                        if (inv) {
-                            key = sort_time_query(e, q, safem, r0);
-                            orank = ln;
-                        }
-                        const bool emit_me = inv ? ln < ns : safe;
-                        const uint64_t emitm = inv ? lanes_below(ns) : safem;
-                        weave_all(op, lslots, lrdy, woven, extra, emit_me, emitm, orank, ns, key, rend, rcnt, rslot, out, omask, wr, tw);
-                        if ((woven >> ln) & 1ull) rcnt = 0;
-                        wr += ns + extra;
-                        space -= ns + extra;
-                        EST_CHK_ORDER(inv ? 3 : 2);
-                        // the run's batches that finish at or after tau wait in the slot of their replica
-                        const uint32_t inv_p = wv::uniform((uint32_t)linv[p - 1u]) + 1u;                      // floor(x / p) = x * inv_p >> 16 for x < 64
-                        const uint32_t kmod = bid - p * ((bid * inv_p) >> 16);   // the replica (idle-table lane) of my group
-                        const uint32_t myslot = wv::shfl(rslot, kmod);
-                        const bool waits = ln < m && !safe;
-                        if (waits) lslots[myslot * bm + (ln - start)] = q;
-                        if (ln < m && ln == start) luns[bid] = waits ? 1u : 0u;
-                        wv::sync_lds();
-                        // new table: every idle replica that served a group holds its last group's completion
-                        // time (and its members, if they wait); then everything is put back in order of time
-                        const uint32_t nb = popc64(heads & lanes_below(m));      // groups accepted
-                        uint32_t cend = rend, ccnt = rcnt, cslot = rslot;
-                        if (ln < p && ln < nb) {
-                            const uint32_t x = nb - 1u - ln;
-                            const uint32_t klast = ln + p * ((x * inv_p) >> 16);
-                            cend = lend[klast];
-                            ccnt = luns[klast] ? lg[klast] : 0u;
-                        }
-                        // back in order of time: sort (time since r0, lane) pairs -- entries idle at r0 count
-                        // as 0 and keep their order -- and fetch each entry from the lane it was in
-                        const uint32_t dl = cend > r0 ? cend - r0 : 0u;
-                        if ((REP & wv::ballot(dl >= (1u << 26))) == 0) {
-                            uint32_t width = 2;
-                            while (width < R) width <<= 1;
-                            const uint32_t from = sort_lanes(isrep ? ((dl << 6) | ln) : 0xFFFFFFFFu, width) & 63u;
-                            const uint32_t se = wv::shfl(cend, from), sc = wv::shfl(ccnt, from), ss = wv::shfl(cslot, from);
-                            if (isrep) { rend = se; rcnt = sc; rslot = ss; }
-                        } else {
-                            uint32_t trank = 0;
-                            for (uint32_t j = 0; j < R; ++j) {
-                                const uint32_t ej = wv::bcast(cend, j);
-                                if (ej < cend || (ej == cend && j < ln)) ++trank;
-                            }
-                            wv::sync_lds();  // (the per-group values in this area have been read)
-                            if (isrep) { ltab[trank] = cend; ltab[64 + trank] = ccnt; ltab[128 + trank] = cslot; }
-                            wv::sync_lds();
-                            if (isrep) { rend = ltab[ln]; rcnt = ltab[64 + ln]; rslot = ltab[128 + ln]; }
-                            wv::sync_lds();
-                        }
-                        lhead += m;
-                        progress = true;
-                    }
-                }
-            }
-            ++d_fp; d_fpe += m;
-            if (DIAG && m > 0) d_tk[1] += wv::ticks() - tk0;
-            if (m < 3) fp_skip = 6;  // not the regime for this shortcut: leave it alone for a few batches
-            if (m > 0) continue;
-            if (space == 0) break;
-        }
-        if (fp_skip) --fp_skip;
-        if (sat_skip) --sat_skip;
-        if (B >= 2 && mono && L1 > 0 && blk_skip == 0 && w >= 4) {
-            // A block of batches: the batch-by-batch recurrence (start = max(earliest free replica,
-            // first ready time), members = those ready by then, up to B) needs only scalars and one
-            // vector compare per batch, so it is run ahead for as many batches as the window decides,
-            // on a copy of the table; emission, slots and the new table are then done once for the
-            // whole block, with the same rule as the light-load step: whatever finishes before
-            // tau = (earliest possible next start) + L(1) is written out now in (completion, query)
-            // order, older waiting batches that finish before tau are woven in, the rest waits.  A
-            // batch replaced on its replica inside the block finished by that later start, hence before tau.
-            const uint64_t WM = lanes_below(w);
-            const bool final = staged <= 64 && rraw == in.wr && in.fin;
-            const uint64_t busyp = wv::ballot(rcnt > 0);
-            // working table: free time, and packed (members waiting << 16 | batch of this block on the entry, 0xFF = none, << 8 | slot)
-            uint32_t trend = rend, tinfo = (rcnt << 16) | 0xFF00u | rslot;
-            uint32_t vE = 0, vP = 0;                                          // per batch (lane k): end, and slot << 16 | first lane << 8 | size
-            uint64_t heads = 0;
-            uint32_t a = 0, K = 0;
-            uint32_t cap = 0xFFFFFFFFu;  // a new batch completes together with an older waiting one at this time: nothing from there on leaves in this step
-            const uint64_t tkl = DIAG ? wv::ticks() : 0;
-            const uint32_t wf = final ? 65u : w;  // a batch that is not full is decided once a query ready later is in view (or none can follow)
-            // (one exit and one branch per batch: the tests are combined as integers, which keeps them on the scalar unit)
-            for (uint32_t go = 1u; go;) {
-                const uint32_t f = wv::uniform(trend);
-                const uint32_t ti0 = wv::uniform(tinfo);
-                const uint32_t T = umax(f, wv::bcast(rdy, a));
-                // (lanes beyond the window hold 2^32-1: they count only when T is the horizon, and then the step ends here)
-                const uint32_t ready = popc64(wv::ballot(rdy <= T));
-                const uint32_t b = umin(B, ready - a);
-                const uint32_t e = wv::sat_add_uniform(T, wv::bcast(Lmine, b - 1u));
-                // stop: more members may still arrive | a clamped time never passes
-                const uint32_t stop = wv::flag_ne_and_ge(b, B, ready, wf) | wv::flag_ge(e, 0xFFFFFFFFu);
-                go = 0u;
-                if (stop == 0u) {
-                    // the earliest entry leaves the table, the new one goes in behind everything that ends no later (the
-                    // entry that leaves is free by T < e, so it is counted; lanes beyond the table hold 2^32-1 > e)
-                    const uint32_t p = popc64(wv::ballot(trend <= e)) - 1u;
-                    const uint32_t slot0 = ti0 & 0xFFu;
-                    uint32_t more = 1u;
-                    if (wv::bcast(trend, p) == e) {
-                        // completes together with an entry of the table; if that is an older batch still waiting, the pair is
-                        // merged by query index when it leaves, later: nothing from this time on leaves in this step, and the
-                        // block ends here (an entry taken after this would lose its slot and have to leave)
-                        const uint32_t e2 = wv::opaque_uniform(e);
-                        const uint64_t tiem = wv::ballot(tinfo >= 0x10000u) & wv::ballot(trend == e2);
-                        const uint32_t hit = wv::flag_ne((uint32_t)tiem | (uint32_t)(tiem >> 32), 0u);
-                        cap = hit ? e2 : cap;
-                        more = hit ^ 1u;
-                    }
-                    vE = wv::set_lane(vE, e, K);
-                    vP = wv::set_lane(vP, (slot0 << 16) | (a << 8) | b, K);
-                    const uint32_t ne = wv::shl1_any(trend), ni = wv::shl1_any(tinfo);  // (p < 64: lane 63 is never among the lanes below p)
-                    if (ln < p) {
-                        trend = ne; tinfo = ni;
-                    }
-                    trend = wv::set_lane(trend, e, p);
-                    tinfo = wv::set_lane(tinfo, (K << 8) | slot0, p);
-                    heads |= 1ull << a;
-                    a += b;
-                    ++K;
-                    go = more & wv::flag_lt(a, w);
-                }
-                go = wv::opaque_uniform(go);
-            }
-            bool done = false;
-            if (DIAG) { d_blkl += wv::ticks() - tkl; d_blkk += K; }
-            if (K >= 2) {
-                const uint32_t f_next = wv::uniform(trend);
-                bool tau_inf = final && a >= w;
-                const uint32_t r_next = wv::bcast(rdy, a < w ? a : w - 1u);  // what follows is ready no earlier
-                uint32_t tau = tau_inf ? 0xFFFFFFFFu : wv::sat_add_uniform(umax(f_next, r_next), L1);
-                const uint32_t kb = wv::rank_below(heads >> 1);             // my batch (lane 0 starts batch 0)
-                const uint32_t e = wv::shfl(vE, kb), pk = wv::shfl(vP, kb), st = (pk >> 8) & 0xFFu, myslot = pk >> 16;
-                const uint64_t AM = lanes_below(a);
-                if (cap != 0xFFFFFFFFu && (tau_inf || cap < tau)) {
-                    tau = cap;
-                    tau_inf = false;
-                }
-                const uint64_t safem = AM & (tau_inf ? ~0ull : wv::ballot(e < tau));
-                const uint32_t nsafe = popc64(safem);
-                // older waiting batches that finish before tau leave with the block (the table is in order of time).  None of
-                // them completes together with a new batch that leaves now: such a pair would have set the cap.
-                const uint64_t woven = tau_inf ? busyp : busyp & wv::ballot(rend < tau);
-                const uint32_t extra = woven ? wv::sum_u32(wv::lane_in(woven) ? rcnt : 0u) : 0u;
-                const bool safe = ln < a && (tau_inf || e < tau);
-                if (nsafe + extra <= space) {
-                    const uint32_t eprev = wv::shr1(e), qprev = wv::shr1(q), kprev = wv::shr1(kb);
-                    uint64_t key = safe ? (((uint64_t)e << 32) | q) : ~0ull;
-                    // in output order already?  (only checked when the safe queries are the leading ones)
-                    const bool ordered = safem == lanes_below(nsafe) &&
-                                         (safem & ~1ull & (wv::ballot(eprev > e) | (wv::ballot(eprev == e) & wv::ballot(qprev > q)))) == 0;
-                    if (!ordered) key = sort_time_query(e, q, safem, wv::uniform(rdy));
-                    const bool emit_me = ln < nsafe;
-                    weave_all(op, lslots, ltab + 192, woven, extra, emit_me, lanes_below(nsafe), ln, nsafe, key, rend, rcnt, rslot, out, omask, wr, tw);
-                    wr += nsafe + extra;
-                    space -= nsafe + extra;
-                    EST_CHK_ORDER(7);
-                    wv::sync_lds();  // the slots of woven batches have been read: they may be written again
-                    // members of batches that wait go to their replica's slot, sorted by query index
-                    const uint64_t waitm = AM & ~safem;
-                    uint32_t qs = q;
-                    if (waitm & ~1ull & wv::ballot(kprev == kb) & wv::ballot(qprev > q))
-                        qs = (uint32_t)sort_lanes64(ln < a ? (((uint64_t)kb << 32) | q) : ~0ull);
-                    if (ln < a && !safe) lslots[myslot * bm + (ln - st)] = qs;
-                    // the working table becomes the table: older entries written out lose their members,
-                    // entries of this block keep theirs if they wait
-                    const uint32_t tk = (tinfo >> 8) & 0xFFu;
-                    const uint32_t bsz = wv::shfl(vP, tk) & 0xFFu;
-                    const bool late = !tau_inf && trend >= tau;
-                    if (isrep) {
-                        rend = trend;
-                        rslot = tinfo & 0xFFu;
-                        rcnt = tk == 0xFFu ? (late ? tinfo >> 16 : 0u) : (late ? bsz : 0u);
-                    }
-                    wv::sync_lds();
-                    lhead += a;
-                    ++d_blk; d_blke += a;
-                    if (DIAG) d_tk[3] += wv::ticks() - tk0;
+                    uint64_t okey = ln < m ? (((uint64_t)x << 32) | q) : ~0ull;
+                    if (!sorted) okey = sort_lanes64(okey);
+                    if (ln < m) out[(wr + ln) & omask] = okey;
+                    wr += m;
+                    space -= m;
+                    ++d_b1; d_b1e += m;
+                    if (DIAG) d_tk[2] += wv::ticks() - tk0;
+                    EST_CHK_ORDER(1);
+                    // the table becomes the last R completion times
+                    const uint32_t keep = R > m ? R - m : 0u;  // old entries that stay
+                    const uint32_t told = wv::shfl(F, ln + m);
+                    const uint32_t tnew = wv::shfl(x, ln + m - R);
+                    if (isrep) F = ln < keep ? told : tnew;
+                    // (old entries that stay ended by some earlier start + L(1): no later than the new ends)
+                    const uint32_t fbefore = wv::shr1(F);
+                    EST_CHECK(ln == 0 || !isrep || F >= fbefore);
+                    (void)fbefore;
+                    lhead += m;
                     progress = true;
-                    done = true;
+                    continue;
                 }
             }
-            if (done) continue;
-            blk_skip = 4;
-        } else if (blk_skip) {
-            --blk_skip;
+            if (single_skip) --single_skip;
         }
-        ++d_gen;
-        const uint32_t f = wv::uniform(rend);  // earliest free replica = lane 0
-        const uint32_t r0 = wv::uniform(rdy);
-        const uint32_t T = umax(f, r0);  // dispatch time of the next batch
-        const uint64_t mm = lanes_below(umin(w, B)) & wv::ballot(rdy <= T);
-        const uint32_t b = popc64(mm);
-        EST_CHECK(b >= 1 && mm == lanes_below(b));
-        // The batch is known once it is full, or a later query is seen to be ready only after T,
-        // or no further input can come.  (Fewer than 64 staged means the source is drained.)
-        const bool decidable = (b == B) || (b < w) || in.fin;
-        if (!decidable) break;
-        // everything that completes by T leaves before this batch is dispatched
-        const uint64_t E = wv::ballot(rcnt > 0) & wv::ballot(rend <= T);
-        if (E && !scan_emit(op, lslots, E, rend, rcnt, rslot, out, omask, wr, space, progress, tw)) break;
-        EST_CHK_ORDER(4);
-        // members wait in the replica's slot sorted by query index
-        if (b > 1) {
-            const uint32_t prev = wv::shr1(q);
-            if (lanes_below(b) & ~1ull & wv::ballot(q < prev)) {
-                uint32_t width = 2;
-                while (width < b) width <<= 1;
-                q = sort_lanes(ln < b ? q : 0xFFFFFFFFu, width);
+        // ---- form the next batches: heads = first queries of the batches, a = queries taken, vA and gend in the lanes
+        //      nG .. K-1 = first query and completion time of every new batch, F = the new free times
+        uint32_t K = nG, a = 0, vA = 0, kind = 3;
+        uint64_t heads = 0;
+        if (sat_skip == 0 && B >= 2 && w >= 2 * B && wv::bcast(rdy, B - 1) <= f0) {
+            // Backlog: while the queue holds a full batch whenever a replica frees, the replicas take
+            // full batches in rotation.  With the free times f_0 <= ... <= f_{R-1} < f_0 + L(B), batch k
+            // (queries kB .. kB+B-1 of the window) starts at f_k, where f_k = f_{k-R} + L(B) for k >= R,
+            // provided its last member is ready by then.  The leading batches that satisfy this are all
+            // dispatched at once.
+            const uint32_t LB = wv::bcast(Lmine, B - 1);
+            if (wv::bcast(F, R - 1) < wv::sat_add_uniform(f0, LB)) {
+                const uint32_t lo = wv::opaque(ln);
+                const uint32_t kb = (lo * inv_b) >> 16;        // my batch
+                const uint32_t kd = (kb * inv_r) >> 16, km = kb - kd * R;
+                const uint64_t ft = (uint64_t)wv::shfl(F, km) + (uint64_t)kd * LB;
+                const uint32_t fk = ft >= 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)ft;
+                const uint32_t e = sat_add(fk, LB);
+                const uint32_t nfull = umin((w * inv_b) >> 16, nslots - nG);
+                const uint32_t lastr = wv::shfl(rdy, kb * B + B - 1u);
+                const uint64_t okm = lanes_below(nfull * B) & wv::ballot(lastr <= fk) & wv::ballot(e != 0xFFFFFFFFu);
+                const uint32_t nl = okm == ~0ull ? 64u : ctz64(~okm);  // a multiple of B: the test is per batch
+                const uint32_t nacc = (nl * inv_b) >> 16;
+                if (nacc >= 2) {
+                    a = nacc * B;
+                    K = nG + nacc;
+                    kind = 4;
+                    heads = lanes_below(a) & wv::ballot(lo == kb * B);
+                    const uint32_t first = (ln - nG) * B, en = wv::shfl(e, first);
+                    if (ln >= nG && ln < K) { gend = en; vA = first; }
+                    // the entries not taken, then the last min(nacc, R) batches
+                    const uint32_t nn = umin(nacc, R);
+                    const uint32_t oe = wv::shfl(F, ln + nn), ne = wv::shfl(e, (nacc - R + ln) * B);
+                    if (isrep) F = ln + nn < R ? oe : ne;
+                }
             }
+            if (a == 0) sat_skip = 4;
+        } else if (sat_skip) {
+            --sat_skip;
         }
-        const uint32_t slot = wv::uniform(rslot);  // the earliest free replica takes the batch
-        EST_CHECK(wv::uniform(rcnt) == 0 && slot < op.r_max);
-        if (ln < b) lslots[slot * bm + ln] = q;
-        const uint32_t end = wv::sat_add_uniform(T, wv::bcast(Lmine, b - 1));
-        // drop lane 0 from the table and insert the new entry so that the table stays sorted
-        const uint32_t p = popc64(REP & ~1ull & wv::ballot(rend <= end));
-        const uint32_t nend = wv::shl1(rend), ncnt = wv::shl1(rcnt), nslot = wv::shl1(rslot);
-        if (ln < p) {
-            rend = nend; rcnt = ncnt; rslot = nslot;
-        } else if (ln == p) {
-            rend = end; rcnt = b; rslot = slot;
+        if (a == 0) {
+            // batch by batch; a batch that is not full is decided once a query ready later is in view, or none can follow
+            const uint64_t tkl = DIAG ? wv::ticks() : 0;
+            wv::form_batches(rdy, Lrot, B, w, last ? 65u : w, nslots, F, gend, vA, heads, a, K);
+            a = umin(a, w);
+            if (DIAG) { d_blkl += wv::ticks() - tkl; d_blkk += K - nG; }
+            if (a == 0) break;  // undecidable: wait for input
         }
-        lhead += b;
-        d_gene += b;
-        if (DIAG) d_tk[5] += wv::ticks() - tk0;
-        progress = true;
+        // ---- the new batches become pending: members to their slots, sizes, everything in order of completion
+        {
+            const uint32_t kb = nG + wv::rank_below(heads >> 1);  // my batch's lane (query 0 starts the first)
+            const uint32_t pk = wv::shfl((ginfo & 0xFFu) | (vA << 8), kb);
+            if (ln < a) lslots[(pk & 0xFFu) * B + (ln - (pk >> 8))] = q;
+            const uint32_t anext = wv::shl1(vA);
+            const uint32_t cnt = (ln + 1u == K ? a : anext) - vA;
+            if (ln >= nG && ln < K) ginfo = (ginfo & 0xFFu) | (cnt << 8);
+            nG = K;
+            EST_CHECK(nG <= nslots);
+            const uint32_t gprev = wv::shr1(gend);
+            if (lanes_below(nG) & ~1ull & wv::ballot(gprev > gend)) {
+                const uint32_t base = T0, d = gend - base;  // (everything pending completes after T0)
+                uint32_t from;
+                if ((lanes_below(nG) & wv::ballot(d >= (1u << 26))) == 0) {
+                    from = sort_lanes(ln < nG ? ((d << 6) | ln) : 0xFFFFFFFFu, pow2_at_least(nG)) & 63u;
+                } else {
+                    from = (uint32_t)sort_lanes64(ln < nG ? (((uint64_t)gend << 32) | ln) : ~0ull) & 63u;
+                }
+                if (ln >= nG) from = ln;  // (the free slots stay where they are)
+                gend = wv::shfl(gend, from);
+                ginfo = wv::shfl(ginfo, from);
+            }
+            wv::sync_lds();
+            lhead += a;
+            progress = true;
+            if (kind == 4) { ++d_sat; d_sate += a; } else { ++d_blk; d_blke += a; }
+            if (DIAG) d_tk[kind] += wv::ticks() - tk0;
+        }
     }
 
     if (DIAG && c.a->dbg_ticks && ln == 0) {
         uint64_t *pc = est_dbg_rec(c.a, c.t, s);  // per candidate and stage (one writer: no atomics)
-        pc[0] += d_gen; pc[2] += d_fp + d_b1 + d_sat + d_blk + d_lean; pc[3] += d_fpe + d_b1e + d_sate + d_hz + d_blke + d_leane;
-        pc[4] += d_leane; pc[5] += d_fpe; pc[6] += d_b1e; pc[7] += d_blke;
+        pc[2] += d_b1 + d_sat + d_blk; pc[3] += d_b1e + d_sate + d_hz + d_blke;
+        pc[6] += d_b1e; pc[7] += d_blke;
         for (uint32_t i = 0; i < 6; ++i) pc[8 + i] += d_tk[i];
         pc[14] += d_blkl; pc[15] += d_blkk;
         uint64_t *po = est_dbg_rec(c.a, c.t, EST_MAX_STAGES - 1);
-        po[6] += 1; po[7] += d_gene;
+        po[6] += 1;
     }
-    // back to memory: the table, the members still waiting, the cursors
-    if (isrep) {
-        g_end[ln] = rend;
-        g_cnt[ln] = rcnt;
-        g_slot[ln] = rslot;
-    }
-    for (uint64_t m = wv::ballot(rcnt > 0); m; m &= m - 1) {
-        const uint32_t l = ctz64(m);
-        const uint32_t cn = wv::bcast(rcnt, l), sl = wv::bcast(rslot, l);
-        if (ln < cn) g_slots[sl * bm + ln] = lslots[sl * bm + ln];
-    }
+    // back to memory: the free times, the pending batches and their members, the cursors
+    if (isrep) g_free[ln] = F;
+    g_end[ln] = gend;
+    g_info[ln] = ginfo;
+    if (ln == 0) *g_n = nG;
+    if (nG)
+        for (uint32_t i = ln; i < SW; i += 64) g_slots[i] = lslots[i];
     // Staged but unconsumed queries are read again next time: the read cursor goes back to the first of
     // them.  Without a filter that is simply their number of places back; with one, the source is walked
     // backwards, a window at a time, until that many accepted queries have been passed.
     uint32_t cursor = rraw;
     {
         uint32_t need = ltail - lhead;
-        if (!op.filtered) {
+        if (!filtered) {
             cursor = rraw - need;
         } else {
             while (need > 0) {
@@ -1581,7 +1067,7 @@ EST_DEV void sim_init(const EstSimArgs &a, const Ctx &c) {
     wv::sync();
     for (uint32_t opi = 0; opi < P.n_ops; ++opi) {
         const EstOp &op = P.ops[opi];
-        if (op.type == EST_OP_SCAN && ln < op.r_max) c.rep[op.rep_off + 2 * op.r_max + ln] = ln;
+        if (op.type == EST_OP_SCAN) c.rep[op.rep_off + 128 + ln] = ln;
     }
     {
         uint32_t *tw = (uint32_t *)c.tab;

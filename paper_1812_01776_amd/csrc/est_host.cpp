@@ -75,6 +75,10 @@ int build_plan(estimator *h, const EstStatus &st, uint64_t n, PlanOut &po, bool 
 
     uint32_t max_rb = 1;
     for (uint32_t s = 0; s < S; ++s) max_rb = std::max(max_rb, st.r_max[s] * st.b_max[s]);
+    // a scan's member slots: room for a full batch per replica, and not so little that a step over small batches runs
+    // out of slots (64 slots of 8)
+    const uint32_t slot_words = (uint32_t)align_up(std::max(max_rb, 512u), 64);
+    P.slot_words = slot_words;
     // A bounded ring must take a whole group of batches that complete together (<= R*B members)
     // while its consumer still holds back a look-ahead window, and a merge wants 64 x sources free.
     // Beyond that need, longer rings let an operation run longer before it has to hand over to its neighbour:
@@ -176,9 +180,9 @@ int build_plan(estimator *h, const EstStatus &st, uint64_t n, PlanOut &po, bool 
             op.r_max = st.r_max[c];
             op.b_max = st.b_max[c];
             op.rep_off = (uint32_t)po.sz.rep_words;
-            po.sz.rep_words += 3ull * op.r_max;
+            po.sz.rep_words += EST_REP_WORDS;
             op.slot_off = po.sz.slot_words;
-            po.sz.slot_words += (uint64_t)op.r_max * op.b_max;
+            po.sz.slot_words += slot_words;
         }
     }
     P.n_ops = no;
@@ -206,8 +210,8 @@ int build_plan(estimator *h, const EstStatus &st, uint64_t n, PlanOut &po, bool 
     for (uint32_t i = 0; i < no; ++i) P.max_src = std::max(P.max_src, P.ops[i].n_src);
     // the scans' in-ring: 256 keys, or 128 where that lets one more wavefront share a SIMD (the smaller ring is
     // refilled twice as often, which costs less than the extra wavefront brings)
-    const uint32_t lds256 = (uint32_t)align_up(std::max<uint64_t>(EST_LDS_MERGE_BYTES(P.max_src), EST_LDS_SCAN_BYTES(max_rb, 256u)), 256);
-    const uint32_t lds128 = (uint32_t)align_up(std::max<uint64_t>(EST_LDS_MERGE_BYTES(P.max_src), EST_LDS_SCAN_BYTES(max_rb, 128u)), 256);
+    const uint32_t lds256 = (uint32_t)align_up(std::max<uint64_t>(EST_LDS_MERGE_BYTES(P.max_src), EST_LDS_SCAN_BYTES(slot_words, 256u)), 256);
+    const uint32_t lds128 = (uint32_t)align_up(std::max<uint64_t>(EST_LDS_MERGE_BYTES(P.max_src), EST_LDS_SCAN_BYTES(slot_words, 128u)), 256);
     P.scan_ring = estbe::waves_per_simd(lds128) > estbe::waves_per_simd(lds256) ? 128u : 256u;
     if (const char *e = getenv("EST_SCAN_RING"))  // for tests: 128 or 256
         if (atoi(e) == 128 || atoi(e) == 256) P.scan_ring = (uint32_t)atoi(e);
@@ -1188,7 +1192,7 @@ uint64_t estimator_workspace_bytes(const estimator_t *h, uint64_t n, uint64_t n_
     const uint64_t cap_b = pow2ceil(EST_MAX_REPLICAS * EST_MAX_BATCH + 64 * EST_KMAX + 65);
     uint64_t per_cfg = (4ull * EST_MAX_RINGS + EST_MAX_EDGES + EST_MAX_OPS) * 4;
     per_cfg += (uint64_t)S * (std::max(cap_b, pow2ceil(std::max<uint64_t>(n, 1))) + cap_b) * 8;
-    per_cfg += (uint64_t)S * (2 * EST_MAX_REPLICAS + EST_MAX_REPLICAS * EST_MAX_BATCH) * 4;
+    per_cfg += (uint64_t)S * (EST_REP_WORDS + EST_MAX_REPLICAS * EST_MAX_BATCH) * 4;
     // time tables of joins: a stage (or the sink) can be fed by several streams at once when it has several
     // parents, or a parent that has (a query that skips that parent takes its ready time from further up);
     // one table per stream, at most EST_KMAX and at most one per ancestor plus the arrivals

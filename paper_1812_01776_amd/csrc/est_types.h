@@ -15,7 +15,8 @@
 #define EST_TRACE_BIT 32        // bit of the "arrival trace" pseudo-source in a source set
 #define EST_SRC_TRACE (-1)
 #define EST_LDS_MERGE_BYTES(k) ((k) * 1664u)   // LDS of one wavefront for a k-source merge: staged keys 128 x 8, passed-on keys 64 x 8, accept masks 128 per source
-#define EST_LDS_SCAN_BYTES(rb, ring) (1440u + 8u * (ring) + 4u * (rb))   // ... for a scan whose replica slots hold rb members and whose in-ring holds ring keys (128 or 256)
+#define EST_LDS_SCAN_BYTES(sw, ring) (8u * (ring) + 4u * (sw))   // ... for a scan with sw words of member slots and an in-ring of ring keys (128 or 256)
+#define EST_REP_WORDS 196           // one scan's saved registers: free times, completion times and infos of the pending batches (64 each), their number
 
 enum { EST_OP_SCAN = 0, EST_OP_MERGE = 1, EST_OP_LAT = 2 };
 
@@ -40,10 +41,10 @@ struct EstOp {
     uint32_t tab_mask;            // MERGE/LAT: bit j = source j feeds some query together with another source and has a
                                   // table (uint32 [tab_len], indexed by query: the time of the query's element in source j)
     uint32_t tab_len;             // MERGE/LAT: entries of one table (queries, rounded up)
-    uint32_t rep_off;             // SCAN: word offset of the replica table inside one candidate's area
-    uint32_t r_max;               // SCAN: replica table width (largest replica count of the stage in this run)
+    uint32_t rep_off;             // SCAN: word offset of the scan's saved registers (EST_REP_WORDS) inside one candidate's area
+    uint32_t r_max;               // SCAN: largest replica count of the stage in this run
     uint64_t slot_off;            // SCAN: word offset of the member slots inside one candidate's slot area
-    uint32_t b_max;               // SCAN: slot width (largest max-batch of the stage in this run)
+    uint32_t b_max;               // SCAN: largest maximum batch size of the stage in this run
     uint32_t filtered;            // SCAN: only the source elements whose accept mask has bit 0 set visit the stage
     uint32_t owner;               // which wavefront of the workgroup runs the operation when a candidate has several (0 .. EST_MW_WAVES-1)
     uint32_t pad;
@@ -52,7 +53,7 @@ struct EstOp {
 struct EstPlan {
     uint32_t n_ops, n_rings, n_edges, state_words;
     // state words of one candidate: wr[n_rings] | fin[n_rings] | rd[n_edges] | opdone[n_ops] | miss, latency count | pub[n_rings]
-    uint32_t wr_off, fin_off, rd_off, done_off, miss_off, max_src, pub_off, scan_ring;  // max_src: widest merge; pub: published prefix of each ring; scan_ring: keys in a scan's LDS in-ring
+    uint32_t wr_off, fin_off, rd_off, done_off, miss_off, max_src, pub_off, scan_ring, slot_words, pad;  // max_src: widest merge; pub: published prefix of each ring; scan_ring: keys in a scan's LDS in-ring; slot_words: words of a scan's member slots
     EstOp ops[EST_MAX_OPS];
     EstRing rings[EST_MAX_RINGS];
 };

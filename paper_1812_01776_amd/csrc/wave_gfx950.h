@@ -83,6 +83,12 @@ EST_DEV uint32_t flag_ge(uint32_t a, uint32_t b) {
     asm("s_cmp_ge_u32 %1, %2\n\ts_cselect_b32 %0, 1, 0" : "=s"(r) : "s"(a), "s"(b) : "scc");
     return r;
 }
+EST_DEV uint32_t flag_eq(uint32_t a, uint32_t b) {
+    uint32_t r;
+    a = uniform(a); b = uniform(b);
+    asm("s_cmp_eq_u32 %1, %2\n\ts_cselect_b32 %0, 1, 0" : "=s"(r) : "s"(a), "s"(b) : "scc");
+    return r;
+}
 EST_DEV uint32_t flag_lt(uint32_t a, uint32_t b) {
     uint32_t r;
     a = uniform(a); b = uniform(b);
@@ -116,6 +122,66 @@ EST_DEV uint32_t sat_add_uniform(uint32_t t, uint32_t d) {
     t = uniform(t); d = uniform(d);
     asm("s_add_u32 %0, %1, %2\n\ts_cselect_b32 %0, -1, %0" : "=s"(r) : "s"(t), "s"(d) : "scc");
     return r;
+}
+
+// The batch-by-batch recurrence of a batched queue, for as many batches as the window decides.  rdy: ready times of the
+// window's queries, ascending (2^32-1 in the lanes beyond the window's w queries); F: the times the replicas are free
+// again, ascending, 2^32-1 beyond the last one; Lrot: lane l holds the latency of a batch of l queries (lane 0 that of 64).
+// A batch starts at T = max(earliest free time, ready time of query a), takes the queries ready by then, up to B, and
+// completes at e = T + latency, at most 2^32-1; e goes into the sorted F in place of the earliest entry (with the right
+// neighbour n of every lane: max(F, min(n, e)), which is n below the place of e, e at it and F above it).  Every batch
+// leaves e and its first query in lane K of gend and vA and a bit at its first query in heads.  The loop ends when the
+// window or the lanes below K_end are used up, or before a batch that is not full while wf or more queries are ready (more
+// members may follow).  Batches that start at 2^32-1 may count lanes beyond the window: a can end up larger than w.
+// What bounds it is the latency of one chain: 23 instructions per batch, one taken branch.  Compiled from C++ the loop had
+// twice the instructions and four taken branches (310 cycles per batch on an idle compute unit).  Wait states: the
+// DPP source F and the lane reads' sources were written at least two instructions earlier, lane selects come from scalar
+// instructions.
+EST_DEV void form_batches(uint32_t rdy, uint32_t Lrot, uint32_t B, uint32_t w, uint32_t wf, uint32_t K_end, uint32_t &F, uint32_t &gend,
+                          uint32_t &vA, uint64_t &heads, uint32_t &a, uint32_t &K) {
+    uint32_t t, u, c, x, m;
+    B = uniform(B); w = uniform(w); wf = uniform(wf); K_end = uniform(K_end);
+    asm volatile("s_mov_b32 %[m], m0\n\t"
+                 "s_mov_b32 m0, %[K]\n\t"
+                 "s_nop 1\n"
+                 "1:\n\t"
+                 "v_readfirstlane_b32 %[t], %[F]\n\t"
+                 "v_readlane_b32 %[u], %[rdy], %[a]\n\t"
+                 "s_max_u32 %[t], %[t], %[u]\n\t"
+                 "v_cmp_ge_u32 vcc, %[t], %[rdy]\n\t"
+                 "s_bcnt1_i32_b64 %[c], vcc\n\t"
+                 "s_sub_u32 %[u], %[c], %[a]\n\t"
+                 "s_min_u32 %[u], %[u], %[B]\n\t"
+                 "s_cmp_ge_u32 %[c], %[wf]\n\t"
+                 "s_cbranch_scc1 3f\n"
+                 "2:\n\t"
+                 "v_readlane_b32 %[c], %[L], %[u]\n\t"
+                 "v_writelane_b32 %[vA], %[a], m0\n\t"
+                 "s_bitset1_b64 %[heads], %[a]\n\t"
+                 "s_add_u32 %[t], %[t], %[c]\n\t"
+                 "s_cselect_b32 %[t], -1, %[t]\n\t"
+                 "v_mov_b32 %[x], %[t]\n\t"
+                 "v_writelane_b32 %[gend], %[t], m0\n\t"
+                 "s_add_u32 m0, m0, 1\n\t"
+                 "v_min_u32_dpp %[x], %[F], %[x] wave_shl:1 row_mask:0xf bank_mask:0xf\n\t"
+                 "s_add_u32 %[a], %[a], %[u]\n\t"
+                 "s_cmp_lt_u32 %[a], %[w]\n\t"
+                 "v_max_u32 %[F], %[F], %[x]\n\t"
+                 "s_cbranch_scc0 4f\n\t"
+                 "s_cmp_lt_u32 m0, %[Ke]\n\t"
+                 "s_cbranch_scc1 1b\n\t"
+                 "s_branch 4f\n"
+                 "3:\n\t"
+                 "s_cmp_eq_u32 %[u], %[B]\n\t"
+                 "s_cbranch_scc1 2b\n"
+                 "4:\n\t"
+                 "s_mov_b32 %[K], m0\n\t"
+                 "s_mov_b32 m0, %[m]\n\t"
+                 "s_nop 1"
+                 : [F] "+v"(F), [gend] "+v"(gend), [vA] "+v"(vA), [heads] "+s"(heads), [a] "+s"(a), [K] "+s"(K), [t] "=&s"(t), [u] "=&s"(u),
+                   [c] "=&s"(c), [x] "=&v"(x), [m] "=&s"(m)
+                 : [rdy] "v"(rdy), [L] "v"(Lrot), [B] "s"(B), [w] "s"(w), [wf] "s"(wf), [Ke] "s"(K_end)
+                 : "vcc", "scc");
 }
 
 EST_DEV uint32_t min_u32(uint32_t v) {

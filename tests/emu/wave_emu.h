@@ -110,6 +110,7 @@ EST_DEV uint32_t set_lane(uint32_t v, uint32_t x, uint32_t l) {
     return emu::lane() == l ? x : v;
 }
 EST_DEV uint32_t flag_ge(uint32_t a, uint32_t b) { check_uniform2(a, b, "flag_ge"); return a >= b ? 1u : 0u; }
+EST_DEV uint32_t flag_eq(uint32_t a, uint32_t b) { check_uniform2(a, b, "flag_eq"); return a == b ? 1u : 0u; }
 EST_DEV uint32_t flag_lt(uint32_t a, uint32_t b) { check_uniform2(a, b, "flag_lt"); return a < b ? 1u : 0u; }
 EST_DEV uint32_t flag_ne_and_ge(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
     check_uniform2(a, b, "flag_ne_and_ge");
@@ -126,6 +127,29 @@ EST_DEV uint32_t sat_add_uniform(uint32_t t, uint32_t d) {
 }
 
 EST_DEV uint32_t uniform(uint32_t v) { return (uint32_t)emu::exchange(v, 4)[0]; }
+
+EST_DEV void form_batches(uint32_t rdy, uint32_t Lrot, uint32_t B, uint32_t w, uint32_t wf, uint32_t K_end, uint32_t &F, uint32_t &gend,
+                          uint32_t &vA, uint64_t &heads, uint32_t &a, uint32_t &K) {
+    check_uniform2(B, w, "form_batches");
+    check_uniform2(wf, K_end, "form_batches");
+    check_uniform2(a, K, "form_batches");
+    EST_CHECK(a < w && K < K_end && K_end <= 64);
+    do {
+        const uint32_t f = bcast(F, 0), r = bcast(rdy, a), T = f > r ? f : r;
+        const uint32_t c = (uint32_t)__builtin_popcountll(ballot(rdy <= T));
+        const uint32_t b = c - a < B ? c - a : B;
+        if (c >= wf && b != B) break;
+        const uint32_t e = sat_add_uniform(T, bcast(Lrot, b & 63u));
+        gend = set_lane(gend, e, K);
+        vA = set_lane(vA, a, K);
+        heads |= 1ull << a;
+        const uint64_t *x = emu::exchange(F, 19);
+        const uint32_t l = emu::lane(), n = l == 63 ? 0xFFFFFFFFu : (uint32_t)x[l + 1], m = n < e ? n : e;
+        F = F > m ? F : m;
+        a += b;
+        ++K;
+    } while (a < w && K < K_end);
+}
 
 EST_DEV uint32_t min_u32(uint32_t v) {
     const uint64_t *x = emu::exchange(v, 5);

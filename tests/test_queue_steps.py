@@ -1,0 +1,73 @@
+"""The scan's steps at the sizes where they can go wrong: one replica, as many replicas as lanes, batches from 2 to 64, more
+pending batches than a step has slots for, groups of more than 64 queries that leave together, free times at the clock's
+horizon, a window cut short by the end of the input.  Every per-query latency is compared with the CPU oracle; the
+kernel logic also runs under the CPU emulation with its consistency checks on."""
+import numpy as np
+import pytest
+
+import emu_lib
+from oracle import oracle
+from paper_1812_01776_amd import estimator as binding
+from paper_1812_01776_amd import workloads
+
+# (replicas, largest batch, offered load, quantum of all times in us)
+SIZES = [(1, 2, 0.9, 1), (1, 64, 1.1, 1), (2, 3, 0.95, 1), (3, 64, 0.8, 10), (5, 4, 1.0, 1), (16, 64, 0.9, 100), (17, 5, 0.97, 1),
+         (31, 8, 0.7, 10), (33, 2, 1.02, 1), (63, 2, 0.9, 1), (64, 2, 0.95, 100), (64, 8, 0.85, 1), (64, 64, 0.9, 1000)]
+
+
+def _queue_case(seed, R, B, load, quantum, n, burst=1, start=0):
+    """A two-stage chain, then a fork and join whose branches are taken by some; every stage has R replicas and batches up to B."""
+    rng = np.random.default_rng(7000 + seed)
+    parents = [[], [0], [1], [1], [2, 3]]
+    S = len(parents)
+    lat = np.zeros((S, 1, B), np.uint32)
+    for s in range(S):
+        a, c = rng.integers(300, 3000), rng.integers(20, 300)
+        lat[s, 0] = np.maximum((a + c * np.arange(1, B + 1)) // quantum * quantum, quantum)
+    gap = float(lat[:, 0, B - 1].max()) / (R * B) / load
+    gaps = np.rint(rng.gamma(0.5, 2.0 * gap, size=n)).astype(np.int64)
+    if burst > 1:
+        gaps = np.where(np.arange(n) % burst == 0, gaps * burst, 0)
+    arr = np.cumsum(gaps // quantum * quantum)
+    if start:  # queueing runs into the horizon
+        arr = arr + (2**32 - 2 - int(arr[-1]) - int(lat.max(axis=2).sum()) - 2 * int(lat.max()))
+    mask = np.full(n, 0b10011, np.uint32)
+    mask |= (rng.random(n) < 0.7).astype(np.uint32) << 2
+    mask |= (rng.random(n) < 0.6).astype(np.uint32) << 3
+    cost = np.full((S, 1), 3, np.uint64)
+    one = np.ones((1, S), np.int64)
+    return workloads.Workload("queue%d" % seed, parents, lat, cost, arr.astype(np.uint32), mask, (one * 0).astype(np.uint8),
+                              (one * B).astype(np.uint8), (one * R).astype(np.uint16), int(lat.max()) * 2)
+
+
+def _compare(w, est):
+    cfg = binding.pack_configs(w.cfg_hw, w.cfg_batch, w.cfg_replicas)
+    ref = oracle.run(w.parents, w.lat_us, w.cost_uusd_hr, w.arrival_us, w.visit_mask, w.cfg_hw, w.cfg_batch,
+                     w.cfg_replicas, w.slo_us, want_latencies=True)
+    assert np.array_equal(est.run_latencies(w.arrival_us, w.visit_mask, cfg).astype(np.uint64), ref["latency"])
+    got = est.run(w.arrival_us, w.visit_mask, cfg, w.slo_us)
+    assert np.array_equal(got["p99_us"].astype(np.uint64), ref["p99_us"])
+    assert np.array_equal(got["miss_count"].astype(np.uint64), ref["miss_count"])
+
+
+def _cases(i, n):
+    R, B, load, quantum = SIZES[i]
+    yield _queue_case(i, R, B, load, quantum, n)
+    yield _queue_case(100 + i, R, B, load, quantum, n, burst=130)         # groups of 130 cut into batches that tie
+    yield _queue_case(200 + i, R, B, 1.3 * load, quantum, n + 1, start=1)
+
+
+@pytest.mark.parametrize("i", range(len(SIZES)))
+def test_steps_at_the_edges_emulated(i):
+    for w in _cases(i, 421):
+        _compare(w, emu_lib.make(w))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 5000])
+@pytest.mark.parametrize("i", range(len(SIZES)))
+def test_steps_at_the_edges_gpu(i, n):
+    for w in _cases(i, n):
+        est = binding.Estimator(w.parents, w.lat_us, w.cost_uusd_hr)
+        _compare(w, est)
+        est.close()
