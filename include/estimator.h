@@ -91,14 +91,14 @@ typedef struct {
 /* Timing of the most recent run, measured with HIP events on the run's stream. */
 typedef struct {
     uint32_t n_launches;      /* launches of the simulation kernel                                    */
-    uint32_t n_slots;         /* wavefronts (each with its own scratch) that shared the candidates    */
+    uint32_t n_slots;         /* scratch slots: candidates in flight at a time                        */
     float sim_ms;             /* duration of the simulation kernel (simulation + P99 selection)       */
     float prep_ms;            /* trace / configuration preprocessing kernels                          */
     uint64_t stage_visits;    /* sum over stages of queries visiting the stage (per candidate)        */
     uint64_t workspace_bytes; /* device scratch used                                                  */
     float capture_ms;         /* estimator_run_shared_dev: the launch that simulates the bases (part of sim_ms) */
     float ops_run_fraction;   /* estimator_run_shared_dev: operations run / (candidates x operations); else 0    */
-    uint32_t waves_per_candidate; /* 1, or 2 or 4 when the call had so few candidates that each was given a workgroup */
+    uint32_t waves_per_candidate; /* wavefronts there were for every candidate in flight: 1, 2 (to 3) or 4 (or more) */
     uint32_t reserved;
 } est_stats_t;
 

@@ -1,5 +1,5 @@
-// Device code of the batched Estimator: one 64-lane wavefront simulates one candidate
-// configuration end to end.  Written against the wv:: primitives only, so that the same text
+// Device code of the batched Estimator: the 64-lane wavefronts of a workgroup simulate a few candidate
+// configurations end to end.  Written against the wv:: primitives only, so that the same text
 // also compiles for a lock-step CPU emulation used by the host-side checks of the kernel logic.
 //
 // The simulated system is the centralized batched queue of arXiv 1812.01776 (Section 3, serving
@@ -22,9 +22,9 @@
 //          SLO miss count (Section 2: latencies must be below the constraint).
 //
 // Streams are per-candidate rings of 64-bit keys (time << 32 | query index) in global memory,
-// so that comparing keys compares (time, query index).  All operations of a candidate are run
-// round-robin by its wavefront until every stream is drained; an operation stops when it needs
-// input that is not there yet or output space that is not free yet.
+// so that comparing keys compares (time, query index).  An operation runs until it needs input that is not
+// there yet or output space that is not free yet, and tells its neighbours on the way how far it is; who runs which
+// operation when is the driver's business (below).
 #pragma once
 #include "est_types.h"
 
@@ -63,18 +63,18 @@ struct Ctx {
 };
 
 // Diagnostics record of candidate t and stage s: EST_DBG_WORDS words (unused, ticks in the stage's scan, steps,
-// queries in steps, of which: unused, unused, one-per-batch, batch by batch; then ticks spent in steps that ended as:
-// unused, unused, one-per-batch, batch by batch, backlog or horizon, unused; then ticks in the batch-by-batch recurrence
-// and the batches it formed).
+// queries in steps, of which: batch by batch with four or more queries per batch, unused, one-per-batch, batch by batch
+// otherwise; then ticks spent in steps of the kinds: batch by batch with four or more, unused, one-per-batch, batch by
+// batch otherwise, backlog or horizon, unused; then ticks in the batch-by-batch recurrence and the batches it formed).
 // The record of stage EST_MAX_STAGES-1 holds what belongs to no stage: ticks in merges, in the sink, in the
 // selection, merge rounds, merge output elements, merge calls, scan calls.
 EST_DEV uint64_t *est_dbg_rec(const EstSimArgs *a, uint32_t t, uint32_t s) {
     return a->dbg_ticks + a->n_cfg + ((uint64_t)t * EST_MAX_STAGES + s) * EST_DBG_WORDS;
 }
 
-// Ring cursors and the other state words of a candidate are written by the operation that owns them and read
-// by its neighbours, which may run in another wavefront of the workgroup (several wavefronts per candidate):
-// they are read and written through these (the value is the same in every lane).
+// Ring cursors and the other state words of a candidate, in LDS, are written by the operation that owns them and read
+// by its neighbours, which may run in another wavefront of the workgroup at the same time: they are read and written
+// through these (the value is the same in every lane).
 EST_DEV uint32_t ld_st(const uint32_t *p) { return wv::load_shared(p); }
 EST_DEV void st_st(uint32_t *p, uint32_t v) { wv::store_shared(p, v); }
 
@@ -95,13 +95,13 @@ EST_DEV View view_of(const Ctx &c, int32_t ring) {
         const EstRing &R = c.a->cap_plan->rings[ring];
         v.base = c.cap_rings + R.off;
         v.mask = R.cap_mask;
-        v.wr = c.st[c.P->wr_off + ring];
+        v.wr = ld_st(&c.st[c.P->wr_off + ring]);
         v.fin = 1;
     } else {
         const EstRing &R = c.P->rings[ring];
         v.base = c.rings + R.off;
         v.mask = R.cap_mask;
-        v.fin = ld_st(&c.st[c.P->fin_off + ring]);  // (before the cursor: a stream seen as ended is seen whole)
+        v.fin = ld_st(&c.st[c.P->fin_off + ring]) != 0u;  // (before the cursor: a stream seen as ended is seen whole)
         v.wr = ld_st(&c.st[c.P->wr_off + ring]);
     }
     return v;
@@ -327,8 +327,11 @@ EST_DEV uint32_t emit_pending(uint32_t B, uint32_t *lslots, uint32_t nE, uint32_
     return nE;
 }
 
+enum { PUBLISH = 256 };  // elements a scan writes before it tells its neighbours
+
+// Returns whether the operation has finished for good.
 template <bool DIAG, bool MEMO>
-EST_DEV bool scan_run(const Ctx &c, const EstOp &op, uint32_t opi) {
+EST_DEV bool scan_run(const Ctx &c, const EstOp &op) {
     const uint32_t ln = wv::lane();
     const EstPlan &P = *c.P;
     const uint32_t s = op.stage;
@@ -346,7 +349,7 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op, uint32_t opi) {
     const uint32_t SW = wv::uniform(P.slot_words);
     const uint32_t nslots = umin(64u, SW / B);  // (at least R)
     EST_CHECK(nslots >= R);
-    uint32_t *g_free = c.rep + op.rep_off, *g_end = g_free + 64, *g_info = g_free + 128, *g_n = g_free + 192;
+    uint32_t *g_free = c.rep + op.rep_off, *g_end = g_free + 64, *g_info = g_free + 128, *g_n = g_free + 192;  // g_n: pending batches, staged keys
     uint32_t *g_slots = c.slots + op.slot_off;
     uint64_t *lkey = c.lds;
     const uint32_t RING = wv::uniform(P.scan_ring), rmask = RING - 1u;
@@ -358,9 +361,12 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op, uint32_t opi) {
     const bool isrep = ln < R;
     uint32_t F = isrep ? g_free[ln] : 0xFFFFFFFFu;
     uint32_t gend = g_end[ln], ginfo = g_info[ln];
-    uint32_t nG = wv::uniform(*g_n);
+    uint32_t nG = wv::uniform(g_n[0]);
+    uint32_t lhead = 0, ltail = wv::uniform(g_n[1]);  // in-ring: consumed / filled
+    uint64_t *g_keys = (uint64_t *)(g_slots + SW);
     if (nG)  // members still pending: back into LDS
         for (uint32_t i = ln; i < SW; i += 64) lslots[i] = g_slots[i];
+    for (uint32_t i = ln; i < ltail; i += 64) lkey[i] = g_keys[i];  // and what had been staged
     wv::sync_lds();
 
     View in = view_of<MEMO>(c, op.src_ring[0]);
@@ -368,21 +374,20 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op, uint32_t opi) {
     in.wr = wv::uniform(in.wr);
     in.fin = wv::uniform(in.fin);
     uint32_t rraw = wv::uniform(c.st[P.rd_off + op.src_edge[0]]);  // next source position to read
-    const uint32_t rd_entry = rraw;
-    uint32_t lhead = 0, ltail = 0;                     // in-ring: consumed / filled
     const EstRing &OR = P.rings[op.out_ring];
     uint64_t *out = c.rings + OR.off;
     const uint32_t omask = wv::uniform(OR.cap_mask);
     uint32_t wr = wv::uniform(c.st[P.wr_off + op.out_ring]);
     uint32_t space = wv::uniform(ring_space(c, op.out_ring, wr));
-    bool progress = false, finished = false;
+    bool finished = false;
+    uint32_t wr_pub = wr;  // what the readers have been told
     EST_CHK_ORDER_INIT();  // (host-side emulation only: everything written from here on is verified to be in order, step by step)
     uint32_t sat_skip = 0;     // steps to go before the backlog front end is tried again
     uint32_t single_skip = 0;  // the same for one query per batch
     uint32_t cf_skip = 0;      // and for its closed forms
     uint64_t d_blkl = 0, d_blkk = 0;  // diagnostics: ticks in the batch-by-batch recurrence, batches it formed
     uint64_t d_tk[6] = {0, 0, 0, 0, 0, 0}, tk0 = 0;  // diagnostics: ticks by the kind of step that ended the iteration
-    uint32_t d_b1 = 0, d_b1e = 0, d_sat = 0, d_sate = 0, d_hz = 0, d_blk = 0, d_blke = 0;  // diagnostics
+    uint32_t d_b1 = 0, d_b1e = 0, d_sat = 0, d_sate = 0, d_hz = 0, d_blk = 0, d_blke = 0, d_grp = 0, d_grpe = 0;  // diagnostics
 
     for (;;) {
         uint32_t staged = ltail - lhead;
@@ -414,13 +419,36 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op, uint32_t opi) {
             if (a2) lkey[i2] = k2;
             rraw += w0 + w1 + w2;
             EST_CHECK(ltail - lhead <= RING);
+            // What has been written so far is in place (the loads just waited for were issued after it): tell the readers,
+            // and the producer what has been read, so that both can run beside this operation.
+            if (wr - wr_pub >= PUBLISH) {
+                wv::sync();
+                if (ln == 0) {
+                    st_st(&c.st[P.wr_off + op.out_ring], wr);
+                    st_st(&c.st[P.rd_off + op.src_edge[0]], rraw);
+                }
+                wr_pub = wr;
+            }
             wv::sync_lds();
             continue;
+        }
+        if (staged < 64 && !in.fin) {
+            // the producer may have gone on meanwhile
+            const uint32_t fin2 = wv::uniform(ld_st(&c.st[P.fin_off + op.src_ring[0]])), wr2 = wv::uniform(ld_st(&c.st[P.wr_off + op.src_ring[0]]));
+            if (fin2 || wr2 != in.wr) {
+                in.fin = fin2 ? 1u : 0u;
+                in.wr = wr2;
+                wv::sync();
+                continue;
+            }
         }
         if (staged == 0 && !in.fin) break;
         // a step may pass on a window of 64 queries: with less room than that in the output ring, let the reader run
         // first rather than squeeze batches through
-        if (staged != 0 && space < 64u) break;
+        if (staged != 0 && space < 64u) {
+            space = wv::uniform(ring_space(c, op.out_ring, wr));  // the reader may have gone on meanwhile
+            if (space < 64u) break;
+        }
         if (DIAG) tk0 = wv::ticks();
         const uint32_t w = umin(staged, 64u);
         const uint64_t key = ln < w ? lkey[(lhead + ln) & rmask] : ~0ull;
@@ -438,7 +466,6 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op, uint32_t opi) {
                 const uint32_t d = emit_pending(B, lslots, nE, gend, ginfo, out, omask, wr, space);
                 EST_CHK_ORDER(4);
                 if (d) {
-                    progress = true;
                     nG -= d;
                     // the batches passed on go to the end of the lanes: their slots are free
                     const uint32_t src = ln + d < nslots ? ln + d : ln + d - nslots;
@@ -464,12 +491,11 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op, uint32_t opi) {
             lhead += m;
             d_hz += m;
             if (DIAG) d_tk[4] += wv::ticks() - tk0;
-            progress = true;
             continue;
         }
         const uint32_t last = wv::flag_ge(64u, staged) & wv::flag_eq(rraw, in.wr) & in.fin;  // the window holds the end of the input
         if (nG == 0 && L1 > 0 && mono) {
-            if (space < 64u) break;
+            if (space < 64u) continue;
             if (cf_skip == 0 && w >= 32 && R <= 31) {
                 // Closed forms for a whole window of queries that are each a batch of their own, checked with one
                 // vote and left to the steps below when they do not hold.  Query i runs on the replica that served
@@ -507,7 +533,6 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op, uint32_t opi) {
                     lhead += m;
                     ++d_b1; d_b1e += m;
                     if (DIAG) d_tk[2] += wv::ticks() - tk0;
-                    progress = true;
                     continue;
                 }
                 cf_skip = 6;
@@ -576,7 +601,6 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op, uint32_t opi) {
                     EST_CHECK(ln == 0 || !isrep || F >= fbefore);
                     (void)fbefore;
                     lhead += m;
-                    progress = true;
                     continue;
                 }
             }
@@ -638,6 +662,7 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op, uint32_t opi) {
             const uint32_t anext = wv::shl1(vA);
             const uint32_t cnt = (ln + 1u == K ? a : anext) - vA;
             if (ln >= nG && ln < K) ginfo = (ginfo & 0xFFu) | (cnt << 8);
+            if (kind == 3 && a >= 4u * (K - nG)) kind = 0;
             nG = K;
             EST_CHECK(nG <= nslots);
             const uint32_t gprev = wv::shr1(gend);
@@ -655,68 +680,35 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op, uint32_t opi) {
             }
             wv::sync_lds();
             lhead += a;
-            progress = true;
-            if (kind == 4) { ++d_sat; d_sate += a; } else { ++d_blk; d_blke += a; }
+            if (kind == 4) { ++d_sat; d_sate += a; } else if (kind == 0) { ++d_grp; d_grpe += a; } else { ++d_blk; d_blke += a; }
             if (DIAG) d_tk[kind] += wv::ticks() - tk0;
         }
     }
 
     if (DIAG && c.a->dbg_ticks && ln == 0) {
         uint64_t *pc = est_dbg_rec(c.a, c.t, s);  // per candidate and stage (one writer: no atomics)
-        pc[2] += d_b1 + d_sat + d_blk; pc[3] += d_b1e + d_sate + d_hz + d_blke;
-        pc[6] += d_b1e; pc[7] += d_blke;
+        pc[2] += d_b1 + d_sat + d_blk + d_grp; pc[3] += d_b1e + d_sate + d_hz + d_blke + d_grpe;
+        pc[4] += d_grpe; pc[6] += d_b1e; pc[7] += d_blke;
         for (uint32_t i = 0; i < 6; ++i) pc[8 + i] += d_tk[i];
         pc[14] += d_blkl; pc[15] += d_blkk;
-        uint64_t *po = est_dbg_rec(c.a, c.t, EST_MAX_STAGES - 1);
-        po[6] += 1;
+        wv::atomic_add_u64(&est_dbg_rec(c.a, c.t, EST_MAX_STAGES - 1)[6], 1);
     }
     // back to memory: the free times, the pending batches and their members, the cursors
     if (isrep) g_free[ln] = F;
     g_end[ln] = gend;
     g_info[ln] = ginfo;
-    if (ln == 0) *g_n = nG;
+    const uint32_t left_over = ltail - lhead;
+    if (ln == 0) { g_n[0] = nG; g_n[1] = left_over; }
     if (nG)
         for (uint32_t i = ln; i < SW; i += 64) g_slots[i] = lslots[i];
-    // Staged but unconsumed queries are read again next time: the read cursor goes back to the first of
-    // them.  Without a filter that is simply their number of places back; with one, the source is walked
-    // backwards, a window at a time, until that many accepted queries have been passed.
-    uint32_t cursor = rraw;
-    {
-        uint32_t need = ltail - lhead;
-        if (!filtered) {
-            cursor = rraw - need;
-        } else {
-            while (need > 0) {
-                const uint32_t wb = umin(64u, cursor - rd_entry);  // (never back beyond where this call started)
-                EST_CHECK(wb > 0);
-                const uint32_t from = cursor - wb;
-                const uint64_t kb = ln < wb ? in.base[(from + ln) & in.mask] : 0ull;
-                const uint64_t Ab = lanes_below(wb) & wv::ballot((acc[(uint32_t)kb] & 1u) != 0u);
-                const uint32_t have = popc64(Ab);
-                if (have < need) {
-                    need -= have;
-                    cursor = from;
-                    continue;
-                }
-                // the need-th accepted query from the top of this window
-                uint64_t rest = Ab;
-                for (uint32_t i = have; i > need; --i) rest &= rest - 1;  // drop the accepted ones below it
-                cursor = from + ctz64(rest);
-                need = 0;
-            }
-        }
-    }
+    for (uint32_t i = ln; i < left_over; i += 64) g_keys[i] = lkey[(lhead + i) & rmask];
     wv::sync();  // what was written to the output ring is in place before its cursor moves
     if (ln == 0) {
-        st_st(&c.st[P.rd_off + op.src_edge[0]], cursor);
+        st_st(&c.st[P.rd_off + op.src_edge[0]], rraw);
         st_st(&c.st[P.wr_off + op.out_ring], wr);
-        if (finished) {
-            st_st(&c.st[P.fin_off + op.out_ring], 1);
-            c.st[P.done_off + opi] = 1;
-        }
+        if (finished) st_st(&c.st[P.fin_off + op.out_ring], EST_FIN);
     }
-    wv::sync();
-    return progress;
+    return finished;
 }
 
 // ------------------------------------------------------------------------------------------ MERGE
@@ -727,10 +719,12 @@ EST_DEV uint64_t eff_key(uint64_t key, uint32_t j, uint32_t l) {
     return (uint32_t)(key >> 32) == 0xFFFFFFFFu ? (0xFFFFFFFF00000000ull | (uint64_t)(j << 8) | l) : key;
 }
 
-enum { MERGE_RING = 128, MERGE_GROUP = 4 };  // staged elements per source of a merge (LDS ring); sources whose loads are issued together
+// Staged elements per source of a merge (LDS ring), how many of them a round looks at, sources whose loads are issued
+// together.  (62 and not 64: a merge of four then fits the LDS of six wavefronts per SIMD.)
+enum { MERGE_RING = 128, MERGE_WIN = 62, MERGE_GROUP = 4 };
 
 template <bool DIAG, bool MEMO>
-EST_DEV bool merge_run(const Ctx &c, const EstOp &op, uint32_t opi) {
+EST_DEV bool merge_run(const Ctx &c, const EstOp &op) {
     const uint32_t ln = wv::lane();
     const EstPlan &P = *c.P;
     const uint32_t K = wv::uniform(op.n_src);
@@ -747,18 +741,25 @@ EST_DEV bool merge_run(const Ctx &c, const EstOp &op, uint32_t opi) {
         wr = wv::uniform(c.st[P.wr_off + op.out_ring]);
         space = wv::uniform(ring_space(c, op.out_ring, wr));
     }
-    uint32_t miss = 0;
+    uint32_t miss = 0, wr_pub = wr;
     uint32_t d_rounds = 0, d_elems = 0;  // diagnostics
-    bool progress = false, finished = false;
+    bool finished = false;
 
     if (K == 1 && !op.has_cnt) {
         // one source, every query fed by it alone: filter and copy, four windows of 64 at a time (their
         // loads are issued together)
-        const View sv = uniform_view_of<MEMO>(c, op.src_ring[0]);
+        View sv = uniform_view_of<MEMO>(c, op.src_ring[0]);
         uint32_t rc = wv::uniform(c.st[P.rd_off + op.src_edge[0]]);
         const uint32_t slo = wv::uniform(c.a->slo_us);
         for (;;) {
-            if (!is_lat && space < 256u) break;  // wait for the consumer
+            if (!is_lat && space < 256u) {
+                space = wv::uniform(ring_space(c, op.out_ring, wr));
+                if (space < 256u) break;  // wait for the consumer
+            }
+            if (sv.wr - rc < 256u && !sv.fin) {  // the producer may have gone on meanwhile
+                sv = uniform_view_of<MEMO>(c, op.src_ring[0]);
+                wv::sync();
+            }
             if (rc == sv.wr) {
                 finished = sv.fin != 0;
                 break;
@@ -793,7 +794,14 @@ EST_UNROLL
                 if (!is_lat) space -= na;
             }
             rc += umin(left, 256u);
-            progress = true;
+            if (wr - wr_pub >= 2048u) {
+                wv::sync();
+                if (ln == 0) {
+                    if (!is_lat) st_st(&c.st[P.wr_off + op.out_ring], wr);
+                    st_st(&c.st[P.rd_off + op.src_edge[0]], rc);
+                }
+                wr_pub = wr;
+            }
         }
         if (ln == 0) st_st(&c.st[P.rd_off + op.src_edge[0]], rc);
     } else {
@@ -804,13 +812,13 @@ EST_UNROLL
         // consumed every element of the same query with a smaller key has been staged already, and an
         // element whose partner is unset or larger is not the last.  No counting, no read-modify-write.
         //
-        // LDS: per source a ring of MERGE_RING staged keys (uint64) | per source 64 passed-on keys (uint64) |
+        // LDS: per source a ring of MERGE_RING staged keys (uint64) | per source MERGE_WIN passed-on keys (uint64) |
         // per source MERGE_RING accept masks (uint8).  The per-source scalars live in two vector registers, one
         // lane per (field, source): reading one is a lane read into a scalar register, not a trip to LDS.
         const uint32_t KS = P.max_src;
         uint64_t *rkey = c.lds;
         uint64_t *lst = c.lds + KS * MERGE_RING;
-        uint8_t *racc = (uint8_t *)(lst + KS * 64);
+        uint8_t *racc = (uint8_t *)(lst + KS * MERGE_WIN);
         enum { F_RD = 0, F_WR = 8, F_FIN = 16, F_HEAD = 24, F_TAIL = 32, F_MASK = 40, F_BLO = 48, F_BHI = 56,  // va: lane = field + source
                F_NFIN = 0, F_CONS = 8 };                                                                    // vb: passed on / consumed this round
         uint32_t va = 0, vb = 0;
@@ -827,7 +835,10 @@ EST_UNROLL
             va = wv::set_lane(va, wv::uniform((uint32_t)(bp >> 32)), F_BHI + j);
         }
         for (;;) {
-            if (!is_lat && space < 64u * K) break;  // wait for the consumer
+            if (!is_lat && space < 64u * K) {
+                space = wv::uniform(ring_space(c, op.out_ring, wr));
+                if (space < 64u * K) break;  // wait for the consumer
+            }
             // ---- refill: every source with no more than a window staged takes up to 64 further elements; the
             //      loads of all sources are issued before any is used
             bool any = false;
@@ -874,6 +885,15 @@ EST_UNROLL
                     va = wv::set_lane(va, wv::bcast(va, F_RD + j) + wx[u], F_RD + j);
                 }
             }
+            if (wr - wr_pub >= 512u) {  // tell the neighbours how far this operation is
+                wv::sync();
+                for (uint32_t j = 0; j < K; ++j) {
+                    const uint32_t back = wv::bcast(va, F_RD + j) - (wv::bcast(va, F_TAIL + j) - wv::bcast(va, F_HEAD + j));
+                    if (ln == 0) st_st(&c.st[P.rd_off + op.src_edge[j]], back);
+                }
+                if (ln == 0 && !is_lat) st_st(&c.st[P.wr_off + op.out_ring], wr);
+                wr_pub = wr;
+            }
             if (any) wv::sync();  // (tables and staged elements: written above, read below by other lanes)
             // ---- the window of every source: its first 64 staged elements
             uint32_t more = 0, total = 0;  // more, bit j: source j may hold elements beyond its window
@@ -881,8 +901,8 @@ EST_UNROLL
             uint64_t bound = ~0ull;  // everything up to the smallest last key of a source that may hold more is final
             for (uint32_t j = 0; j < K; ++j) {
                 const uint32_t h = wv::bcast(va, F_HEAD + j), staged = wv::bcast(va, F_TAIL + j) - h;
-                const uint32_t w = umin(64u, staged);
-                const bool has_more = staged > 64u || wv::bcast(va, F_RD + j) != wv::bcast(va, F_WR + j) || !wv::bcast(va, F_FIN + j);
+                const uint32_t w = umin((uint32_t)MERGE_WIN, staged);
+                const bool has_more = staged > (uint32_t)MERGE_WIN || wv::bcast(va, F_RD + j) != wv::bcast(va, F_WR + j) || !wv::bcast(va, F_FIN + j);
                 if (has_more) more |= 1u << j;
                 total += w;
                 if (w == 0) {
@@ -898,8 +918,22 @@ EST_UNROLL
                 }
             }
             if (blocked || total == 0) {
-                if (!blocked) finished = more == 0;
-                break;
+                if (!blocked && more == 0) {
+                    finished = true;
+                    break;
+                }
+                // the producers may have gone on meanwhile
+                bool news = false;
+                for (uint32_t j = 0; j < K; ++j) {
+                    if (wv::bcast(va, F_FIN + j)) continue;
+                    const View sv = uniform_view_of<MEMO>(c, op.src_ring[j]);
+                    if (sv.wr != wv::bcast(va, F_WR + j) || sv.fin) news = true;
+                    va = wv::set_lane(va, sv.wr, F_WR + j);
+                    va = wv::set_lane(va, sv.fin, F_FIN + j);
+                }
+                if (!news) break;
+                wv::sync();
+                continue;
             }
             // ---- which of the consumed elements are passed on (the table look-ups of all sources are issued together)
             uint32_t n_out = 0;
@@ -914,7 +948,7 @@ EST_UNROLL
                     kx[u] = 0; amx[u] = 0; t2x[u] = 0; px[u] = false;
                     if (j < K) {
                         const uint32_t h = wv::bcast(va, F_HEAD + j);
-                        const uint32_t w = umin(64u, wv::bcast(va, F_TAIL + j) - h);
+                        const uint32_t w = umin((uint32_t)MERGE_WIN, wv::bcast(va, F_TAIL + j) - h);
                         const uint32_t at = j * MERGE_RING + ((h + ln) & (MERGE_RING - 1u));
                         if (ln < w) { kx[u] = rkey[at]; amx[u] = racc[at]; }
                         const uint64_t x = clamped ? eff_key(kx[u], j, ln) : kx[u];
@@ -951,7 +985,7 @@ EST_UNROLL
                         }
                         const uint64_t F = wv::ballot(pass);
                         const uint32_t fr = wv::rank_below(F);
-                        if (pass) lst[j * 64 + fr] = kx[u];
+                        if (pass) lst[j * MERGE_WIN + fr] = kx[u];
                         vb = wv::set_lane(vb, popc64(F), F_NFIN + j);
                         n_out += popc64(F);
                     }
@@ -964,12 +998,12 @@ EST_UNROLL
                 const uint32_t nf = wv::bcast(vb, F_NFIN + j);
                 if (nf == 0) continue;
                 const bool have = ln < nf;
-                const uint64_t rk = have ? lst[j * 64 + ln] : 0ull;
+                const uint64_t rk = have ? lst[j * MERGE_WIN + ln] : 0ull;
                 uint32_t rank = ln;
                 for (uint32_t j2 = 0; j2 < K; ++j2) {
                     const uint32_t n2 = wv::bcast(vb, F_NFIN + j2);
                     if (j2 == j || n2 == 0) continue;
-                    const uint64_t *l2 = lst + j2 * 64;
+                    const uint64_t *l2 = lst + j2 * MERGE_WIN;
                     const uint32_t top = 1u << (31u - (uint32_t)__builtin_clz(n2));  // the largest power of two within the list
                     uint32_t lo = 0;  // elements of list j2 below rk (no two lists hold the same key: one element per query is passed on)
                     if (!clamped) {
@@ -1005,7 +1039,6 @@ EST_UNROLL
             wr += n_out;
             if (!is_lat) space -= n_out;  // (nobody consumes while this operation runs)
             for (uint32_t j = 0; j < K; ++j) va = wv::set_lane(va, wv::bcast(va, F_HEAD + j) + wv::bcast(vb, F_CONS + j), F_HEAD + j);
-            progress = true;
             wv::sync_lds();
         }
         // staged but not consumed: read again next time
@@ -1015,35 +1048,85 @@ EST_UNROLL
         }
     }
 
-    if (DIAG && c.a->dbg_ticks && ln == 0) { uint64_t *po = est_dbg_rec(c.a, c.t, EST_MAX_STAGES - 1); po[3] += d_rounds; po[4] += d_elems; po[5] += 1; }
+    if (DIAG && c.a->dbg_ticks && ln == 0) {
+        uint64_t *po = est_dbg_rec(c.a, c.t, EST_MAX_STAGES - 1);
+        wv::atomic_add_u64(&po[3], d_rounds); wv::atomic_add_u64(&po[4], d_elems); wv::atomic_add_u64(&po[5], 1);
+    }
     const uint32_t miss_all = is_lat ? wv::sum_u32(miss) : 0u;
     wv::sync();  // what was written to the output ring is in place before its cursor moves
     if (ln == 0) {
         if (is_lat) {
-            c.st[P.miss_off + 1] = wr;
-            c.st[P.miss_off] += miss_all;
+            st_st(&c.st[P.miss_off + 1], wr);
+            st_st(&c.st[P.miss_off], ld_st(&c.st[P.miss_off]) + miss_all);
         } else {
             st_st(&c.st[P.wr_off + op.out_ring], wr);
-        }
-        if (finished) {
-            if (!is_lat) st_st(&c.st[P.fin_off + op.out_ring], 1);
-            c.st[P.done_off + opi] = 1;
+            if (finished) st_st(&c.st[P.fin_off + op.out_ring], EST_FIN);
         }
     }
-    wv::sync();
-    return progress;
+    return finished;
 }
 
 // ------------------------------------------------------------------------------------------ driver
+//
+// A workgroup of a.waves wavefronts works on up to a.per_group candidates at a time (one scratch slot each).  Wavefront
+// w < per_group takes a candidate from the launch's work counter whenever slot w is free, and prefers that candidate's
+// operations; a wavefront whose own candidate has nothing it could run, or that has none (fewer candidates than
+// wavefronts, or none left), runs an operation of another candidate of the workgroup.  An operation is run by one wavefront at
+// a time (a lock per operation); what it needs is in the slot's memory, so any wavefront can go on with it.  So a
+// candidate alone in its workgroup runs as a pipeline over all of its wavefronts, and the last candidates of a launch are
+// finished by everybody.  (What bounds a call with few candidates is its slowest single simulation, and what a sweep loses
+// at its end are the wavefronts without a candidate.  With one wavefront per candidate, or the operations of a candidate
+// cut beforehand into four runs for a workgroup of four, against this: 16 candidates x 10^6 queries of the ten-stage pipeline
+// 341 -> 130 ms, 4,500 x 50,000 62 -> 49 ms, 12,288 x 100,000 255 -> 217 ms.)
+//
+// Control words in LDS.  Of the workgroup: [0] no candidates are left; then the plan's lists of state words to watch.
+// Of a slot: candidate, phase, operations done, memoised rings (two words), spare; then per operation its lock (0 free,
+// 1 running, 2 done) and what it had seen when it was last entered; then the candidate's state words.
+enum { G_DRAINED = 0, G_WORDS = 4, C_T = 0, C_PHASE = 1, C_DONE = 2, C_MEMO = 3, C_T0 = 5, C_LOCK = 6 };
+enum { PH_EMPTY = 0, PH_INIT = 1, PH_RUN = 2 };
+enum { STEP_IDLE = 0, STEP_WORKED = 1, STEP_END = 2 };
 
-// One wavefront = one candidate.  Every loop ends: an operation that consumes or emits nothing
-// reports no progress, and a full pass over the operations without progress stops the candidate with
-// an error flag.
-EST_DEV Ctx make_ctx(const EstSimArgs &a, uint32_t t, uint32_t slot, uint64_t *lds) {
+struct Pool {
+    const EstSimArgs *a;
+    uint32_t *gw, *ctl;
+    const uint16_t *woff, *watch;
+};
+
+EST_DEV Pool make_pool(const EstSimArgs &a, uint32_t *lds) {
+    Pool p;
+    p.a = &a;
+    p.gw = lds;
+    p.woff = (const uint16_t *)(lds + G_WORDS);
+    p.watch = p.woff + EST_WATCH_HEAD(a.n_ops);
+    p.ctl = lds + G_WORDS + EST_WATCH_WORDS(a.n_ops, a.n_watch);
+    return p;
+}
+
+EST_DEV uint32_t *slot_ctl(const Pool &p, uint32_t j) { return p.ctl + j * p.a->ctl_words; }
+EST_DEV uint32_t *slot_state(const Pool &p, uint32_t j) { return p.ctl + j * p.a->ctl_words + C_LOCK + 2u * p.a->n_ops; }
+
+// By one wavefront, before any other starts.
+EST_DEV void pool_setup(const Pool &p) {
+    const uint32_t ln = wv::lane();
+    const EstSimArgs &a = *p.a;
+    if (ln < G_WORDS) p.gw[ln] = 0;
+    if (a.n > 0) {
+        uint16_t *wo = (uint16_t *)p.woff, *wt = (uint16_t *)p.watch;
+        for (uint32_t i = ln; i <= a.n_ops; i += 64) wo[i] = a.plan->watch_off[i];
+        for (uint32_t i = ln; i < a.n_watch; i += 64) wt[i] = a.plan->watch[i];
+    }
+    for (uint32_t j = 0; j < a.per_group; ++j) {
+        if (ln == 0) slot_ctl(p, j)[C_PHASE] = PH_EMPTY;
+        for (uint32_t i = ln; i < a.n_ops; i += 64) slot_ctl(p, j)[C_LOCK + i] = 2;
+    }
+    wv::sync_lds();
+}
+
+EST_DEV Ctx make_ctx(const EstSimArgs &a, uint32_t t, uint32_t slot, uint32_t *st, uint64_t *lds) {
     Ctx c;
     c.a = &a;
     c.P = a.plan;
-    c.st = a.state + (uint64_t)slot * a.state_stride;
+    c.st = st;
     c.rings = a.rings + (uint64_t)slot * a.ring_stride;
     c.rep = a.rep + (uint64_t)slot * a.rep_stride;
     c.slots = a.slots + (uint64_t)slot * a.slot_stride;
@@ -1057,15 +1140,21 @@ EST_DEV Ctx make_ctx(const EstSimArgs &a, uint32_t t, uint32_t slot, uint64_t *l
     return c;
 }
 
-// A candidate's scratch before its first operation: cursors and flags zero, every replica idle at t = 0 and
-// owning one slot, no element of any joined stream looked at yet.
-EST_DEV void sim_init(const EstSimArgs &a, const Ctx &c) {
+// A candidate's scratch before its first operation: cursors and flags zero, every replica idle at t = 0, every member
+// slot free, no element of any joined stream looked at yet.
+template <bool MEMO>
+EST_DEV void slot_init(const Pool &p, uint32_t j, uint32_t t, uint32_t slot) {
     const uint32_t ln = wv::lane();
-    const EstPlan &P = *c.P;
-    for (uint32_t i = ln; i < P.state_words; i += 64) c.st[i] = 0;
+    const EstSimArgs &a = *p.a;
+    const EstPlan &P = *a.plan;
+    uint32_t *ctl = slot_ctl(p, j), *st = slot_state(p, j);
+    const Ctx c = make_ctx(a, t, slot, st, nullptr);
+    for (uint32_t i = C_LOCK + 2u * a.n_ops + ln; i < a.ctl_words; i += 64) ctl[i] = 0;
+    // (what an operation had seen when it was last entered: a reader of the trace is ready at once)
+    for (uint32_t i = ln; i < a.n_ops; i += 64) ctl[C_LOCK + a.n_ops + i] = P.ops[i].from_trace ? 0x80000000u : 0u;
     for (uint64_t i = ln; i < a.rep_stride; i += 64) c.rep[i] = 0;
     wv::sync();
-    for (uint32_t opi = 0; opi < P.n_ops; ++opi) {
+    for (uint32_t opi = 0; opi < a.n_ops; ++opi) {
         const EstOp &op = P.ops[opi];
         if (op.type == EST_OP_SCAN) c.rep[op.rep_off + 128 + ln] = ln;
     }
@@ -1073,20 +1162,8 @@ EST_DEV void sim_init(const EstSimArgs &a, const Ctx &c) {
         uint32_t *tw = (uint32_t *)c.tab;
         for (uint64_t i = ln; i < a.tab_stride / 4; i += 64) tw[i] = 0xFFFFFFFFu;
     }
-    wv::sync();
-}
-
-// One wavefront = one candidate.  Every loop ends: an operation that consumes or emits nothing
-// reports no progress, and a full pass over the operations without progress stops the candidate with
-// an error flag.
-template <bool DIAG, bool MEMO>
-EST_DEV void sim_wave(const EstSimArgs &a, uint32_t t, uint32_t slot, uint64_t *lds) {
-    const uint32_t ln = wv::lane();
-    const EstPlan &P = *a.plan;
-    Ctx c = make_ctx(a, t, slot, lds);
-    sim_init(a, c);
-    c.memo_rings = 0;
-    c.cap_rings = nullptr;
+    uint32_t done = 0;
+    uint64_t mr = 0;
     if (MEMO) {
         // Operations this candidate does not run count as done.  In a replay the streams they would have
         // produced are complete already in the captured run of the candidate's base: point the readers
@@ -1095,70 +1172,155 @@ EST_DEV void sim_wave(const EstSimArgs &a, uint32_t t, uint32_t slot, uint64_t *
         const bool replay = a.cap_rings != nullptr;
         const uint32_t b = replay ? a.base_of[t] : 0u;
         const uint32_t *cs = replay ? a.cap_state + (uint64_t)b * a.cap_state_stride : nullptr;
-        if (replay) c.cap_rings = a.cap_rings + (uint64_t)b * a.cap_ring_stride;
-        uint64_t mr = 0;
-        for (uint32_t opi = 0; opi < P.n_ops; ++opi) {
+        for (uint32_t opi = 0; opi < a.n_ops; ++opi) {
             if (!((skip >> opi) & 1ull)) continue;
             const int32_t r = P.ops[opi].out_ring;
-            if (ln == 0) c.st[P.done_off + opi] = 1;
+            ++done;
             if (replay && r >= 0) {
                 mr |= 1ull << r;
                 if (ln == 0) {
-                    c.st[P.wr_off + r] = cs[P.wr_off + r];
-                    c.st[P.fin_off + r] = 1;
+                    st[P.wr_off + r] = cs[P.wr_off + r];
+                    st[P.fin_off + r] = EST_FIN;
                 }
             }
         }
-        c.memo_rings = mr;
-        wv::sync();
     }
+    if (ln == 0) {
+        ctl[C_T] = t;
+        ctl[C_DONE] = done;
+        ctl[C_MEMO] = (uint32_t)mr;
+        ctl[C_MEMO + 1] = (uint32_t)(mr >> 32);
+    }
+    wv::sync();
+    // Last of all the locks, which have stood at "done" since the slot's previous candidate: a wavefront that still takes
+    // the slot for that one's finds either nothing to run or the new candidate complete.
+    for (uint32_t i = ln; i < a.n_ops; i += 64)
+        st_st(&ctl[C_LOCK + i], MEMO && i < 64u && ((a.skip_ops[t] >> i) & 1ull) ? 2u : 0u);
+    wv::sync_lds();
+}
 
-    for (;;) {
-        bool progress = false, alldone = true;
-        for (uint32_t opi = 0; opi < P.n_ops; ++opi) {
-            if (wv::uniform(c.st[P.done_off + opi])) continue;
-            const EstOp &op = P.ops[opi];
-            const uint64_t k0 = (DIAG && a.dbg_ticks) ? wv::ticks() : 0;
-            bool p = op.type == EST_OP_SCAN ? scan_run<DIAG, MEMO>(c, op, opi) : merge_run<DIAG, MEMO>(c, op, opi);
-            if (DIAG && a.dbg_ticks && ln == 0) {
-                const uint64_t dt = wv::ticks() - k0;
-                if (op.type == EST_OP_SCAN) est_dbg_rec(&a, t, op.stage)[1] += dt;
-                else est_dbg_rec(&a, t, EST_MAX_STAGES - 1)[op.type == EST_OP_LAT ? 1 : 0] += dt;
+// Locks an operation of the candidate in slot j that has something new to work on: at least a.quantum elements or the
+// end of a stream more than when it was last entered (anything at all while no other operation of the candidate is running).
+// Operations are looked at from index `from` on, round and round.  Returns its index, or n_ops.
+EST_DEV uint32_t pick_op(const Pool &p, uint32_t j, uint32_t from) {
+    const uint32_t ln = wv::lane();
+    const EstSimArgs &a = *p.a;
+    const uint32_t n_ops = a.n_ops;
+    uint32_t *ctl = slot_ctl(p, j);
+    const uint32_t *st = slot_state(p, j);
+    for (uint32_t base = 0; base < n_ops; base += 64) {
+        const uint32_t l = base + ln;
+        const bool in = l < n_ops;
+        const uint32_t lock = in ? ld_st(&ctl[C_LOCK + l]) : 2u, seen = in ? ld_st(&ctl[C_LOCK + n_ops + l]) : 0u;
+        const uint32_t o = in ? p.woff[l] : 0u, k = in ? p.woff[l + 1u] - o : 0u;
+        uint32_t sum = 0;
+        for (uint32_t i = 0; i < a.max_watch; ++i)
+            if (i < k) sum += ld_st(&st[p.watch[o + i]]);
+        const uint64_t idle = wv::ballot(lock == 0u);
+        uint64_t ready = idle & wv::ballot(sum - seen >= a.quantum);
+        if (ready == 0 && wv::ballot(lock == 1u) == 0 && n_ops <= 64u) ready = idle & wv::ballot(sum != seen);
+        if (n_ops > 64u) ready = idle & wv::ballot(sum != seen);
+        while (ready) {
+            const uint64_t later = from > base && from - base < 64u ? ready & ~lanes_below(from - base) : ready;
+            const uint32_t i = ctz64(later ? later : ready);
+            uint32_t got = 0;
+            if (ln == i) {
+                got = wv::lds_cas(&ctl[C_LOCK + l], 0u, 1u) == 0u ? 1u : 0u;
+                if (got) st_st(&ctl[C_LOCK + n_ops + l], sum);
             }
-            progress = progress || p;
-            alldone = alldone && wv::uniform(c.st[P.done_off + opi]) != 0;
-        }
-        if (alldone) break;
-        if (!progress) {
-            if (ln == 0) a.status->sim_error = 1;
-            break;
+            if (wv::bcast(got, i)) return base + i;
+            ready &= ~(1ull << i);
         }
     }
+    return n_ops;
 }
 
-// Several wavefronts per candidate (for calls with fewer candidates than the device has room for: the time
-// of such a call is the time of one simulation, Section 4.2).  The operations of the candidate are dealt out
-// to the wavefronts of a workgroup (EstOp::owner), which then run as a pipeline: streams between operations of
-// different wavefronts are the same rings, their cursors read and written through ld_st / st_st.  One call =
-// one pass of wavefront `wave` over its own operations.  Returns bit 0: progress, bit 1: all of them are done.
-EST_DEV void mw_init(const EstSimArgs &a, uint32_t t, uint32_t slot) {
-    const Ctx c = make_ctx(a, t, slot, nullptr);
-    sim_init(a, c);
-}
+EST_DEV void select_wave(const EstSimArgs &a, uint32_t t, uint32_t slot, uint32_t miss, uint64_t *lds);
 
-EST_DEV uint32_t mw_pass(const EstSimArgs &a, uint32_t t, uint32_t slot, uint64_t *lds, uint32_t wave) {
-    const EstPlan &P = *a.plan;
-    const Ctx c = make_ctx(a, t, slot, lds);
-    bool progress = false, alldone = true;
-    for (uint32_t opi = 0; opi < P.n_ops; ++opi) {
-        const EstOp &op = P.ops[opi];
-        if (wv::uniform(op.owner) != wave) continue;
-        if (wv::uniform(c.st[P.done_off + opi])) continue;  // (written by this wavefront only)
-        const bool p = op.type == EST_OP_SCAN ? scan_run<false, false>(c, op, opi) : merge_run<false, false>(c, op, opi);
-        progress = progress || p;
-        alldone = alldone && wv::uniform(c.st[P.done_off + opi]) != 0;
+// One step of a wavefront: start a candidate, or run one operation, or find nothing to do.  group: index of the workgroup;
+// at: where the search for an operation starts; lds: the wavefront's own area.
+template <bool DIAG, bool MEMO>
+EST_DEV uint32_t pool_step(const Pool &p, uint32_t group, uint32_t wave, uint32_t &at, uint64_t *lds) {
+    const uint32_t ln = wv::lane();
+    const EstSimArgs &a = *p.a;
+    const uint32_t K = a.per_group, n_ops = a.n_ops;
+    const uint32_t home = wave < K ? wave : wave % K;
+    if (wave < K && group * K + home < a.n_slots && wv::uniform(ld_st(&slot_ctl(p, home)[C_PHASE])) == PH_EMPTY && wv::uniform(ld_st(&p.gw[G_DRAINED])) == 0u) {
+        uint32_t *ctl = slot_ctl(p, home);
+        uint32_t t = 0;
+        if (ln == 0) {
+            st_st(&ctl[C_PHASE], PH_INIT);
+            t = wv::fetch_add_u32(&a.status->next_cfg, 1u);
+        }
+        t = wv::bcast(t, 0);
+        if (t >= a.n_cfg) {
+            if (ln == 0) {
+                st_st(&ctl[C_PHASE], PH_EMPTY);
+                st_st(&p.gw[G_DRAINED], 1u);
+            }
+        } else {
+            if (MEMO && a.order) t = a.order[t];
+            slot_init<MEMO>(p, home, t, (MEMO && a.slot_by_cfg) ? t : group * K + home);
+            if (DIAG && a.dbg_ticks && ln == 0) ctl[C_T0] = (uint32_t)wv::ticks();
+            wv::sync();
+            if (ln == 0) st_st(&ctl[C_PHASE], PH_RUN);
+            at = 0;
+            if (n_ops > 0) return STEP_WORKED;
+        }
     }
-    return (progress ? 1u : 0u) | (alldone ? 2u : 0u);
+    const uint32_t ph = ln < K ? ld_st(&slot_ctl(p, ln)[C_PHASE]) : (uint32_t)PH_EMPTY;
+    const uint64_t run = wv::ballot(ph == PH_RUN);
+    if (wv::ballot(ph != PH_EMPTY) == 0 && wv::uniform(ld_st(&p.gw[G_DRAINED])) != 0u) return STEP_END;
+    uint32_t j = home, opi = n_ops;
+    for (uint32_t i = 0; i < K; ++i) {
+        j = home + i < K ? home + i : home + i - K;
+        if (!((run >> j) & 1ull)) continue;
+        opi = pick_op(p, j, i == 0 ? at : 0u);
+        if (opi < n_ops || n_ops == 0) break;
+    }
+    if (opi == n_ops && !(n_ops == 0 && ((run >> home) & 1ull) && wave == home)) return STEP_IDLE;
+    wv::sync();  // (what the operation's last runner and its neighbours left)
+    uint32_t *ctl = slot_ctl(p, j), *st = slot_state(p, j);
+    const uint32_t t = wv::uniform(ld_st(&ctl[C_T]));
+    const uint32_t slot = (MEMO && a.slot_by_cfg) ? t : group * K + j;
+    bool whole = n_ops == 0;  // the candidate is through
+    if (n_ops > 0) {
+        Ctx c = make_ctx(a, t, slot, st, lds);
+        if (MEMO) {
+            c.memo_rings = ((uint64_t)wv::uniform(ctl[C_MEMO + 1]) << 32) | wv::uniform(ctl[C_MEMO]);
+            if (a.cap_rings) c.cap_rings = a.cap_rings + (uint64_t)a.base_of[t] * a.cap_ring_stride;
+        }
+        const EstOp &op = a.plan->ops[opi];
+        const uint64_t k0 = (DIAG && a.dbg_ticks) ? wv::ticks() : 0;
+        const bool fin = wv::uniform(op.type) == EST_OP_SCAN ? scan_run<DIAG, MEMO>(c, op) : merge_run<DIAG, MEMO>(c, op);
+        if (DIAG && a.dbg_ticks && ln == 0) {
+            const uint64_t dt = wv::ticks() - k0;
+            if (op.type == EST_OP_SCAN) est_dbg_rec(&a, t, op.stage)[1] += dt;
+            else wv::atomic_add_u64(&est_dbg_rec(&a, t, EST_MAX_STAGES - 1)[op.type == EST_OP_LAT ? 1 : 0], dt);
+        }
+        wv::sync();  // (everything the operation leaves is in place before somebody else may enter it)
+        uint32_t nd = 0;
+        if (ln == 0) {
+            if (fin) nd = wv::lds_fetch_add(&ctl[C_DONE], 1u) + 1u;
+            st_st(&ctl[C_LOCK + opi], fin ? 2u : 0u);
+        }
+        whole = fin && wv::bcast(nd, 0) == n_ops;
+        at = opi + 1u < n_ops ? opi + 1u : 0u;
+    }
+    if (whole) {
+        wv::sync();
+        const uint64_t k1 = (DIAG && a.dbg_ticks) ? wv::ticks() : 0;
+        if (MEMO && a.slot_by_cfg)  // a captured run: its stream lengths stay with it
+            for (uint32_t i = ln; i < a.plan->state_words; i += 64) a.state[(uint64_t)slot * a.state_stride + i] = st[i];
+        if (!a.lat_by_qid) select_wave(a, t, slot, a.n > 0 ? wv::uniform(ld_st(&st[a.plan->miss_off])) : 0u, lds);
+        if (DIAG && a.dbg_ticks && ln == 0) {
+            wv::atomic_add_u64(&est_dbg_rec(&a, t, EST_MAX_STAGES - 1)[2], wv::ticks() - k1);
+            a.dbg_ticks[t] = (uint32_t)wv::ticks() - ctl[C_T0];
+        }
+        wv::sync();
+        if (ln == 0) st_st(&ctl[C_PHASE], PH_EMPTY);
+    }
+    return STEP_WORKED;
 }
 
 // ------------------------------------------------------------------------------------------ P99
@@ -1166,7 +1328,7 @@ EST_DEV uint32_t mw_pass(const EstSimArgs &a, uint32_t t, uint32_t slot, uint64_
 // Nearest-rank P99 of one candidate's latencies by a 4-pass radix select (8 bits per pass), one
 // wavefront per candidate, plus the candidate's cost = sum over stages of replicas x price
 // (Section 6, cost model).
-EST_DEV void select_wave(const EstSimArgs &a, uint32_t t, uint32_t slot, uint64_t *lds) {
+EST_DEV void select_wave(const EstSimArgs &a, uint32_t t, uint32_t slot, uint32_t miss, uint64_t *lds) {
     const uint32_t ln = wv::lane();
     const EstStageCfg *cfg = a.cfg + (uint64_t)t * a.dag->S;
     if (ln == 0) {
@@ -1221,30 +1383,7 @@ EST_UNROLL
     }
     if (ln == 0) {
         a.p99[t] = prefix;
-        a.miss[t] = a.state[(uint64_t)slot * a.state_stride + a.plan->miss_off];
-    }
-}
-
-// A wavefront takes candidates from the launch's work counter until none is left, simulating each
-// in its own scratch slot and, unless per-query latencies were asked for, selecting the P99 right
-// away from the slot's latency array.
-template <bool DIAG, bool MEMO>
-EST_DEV void slot_loop(const EstSimArgs &a, uint32_t wave_slot, uint64_t *lds) {
-    for (;;) {
-        uint32_t t = 0;
-        if (wv::lane() == 0) t = wv::fetch_add_u32(&a.status->next_cfg, 1u);
-        t = wv::bcast(t, 0);
-        if (t >= a.n_cfg) break;
-        if (MEMO && a.order) t = a.order[t];
-        const uint32_t slot = (MEMO && a.slot_by_cfg) ? t : wave_slot;
-        const uint64_t t0 = (DIAG && a.dbg_ticks) ? wv::ticks() : 0;
-        if (a.n > 0) sim_wave<DIAG, MEMO>(a, t, slot, lds);
-        wv::sync();
-        const uint64_t k1 = (DIAG && a.dbg_ticks) ? wv::ticks() : 0;
-        if (!a.lat_by_qid) select_wave(a, t, slot, lds);
-        wv::sync();
-        if (DIAG && a.dbg_ticks && wv::lane() == 0) est_dbg_rec(&a, t, EST_MAX_STAGES - 1)[2] += wv::ticks() - k1;
-        if (DIAG && a.dbg_ticks && wv::lane() == 0) a.dbg_ticks[t] = wv::ticks() - t0;
+        a.miss[t] = miss;
     }
 }
 

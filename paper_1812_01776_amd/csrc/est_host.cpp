@@ -50,9 +50,48 @@ struct Sizes {
     }
 };
 
+// The launch shape of the simulation kernel: wavefronts of a workgroup, workgroups the device holds at once, which build
+// of the kernel (wavefronts per SIMD).
+struct Shape {
+    uint32_t waves = 0, groups = 0, waves_per_simd = 0;
+    uint32_t slots() const { return waves * groups; }  // candidates in flight when every wavefront has one of its own
+};
+
+uint32_t ctl_words_of(const EstPlan &P) { return (uint32_t)align_up(6 + 2 * P.n_ops + P.state_words, 2); }
+uint32_t shared_bytes_of(const EstPlan &P, uint32_t per_group) {
+    return (uint32_t)align_up(4ull * (4 + EST_WATCH_WORDS(P.n_ops, P.n_watch) + (uint64_t)per_group * ctl_words_of(P)), 16);
+}
+
+// As many wavefronts per compute unit as LDS and registers allow, in workgroups of twelve for pipelines of more than eight
+// operations and of four for shorter ones.  An operation is run by one wavefront at a time and the slowest sets the pace of a
+// candidate that has a workgroup to itself, so a short pipeline has no use for more wavefronts.  Measured with 4 / 8 / 12: ten
+// stages, 16 candidates x 10^6 queries 212 / 126 / 127 ms, 12,288 x 100,000 230 / 221 / 217 ms; fork and join of five stages,
+// 97 x 100,000 16.6 / 16.7 ms, 8,192 x 100,000 141 / 153 ms.
+Shape pick_shape(const EstPlan &P, uint32_t lds_per_wave) {
+    Shape best;
+    const uint32_t top = P.n_ops <= 8 ? 4u : 12u;
+    for (uint32_t w = top; w >= 4; w -= 4)
+        for (uint32_t simd = 6; simd >= 4; simd -= 2) {
+            Shape s;
+            s.waves = w;
+            s.waves_per_simd = simd;
+            s.groups = estbe::max_resident_groups(w, shared_bytes_of(P, w) + w * lds_per_wave, simd);
+            if (s.slots() > best.slots()) best = s;
+        }
+    if (best.groups == 0) {  // (very wide slots or merges: fewer wavefronts than four)
+        for (uint32_t w = 2; w >= 1 && best.groups == 0; --w) {
+            best.waves = w;
+            best.waves_per_simd = 4;
+            best.groups = estbe::max_resident_groups(w, shared_bytes_of(P, w) + w * lds_per_wave, 4);
+        }
+    }
+    return best;
+}
+
 struct PlanOut {
     EstPlan plan;
     Sizes sz;
+    Shape shape;
     uint32_t n_acc = 0;
     uint32_t lds_bytes = 0;
     uint32_t acc_stage[EST_MAX_STAGES + 1];
@@ -182,41 +221,18 @@ int build_plan(estimator *h, const EstStatus &st, uint64_t n, PlanOut &po, bool 
             op.rep_off = (uint32_t)po.sz.rep_words;
             po.sz.rep_words += EST_REP_WORDS;
             op.slot_off = po.sz.slot_words;
-            po.sz.slot_words += slot_words;
+            po.sz.slot_words += slot_words + 2 * 256;  // (and the keys staged in the in-ring)
         }
     }
     P.n_ops = no;
     P.n_edges = ne;
-    {
-        // several wavefronts per candidate: the operations, in pipeline order, are cut into EST_MW_WAVES runs of
-        // about equal work (elements an operation reads), so that neighbouring wavefronts are neighbouring pipeline sections
-        std::vector<uint64_t> work(no);
-        uint64_t total = 0;
-        for (uint32_t i = 0; i < no; ++i) {
-            const EstOp &op = P.ops[i];
-            uint64_t wk = 0;
-            for (uint32_t j = 0; j < op.n_src; ++j)
-                wk += op.src_ring[j] == EST_SRC_TRACE ? n : (op.type == EST_OP_SCAN && !op.filtered ? st.n_visit[op.stage] : n);
-            work[i] = std::max<uint64_t>(wk, 1);
-            total += work[i];
-        }
-        uint64_t acc = 0;
-        for (uint32_t i = 0; i < no; ++i) {
-            P.ops[i].owner = (uint32_t)std::min<uint64_t>(EST_MW_WAVES - 1, acc * EST_MW_WAVES / total);
-            acc += work[i];
-        }
-    }
     P.max_src = 1;
     for (uint32_t i = 0; i < no; ++i) P.max_src = std::max(P.max_src, P.ops[i].n_src);
-    // the scans' in-ring: 256 keys, or 128 where that lets one more wavefront share a SIMD (the smaller ring is
-    // refilled twice as often, which costs less than the extra wavefront brings)
-    const uint32_t lds256 = (uint32_t)align_up(std::max<uint64_t>(EST_LDS_MERGE_BYTES(P.max_src), EST_LDS_SCAN_BYTES(slot_words, 256u)), 256);
-    const uint32_t lds128 = (uint32_t)align_up(std::max<uint64_t>(EST_LDS_MERGE_BYTES(P.max_src), EST_LDS_SCAN_BYTES(slot_words, 128u)), 256);
-    P.scan_ring = estbe::waves_per_simd(lds128) > estbe::waves_per_simd(lds256) ? 128u : 256u;
-    if (const char *e = getenv("EST_SCAN_RING"))  // for tests: 128 or 256
-        if (atoi(e) == 128 || atoi(e) == 256) P.scan_ring = (uint32_t)atoi(e);
-    po.lds_bytes = P.scan_ring == 128u ? lds128 : lds256;
-
+    // the scans' in-ring: 256 keys, or 128 where that lets more wavefronts share a compute unit
+    const uint32_t lds256 = (uint32_t)align_up(std::max<uint64_t>(EST_LDS_MERGE_BYTES(P.max_src), EST_LDS_SCAN_BYTES(slot_words, 256u)), 16);
+    const uint32_t lds128 = (uint32_t)align_up(std::max<uint64_t>(EST_LDS_MERGE_BYTES(P.max_src), EST_LDS_SCAN_BYTES(slot_words, 128u)), 16);
+    P.scan_ring = 256u;
+    po.lds_bytes = lds256;
     // ring capacities: a stream read by several operations may have to hold the whole skew between
     // them (one branch of a fork can lag another by the length of its simulated queue), so it gets
     // room for every element; a stream with one reader is a bounded ring
@@ -242,10 +258,41 @@ int build_plan(estimator *h, const EstStatus &st, uint64_t n, PlanOut &po, bool 
     P.wr_off = 0;
     P.fin_off = P.n_rings;
     P.rd_off = 2 * P.n_rings;
-    P.done_off = P.rd_off + P.n_edges;
-    P.miss_off = P.done_off + P.n_ops;
-    P.pub_off = P.miss_off + 2;
-    P.state_words = (uint32_t)align_up(P.pub_off + P.n_rings, 4);
+    P.miss_off = P.rd_off + P.n_edges;
+    P.state_words = (uint32_t)align_up(P.miss_off + 2, 4);
+    // what every operation watches, and the shape of the launch
+    for (uint32_t i = 0; i < no; ++i) {
+        EstOp &op = P.ops[i];
+        P.watch_off[i] = (uint16_t)P.n_watch;
+        auto add = [&](uint32_t word) { P.watch[P.n_watch++] = (uint16_t)word; };
+        if (P.n_watch + 2 * EST_KMAX + EST_MAX_CONS > EST_MAX_WATCH) return fail(h, EST_EUNSUPPORTED, "too many streams between operations");
+        for (uint32_t j = 0; j < op.n_src; ++j) {
+            if (op.src_ring[j] == EST_SRC_TRACE) {
+                op.from_trace = 1;
+                continue;
+            }
+            add(P.wr_off + (uint32_t)op.src_ring[j]);
+            add(P.fin_off + (uint32_t)op.src_ring[j]);
+        }
+        if (op.out_ring >= 0)
+            for (uint32_t k = 0; k < P.rings[op.out_ring].n_cons; ++k) add(P.rd_off + P.rings[op.out_ring].cons_edge[k]);
+        P.watch_off[i + 1] = (uint16_t)P.n_watch;
+        P.max_watch = std::max(P.max_watch, P.n_watch - (uint32_t)P.watch_off[i]);
+    }
+    po.shape = pick_shape(P, lds256);
+    const Shape small = pick_shape(P, lds128);
+    if (small.waves * small.groups > po.shape.waves * po.shape.groups) {
+        P.scan_ring = 128u;
+        po.lds_bytes = lds128;
+        po.shape = small;
+    }
+    if (const char *e = getenv("EST_SCAN_RING"))  // for tests: 128 or 256
+        if (atoi(e) == 128 || atoi(e) == 256) {
+            P.scan_ring = (uint32_t)atoi(e);
+            po.lds_bytes = P.scan_ring == 128u ? lds128 : lds256;
+            po.shape = pick_shape(P, po.lds_bytes);
+        }
+    if (po.shape.groups == 0) return fail(h, EST_EDEVICE, "the simulation kernel does not fit a compute unit: %s", estbe::last_error());
     po.sz.state_words = P.state_words;
     po.sz.rep_words = align_up(po.sz.rep_words, 4);
     po.sz.slot_words = align_up(po.sz.slot_words, 4);
@@ -265,6 +312,22 @@ struct EventSet {
 };
 
 enum { MODE_P99 = 0, MODE_LAT = 1 };
+
+// The launch shape and what of the plan the kernel needs before it reads the plan itself.
+void set_shape(EstSimArgs &sa, const PlanOut &po, const Shape &shape, uint32_t per_group, uint32_t n_slots) {
+    const EstPlan &P = po.plan;
+    sa.lds_bytes = po.lds_bytes;
+    sa.n_slots = n_slots;
+    sa.waves = shape.waves;
+    sa.per_group = per_group;
+    sa.waves_per_simd = shape.waves_per_simd;
+    sa.n_ops = P.n_ops;
+    sa.n_watch = P.n_watch;
+    sa.max_watch = P.max_watch;
+    sa.ctl_words = ctl_words_of(P);
+    sa.shared_bytes = shared_bytes_of(P, per_group);
+    sa.quantum = 256;
+}
 
 struct DevBuf {
     void *p = nullptr;
@@ -327,20 +390,16 @@ int run_core(estimator *h, uint64_t n, const uint32_t *d_arrival, const uint32_t
     po.sz = Sizes();
     po.n_acc = 0;
     if (n > 0) {
-        // Calls whose candidates will get several wavefronts each (below) keep the short rings: there the operations of
-        // a candidate run side by side, and a consumer starts when its producer first hands over, so long rings delay
-        // the pipeline instead of saving hand-overs (the planner on a five-stage pipeline: 0.67 s with short rings,
-        // 0.72 s with long ones).
-        bool small_rings = no_alloc;
-        const char *e = getenv("EST_WAVES_PER_CANDIDATE");
-        if (e ? (atoi(e) == 2 || atoi(e) == EST_MW_WAVES) : n_cfg * 2 <= (uint64_t)estbe::max_resident_groups(1024, EST_MW_WAVES) * 3)
-            small_rings = true;
-        int rc = build_plan(h, st, n, po, small_rings);
+        int rc = build_plan(h, st, n, po, no_alloc);
         if (rc != EST_OK) return rc;
     } else {
         memset(&po.plan, 0, sizeof po.plan);
         po.plan.state_words = 4;
         po.sz.state_words = 4;
+        po.lds_bytes = 1024;
+        po.shape.waves = 4;
+        po.shape.waves_per_simd = 4;
+        po.shape.groups = 256;
     }
     const bool with_lat = mode == MODE_P99 && n > 0;
 
@@ -362,7 +421,7 @@ int run_core(estimator *h, uint64_t n, const uint32_t *d_arrival, const uint32_t
     uint8_t *ws = (uint8_t *)workspace;
     uint64_t ws_bytes = workspace_bytes;
     if (!ws) {
-        const uint64_t max_slots = std::min<uint64_t>(n_cfg, std::max<uint32_t>(estbe::max_resident_waves(po.lds_bytes), 1));
+        const uint64_t max_slots = std::min<uint64_t>(n_cfg, po.shape.slots());
         uint64_t want = fixed + per_cfg * max_slots + 8 * 256;
         uint64_t avail = (uint64_t)estbe::mem_free() + h->ws_bytes;
         uint64_t budget = std::min<uint64_t>(want, avail / 100 * 92);  // (an allocation that fails is tried again smaller, below)
@@ -399,25 +458,28 @@ int run_core(estimator *h, uint64_t n, const uint32_t *d_arrival, const uint32_t
     // scratch slots: one per wavefront that works on this launch; more than the device can hold at once
     // would only wait
     uint64_t n_slots = std::min<uint64_t>((ws_bytes - fixed - 8 * 256) / per_cfg, n_cfg);
-    n_slots = std::min<uint64_t>(n_slots, std::max<uint32_t>(estbe::max_resident_waves(po.lds_bytes), 1));
-    // A call with so few candidates that most of the device would stay empty gives every candidate a workgroup of
-    // EST_MW_WAVES wavefronts instead of one wavefront, up to one and a half times the workgroups the device holds at
-    // once (EST_WAVES_PER_CANDIDATE = 1, 2 or 4 overrides the choice).  Measured on a ten-stage pipeline, 10^6 queries,
-    // 1,536 resident workgroups of four, kernel seconds with 1 / 2 / 4 wavefronts per candidate: 1,024 candidates
-    // 0.87 / 0.65 / 0.41; 1,536: 1.17 / 0.91 / 0.65; 2,304: 1.28 / 1.06 / 0.92; 3,072: 1.27 / 1.18 / 1.04; on a
-    // five-stage pipeline four stop paying at 2,048 candidates (104 / 104 / 102 ms; 3,072: 117 / 127 / 136).
-    // Workgroups of two are never better than both alternatives by much, so they are not chosen automatically.
-    uint32_t nw = 1;  // wavefronts per candidate
-    if (n > 0 && po.plan.n_ops >= 2 && n_cfg <= n_slots && n_cfg * 2 <= (uint64_t)estbe::max_resident_groups(po.lds_bytes, EST_MW_WAVES) * 3)
-        nw = EST_MW_WAVES;
-    if (const char *e = getenv("EST_WAVES_PER_CANDIDATE")) nw = n > 0 && (atoi(e) == 2 || atoi(e) == EST_MW_WAVES) ? (uint32_t)atoi(e) : 1;
-    if (getenv("EST_DEBUG_TICKS") && !no_alloc) nw = 1;  // (the step counters are per wavefront)
-    const bool several = nw > 1;
-    if (several) {
-        n_slots = std::min<uint64_t>(n_slots, std::max<uint32_t>(estbe::max_resident_groups(po.lds_bytes, nw), 1));
-        // (build_plan cut the operations into EST_MW_WAVES runs; a smaller workgroup takes neighbouring runs together)
-        for (uint32_t i = 0; i < po.plan.n_ops; ++i) po.plan.ops[i].owner = po.plan.ops[i].owner * nw / EST_MW_WAVES;
+    Shape shape = po.shape;
+    uint32_t per_group = 0;  // candidates a workgroup works on at a time
+    // EST_WAVES_PER_CANDIDATE = 1, 2 or 4 (for tests): workgroups of four with a candidate per wavefront, or workgroups of two or
+    // four with one candidate
+    const char *force = n > 0 ? getenv("EST_WAVES_PER_CANDIDATE") : nullptr;
+    if (force) {
+        shape.waves = atoi(force) == 2 ? 2 : std::min<uint32_t>(4, shape.waves);
+        shape.groups = std::max<uint32_t>(estbe::max_resident_groups(shape.waves, shared_bytes_of(po.plan, shape.waves) + shape.waves * po.lds_bytes, shape.waves_per_simd), 1);
+        per_group = atoi(force) == 1 ? shape.waves : 1;
     }
+    n_slots = std::min<uint64_t>(n_slots, shape.slots());
+    if (!per_group) {
+        // the candidates are spread over all the workgroups the device holds: few candidates, and each has a workgroup to itself
+        per_group = (uint32_t)std::min<uint64_t>(shape.waves, (n_slots + shape.groups - 1) / shape.groups);
+        // ... with more registers per wavefront when that leaves a compute unit one workgroup at most
+        if (n > 0 && shape.waves_per_simd == 6) {
+            const uint32_t g4 = estbe::max_resident_groups(shape.waves, shared_bytes_of(po.plan, per_group) + shape.waves * po.lds_bytes, 4);
+            if (n_slots <= (uint64_t)g4 * per_group && n_cfg <= (uint64_t)g4 * per_group) shape.waves_per_simd = 4;
+        }
+    }
+    uint64_t n_groups = std::min<uint64_t>(shape.groups, (n_slots + per_group - 1) / per_group);
+    n_slots = std::min<uint64_t>(n_slots, n_groups * per_group);
     uint64_t at = fixed;
     auto area = [&](uint64_t bytes_per_cfg) {
         uint64_t a0 = at;
@@ -484,8 +546,7 @@ int run_core(estimator *h, uint64_t n, const uint32_t *d_arrival, const uint32_t
         sa.slo_us = slo_us;
         sa.lat_by_qid = mode == MODE_LAT;
         sa.max_src = po.plan.max_src;
-        sa.lds_bytes = n > 0 ? po.lds_bytes : 1024;
-        sa.n_slots = (uint32_t)n_slots;
+        set_shape(sa, po, shape, per_group, (uint32_t)n_slots);
         sa.have_lat = with_lat ? 1 : 0;
         sa.state = (uint32_t *)(ws + o_state);  sa.state_stride = po.sz.state_words;
         sa.rings = (uint64_t *)(ws + o_rings);  sa.ring_stride = po.sz.ring_elems;
@@ -503,7 +564,7 @@ int run_core(estimator *h, uint64_t n, const uint32_t *d_arrival, const uint32_t
         sa.dbg_ticks = dbg_ticks;
         sa.p99 = s_p99; sa.miss = s_miss; sa.cost = s_cost;
         if (mode == MODE_P99 || n > 0)
-            if (several ? estbe::launch_sim_mw(sa, nw, stream) : estbe::launch_sim(sa, stream)) return dev_fail(h, "simulation kernel");
+            if (estbe::launch_sim(sa, stream)) return dev_fail(h, "simulation kernel");
     }
     estbe::event_record(e1, stream);
     EstStatus st2_local;
@@ -528,7 +589,7 @@ int run_core(estimator *h, uint64_t n, const uint32_t *d_arrival, const uint32_t
     memset(&ss, 0, sizeof ss);
     ss.n_launches = 1;
     ss.n_slots = (uint32_t)n_slots;
-    ss.waves_per_candidate = nw;
+    ss.waves_per_candidate = shape.waves >= 4 * per_group ? 4 : shape.waves >= 2 * per_group ? 2 : 1;
     ss.sim_ms = estbe::event_ms(e0, e1);
     ss.prep_ms = estbe::event_ms(ev_p0, ev_p1) + estbe::event_ms(ev_p2, ev_p3);
     for (uint32_t s = 0; s < S; ++s) ss.stage_visits += st.n_visit[s];
@@ -671,7 +732,7 @@ int run_shared_core(estimator *h, uint64_t n, const uint32_t *d_arrival, const u
         if (((needed >> i) & 1ull) && P.ops[i].tab_mask) cap_tab_bytes = po.sz.tab_bytes;
     const uint64_t cap_bytes = po.sz.state_words * 4 + cap_elems * 8 + po.sz.rep_words * 4 + po.sz.slot_words * 4 + cap_tab_bytes + 8 + 8;
     const uint64_t per_cfg = po.sz.per_cfg_bytes(n, true) + 64;
-    const uint32_t resident = std::max<uint32_t>(estbe::max_resident_waves(po.lds_bytes), 1);
+    const uint32_t resident = po.shape.slots();
     const uint64_t avail = ((uint64_t)estbe::mem_free() + h->ws_bytes) / 100 * 85;
     const uint64_t fixed_est = n_pad * 8 + (uint64_t)std::max<uint32_t>(po.n_acc, 1) * n_pad + n_cfg * 32 + sizeof(EstPlan) + 2 * sizeof(EstStatus) + 64 * 256;
     uint64_t n_slots = std::min<uint64_t>(n_cfg, resident);
@@ -824,9 +885,12 @@ int run_shared_core(estimator *h, uint64_t n, const uint32_t *d_arrival, const u
     sa.n = (uint32_t)n;
     sa.slo_us = slo_us;
     sa.max_src = po.plan.max_src;
-    sa.lds_bytes = po.lds_bytes;
 
     const bool capture = needed != 0;
+    // candidates per workgroup: as few as spread a launch over the device; a wavefront for each where two launches share it
+    auto share = [&](uint64_t slots) -> uint32_t {
+        return n_rounds > 1 ? po.shape.waves : (uint32_t)std::min<uint64_t>(po.shape.waves, (slots + po.shape.groups - 1) / po.shape.groups);
+    };
     struct SideStream {  // the second stream, drained and destroyed on every path out
         void *s = nullptr;
         ~SideStream() {
@@ -857,7 +921,7 @@ int run_shared_core(estimator *h, uint64_t n, const uint32_t *d_arrival, const u
         c2.plan = (const EstPlan *)(ws + o_plan_cap);
         c2.cfg = (const EstStageCfg *)d_bases + b0 * S;
         c2.n_cfg = (uint32_t)nbk;
-        c2.n_slots = (uint32_t)std::min<uint64_t>(nbk, resident);
+        set_shape(c2, po, po.shape, share(std::min<uint64_t>(nbk, resident)), (uint32_t)std::min<uint64_t>(nbk, resident));
         c2.have_lat = 0;
         c2.state = (uint32_t *)(ws + o_cstate[ar]);  c2.state_stride = po.sz.state_words;
         c2.rings = (uint64_t *)(ws + o_crings[ar]);  c2.ring_stride = cap_elems;
@@ -892,7 +956,7 @@ int run_shared_core(estimator *h, uint64_t n, const uint32_t *d_arrival, const u
                 const uint64_t next = std::min<uint64_t>(nb, n_bases - (k + 1) * nb);
                 mine = std::max<uint64_t>(n_slots > next ? n_slots - next : 0, std::min<uint64_t>(n_slots, 64));  // never more than exist
             }
-            cb.n_slots = (uint32_t)std::min<uint64_t>(mine, hi - lo);
+            set_shape(cb, po, po.shape, share(std::min<uint64_t>(mine, hi - lo)), (uint32_t)std::min<uint64_t>(mine, hi - lo));
             cb.have_lat = 1;
             cb.state = (uint32_t *)(ws + o_state);  cb.state_stride = po.sz.state_words;
             cb.rings = (uint64_t *)(ws + o_rings);  cb.ring_stride = po.sz.ring_elems;
@@ -1192,7 +1256,7 @@ uint64_t estimator_workspace_bytes(const estimator_t *h, uint64_t n, uint64_t n_
     const uint64_t cap_b = pow2ceil(EST_MAX_REPLICAS * EST_MAX_BATCH + 64 * EST_KMAX + 65);
     uint64_t per_cfg = (4ull * EST_MAX_RINGS + EST_MAX_EDGES + EST_MAX_OPS) * 4;
     per_cfg += (uint64_t)S * (std::max(cap_b, pow2ceil(std::max<uint64_t>(n, 1))) + cap_b) * 8;
-    per_cfg += (uint64_t)S * (EST_REP_WORDS + EST_MAX_REPLICAS * EST_MAX_BATCH) * 4;
+    per_cfg += (uint64_t)S * (EST_REP_WORDS + EST_MAX_REPLICAS * EST_MAX_BATCH + 2 * 256) * 4;
     // time tables of joins: a stage (or the sink) can be fed by several streams at once when it has several
     // parents, or a parent that has (a query that skips that parent takes its ready time from further up);
     // one table per stream, at most EST_KMAX and at most one per ancestor plus the arrivals

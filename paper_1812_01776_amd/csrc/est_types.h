@@ -6,7 +6,8 @@
 
 #define EST_WAVE 64
 #define EST_DBG_WORDS 16          // diagnostics: words per candidate and stage
-#define EST_MW_WAVES 4            // wavefronts that share one candidate in calls that leave the device mostly empty
+#define EST_MAX_WAVES 12          // most wavefronts of a workgroup of the simulation kernel
+#define EST_FIN (1u << 20)        // value of a stream's end flag (state word): counts as that many new elements
 #define EST_KMAX EST_MAX_MERGE_SOURCES   // sources of one merge operation (accept masks are 8 bits)
 #define EST_MAX_OPS 72          // <= 2 per stage + the latency sink
 #define EST_MAX_RINGS 66
@@ -14,9 +15,12 @@
 #define EST_MAX_CONS 36         // consumers of one ring
 #define EST_TRACE_BIT 32        // bit of the "arrival trace" pseudo-source in a source set
 #define EST_SRC_TRACE (-1)
-#define EST_LDS_MERGE_BYTES(k) ((k) * 1664u)   // LDS of one wavefront for a k-source merge: staged keys 128 x 8, passed-on keys 64 x 8, accept masks 128 per source
+#define EST_LDS_MERGE_BYTES(k) ((k) * 1648u)   // LDS of one wavefront for a k-source merge: staged keys 128 x 8, passed-on keys 62 x 8, accept masks 128 per source
 #define EST_LDS_SCAN_BYTES(sw, ring) (8u * (ring) + 4u * (sw))   // ... for a scan with sw words of member slots and an in-ring of ring keys (128 or 256)
-#define EST_REP_WORDS 196           // one scan's saved registers: free times, completion times and infos of the pending batches (64 each), their number
+#define EST_MAX_WATCH 2400        // all lists of state words that operations watch
+#define EST_WATCH_HEAD(n_ops) (((n_ops) + 2u) & ~1u)                                     // half words: the lists' offsets
+#define EST_WATCH_WORDS(n_ops, n_watch) ((EST_WATCH_HEAD(n_ops) + (n_watch) + 1u) / 2u)  // words of LDS the lists take
+#define EST_REP_WORDS 196           // one scan's saved registers: free times, completion times and infos of the pending batches (64 each), how many are pending, how many keys are staged
 
 enum { EST_OP_SCAN = 0, EST_OP_MERGE = 1, EST_OP_LAT = 2 };
 
@@ -43,17 +47,21 @@ struct EstOp {
     uint32_t tab_len;             // MERGE/LAT: entries of one table (queries, rounded up)
     uint32_t rep_off;             // SCAN: word offset of the scan's saved registers (EST_REP_WORDS) inside one candidate's area
     uint32_t r_max;               // SCAN: largest replica count of the stage in this run
-    uint64_t slot_off;            // SCAN: word offset of the member slots inside one candidate's slot area
+    uint64_t slot_off;            // SCAN: word offset of the saved member slots and staged keys inside one candidate's slot area
     uint32_t b_max;               // SCAN: largest maximum batch size of the stage in this run
     uint32_t filtered;            // SCAN: only the source elements whose accept mask has bit 0 set visit the stage
-    uint32_t owner;               // which wavefront of the workgroup runs the operation when a candidate has several (0 .. EST_MW_WAVES-1)
+    uint32_t from_trace;          // some source is the arrival trace
     uint32_t pad;
 };
 
 struct EstPlan {
     uint32_t n_ops, n_rings, n_edges, state_words;
-    // state words of one candidate: wr[n_rings] | fin[n_rings] | rd[n_edges] | opdone[n_ops] | miss, latency count | pub[n_rings]
-    uint32_t wr_off, fin_off, rd_off, done_off, miss_off, max_src, pub_off, scan_ring, slot_words, pad;  // max_src: widest merge; pub: published prefix of each ring; scan_ring: keys in a scan's LDS in-ring; slot_words: words of a scan's member slots
+    // state words of one candidate: wr[n_rings] | fin[n_rings] | rd[n_edges] | miss, latency count
+    uint32_t wr_off, fin_off, rd_off, miss_off, max_src, scan_ring, slot_words, n_watch, max_watch, pad;  // max_src: widest merge; scan_ring: keys in a scan's LDS in-ring; slot_words: words of a scan's member slots
+    // per operation the state words that change when it has something new to do: write cursor and end flag of the streams it
+    // reads, read cursors of the readers of the stream it writes; list i is watch[watch_off[i] .. watch_off[i+1])
+    uint16_t watch_off[EST_MAX_OPS + 2];
+    uint16_t watch[EST_MAX_WATCH];
     EstOp ops[EST_MAX_OPS];
     EstRing rings[EST_MAX_RINGS];
 };
@@ -102,7 +110,11 @@ struct EstSimArgs {
     uint32_t lat_by_qid;           // 1: latencies indexed by query (checking mode)
     uint32_t max_src;              // widest merge of the plan (sizes the LDS)
     uint32_t lds_bytes;            // LDS per wavefront
-    uint32_t n_slots;              // wavefronts that share the candidates of this launch, each with its own scratch
+    uint32_t n_slots;              // scratch slots: candidates in flight at most
+    uint32_t waves, per_group;     // wavefronts of a workgroup, candidates it works on at a time
+    uint32_t n_ops, n_watch, max_watch, ctl_words, shared_bytes;  // of the plan; control words per slot; LDS before the wavefronts' own areas
+    uint32_t quantum;              // elements that make an operation worth entering while others of its candidate run
+    uint32_t waves_per_simd;       // which build of the kernel
     uint32_t have_lat;             // 1: select P99 from the slot's latency array after each candidate
     // per-slot scratch, slot k at base + k * stride
     uint32_t *state;    uint64_t state_stride;   // words

@@ -238,6 +238,9 @@ EST_DEV uint32_t load_shared(const uint32_t *p) { return __hip_atomic_load(p, __
 EST_DEV void store_shared(uint32_t *p, uint32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
 
 EST_DEV void lds_add(uint32_t *p, uint32_t v) { atomicAdd(p, v); }
+// (by one lane) the word before: compare and swap, fetch and add
+EST_DEV uint32_t lds_cas(uint32_t *p, uint32_t expect, uint32_t v) { return atomicCAS(p, expect, v); }
+EST_DEV uint32_t lds_fetch_add(uint32_t *p, uint32_t v) { return atomicAdd(p, v); }
 EST_DEV void atomic_or_u64(uint64_t *p, uint64_t v) { atomicOr((unsigned long long *)p, (unsigned long long)v); }
 EST_DEV void atomic_or_u32(uint32_t *p, uint32_t v) { atomicOr(p, v); }
 EST_DEV void atomic_add_u32(uint32_t *p, uint32_t v) { atomicAdd(p, v); }

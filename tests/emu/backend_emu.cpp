@@ -114,63 +114,43 @@ int launch_envelope(const EstEnvArgs &a, void *) {
     for (uint32_t t = 0; t < 7; ++t) estdev::envelope_thread(a, t, 7);
     return 0;
 }
+// The wavefronts of all workgroups take turns, one step each, until every one has ended (a full turn in which nobody
+// finds anything to do is a stuck candidate).
 int launch_sim(const EstSimArgs &a, void *) {
-    static uint64_t lds[(64 * 1024) / 8];
-    if (a.lds_bytes > sizeof lds) abort();
-    // the slots run one after the other; the first takes candidates until the counter runs out, so to
-    // exercise every slot's scratch the counter is handed out in turns: slot k gets candidates k, k+n_slots, ...
-    EstSimArgs b = a;
-    for (uint32_t slot = 0; slot < a.n_slots; ++slot) {
-        for (uint32_t t = slot; t < a.n_cfg; t += a.n_slots) {
-            EstStatus *st = a.status;
-            st->next_cfg = t;
-            b.n_cfg = t + 1;  // this slot stops after candidate t
-            memset(lds, 0x5A, sizeof lds);
+    const uint32_t groups = (a.n_slots + a.per_group - 1) / a.per_group, total = groups * a.waves;
+    const size_t words = (a.shared_bytes + (size_t)a.lds_bytes * a.waves) / 8 + 1;
+    std::vector<std::vector<uint64_t>> lds(groups, std::vector<uint64_t>(words, 0x5A5A5A5A5A5A5A5Aull));
+    std::vector<uint32_t> at(total, 0);
+    std::vector<char> ended(total, 0);
+    for (uint32_t g = 0; g < groups; ++g)
+        emu::run_wave([&] { estdev::pool_setup(estdev::make_pool(a, (uint32_t *)lds[g].data())); });
+    for (uint32_t left = total; left > 0;) {
+        bool worked = false;
+        for (uint32_t i = 0; i < total; ++i) {
+            if (ended[i]) continue;
+            const uint32_t g = i / a.waves, w = i % a.waves;
+            uint64_t *mine = lds[g].data() + a.shared_bytes / 8 + (size_t)w * (a.lds_bytes / 8);
+            uint32_t r = 0, next = at[i];
             emu::run_wave([&] {
-                if (b.skip_ops)
-                    estdev::slot_loop<false, true>(b, slot, lds);
-                else if (b.dbg_ticks)
-                    estdev::slot_loop<true, false>(b, slot, lds);
-                else
-                    estdev::slot_loop<false, false>(b, slot, lds);
+                uint32_t my_at = at[i];
+                const estdev::Pool p = estdev::make_pool(a, (uint32_t *)lds[g].data());
+                const uint32_t x = a.skip_ops     ? estdev::pool_step<false, true>(p, g, w, my_at, mine)
+                                   : a.dbg_ticks ? estdev::pool_step<true, false>(p, g, w, my_at, mine)
+                                                 : estdev::pool_step<false, false>(p, g, w, my_at, mine);
+                if (wv::lane() == 0) { r = x; next = my_at; }
             });
+            at[i] = next;
+            if (r == estdev::STEP_END) { ended[i] = 1; --left; }
+            worked = worked || r != estdev::STEP_IDLE;
+        }
+        if (!worked) {
+            a.status->sim_error = 1;
+            break;
         }
     }
     return 0;
 }
-// Several wavefronts per candidate: the wavefronts of a workgroup take turns, one pass over their own operations
-// each, until all are done (a full turn without progress is a stuck candidate).
-int launch_sim_mw(const EstSimArgs &a, uint32_t waves, void *) {
-    static uint64_t lds[EST_MW_WAVES][(64 * 1024) / 8];
-    if (a.lds_bytes > sizeof lds[0]) abort();
-    for (uint32_t t = 0; t < a.n_cfg; ++t) {
-        const uint32_t slot = t % a.n_slots;
-        memset(lds, 0x5A, sizeof lds);
-        if (a.n > 0) {
-            emu::run_wave([&] { estdev::mw_init(a, t, slot); });
-            uint32_t done = 0;
-            while (done != (1u << waves) - 1u) {
-                bool progress = false;
-                for (uint32_t wv_ = 0; wv_ < waves; ++wv_) {
-                    if ((done >> wv_) & 1u) continue;
-                    uint32_t r = 0;
-                    emu::run_wave([&] { uint32_t x = estdev::mw_pass(a, t, slot, lds[wv_], wv_); if (wv::lane() == 0) r = x; });
-                    if (r & 2u) done |= 1u << wv_;
-                    progress = progress || (r & 3u);
-                }
-                if (!progress) {
-                    a.status->sim_error = 1;
-                    break;
-                }
-            }
-        }
-        if (!a.lat_by_qid) emu::run_wave([&] { estdev::select_wave(a, t, slot, lds[0]); });
-    }
-    return 0;
-}
-uint32_t max_resident_groups(uint32_t, uint32_t) { return 2; }
-uint32_t max_resident_waves(uint32_t) { return 3; }
-uint32_t waves_per_simd(uint32_t) { return 4; }
+uint32_t max_resident_groups(uint32_t waves, uint32_t, uint32_t) { return waves <= 4 ? 2 : 0; }
 
 void *stream_create() { return malloc(1); }  // everything runs in program order here
 void stream_destroy(void *s) { free(s); }

@@ -178,6 +178,8 @@ EST_DEV void sync() { (void)emu::exchange(0, 8); }
 EST_DEV void sync_lds() { (void)emu::exchange(0, 16); }  // (memory here is host memory either way)
 
 EST_DEV void lds_add(uint32_t *p, uint32_t v) { *p += v; }
+EST_DEV uint32_t lds_cas(uint32_t *p, uint32_t expect, uint32_t v) { const uint32_t o = *p; if (o == expect) *p = v; return o; }
+EST_DEV uint32_t lds_fetch_add(uint32_t *p, uint32_t v) { const uint32_t o = *p; *p += v; return o; }
 EST_DEV void atomic_or_u64(uint64_t *p, uint64_t v) { *p |= v; }
 EST_DEV void atomic_or_u32(uint32_t *p, uint32_t v) { *p |= v; }
 EST_DEV void atomic_add_u32(uint32_t *p, uint32_t v) { *p += v; }

@@ -71,3 +71,30 @@ def test_steps_at_the_edges_gpu(i, n):
         est = binding.Estimator(w.parents, w.lat_us, w.cost_uusd_hr)
         _compare(w, est)
         est.close()
+
+
+# ---- workgroups that share candidates: one candidate alone, fewer candidates than workgroups, more candidates than wavefronts,
+#      a last workgroup with fewer candidates than the others
+def _counted(C, S, n, seed):
+    rng = np.random.default_rng(9000 + seed)
+    w = workloads.random_case(50 + S, S=S, n=n, C=1, dag="random", max_b=8, max_r=4)
+    w.cfg_hw = rng.integers(0, 2, size=(C, S)).astype(np.uint8)
+    w.cfg_batch = rng.integers(1, 9, size=(C, S)).astype(np.uint8)
+    w.cfg_replicas = rng.integers(1, 5, size=(C, S)).astype(np.uint16)
+    return w
+
+
+@pytest.mark.parametrize("C", [1, 2, 3, 7, 17])
+def test_candidate_counts_emulated(C):
+    w = _counted(C, 4, 90, C)
+    _compare(w, emu_lib.make(w))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("S", [2, 9])
+@pytest.mark.parametrize("C", [1, 255, 513, 1537, 6145])
+def test_candidate_counts_gpu(C, S):
+    w = _counted(C, S, 130, C)
+    est = binding.Estimator(w.parents, w.lat_us, w.cost_uusd_hr)
+    _compare(w, est)
+    est.close()
