@@ -345,6 +345,9 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op) {
     const uint32_t Lrot = wv::shfl(Lmine, ln - 1u);  // lane l holds L(l), lane 0 L(64)
     const uint32_t L1 = wv::bcast(Lmine, 0);
     const uint32_t Lmin = wv::min_u32(ln < B ? Lmine : 0xFFFFFFFFu);
+    const uint32_t Lmax = wv::max_u32(ln < B ? Lmine : 0u);
+    // window and free times below this: 64 batches one after the other stay below the horizon
+    const uint32_t t_inside = Lmax < (1u << 26) ? 0xFFFFFFFFu - 64u * Lmax : 0u;
     const bool mono = Lmin == L1;  // no batch is faster than a single query
     const uint32_t SW = wv::uniform(P.slot_words);
     const uint32_t nslots = umin(64u, SW / B);  // (at least R)
@@ -606,9 +609,9 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op) {
             }
             if (single_skip) --single_skip;
         }
-        // ---- form the next batches: heads = first queries of the batches, a = queries taken, vA and gend in the lanes
-        //      nG .. K-1 = first query and completion time of every new batch, F = the new free times
-        uint32_t K = nG, a = 0, vA = 0, kind = 3;
+        // ---- form the next batches: heads = first queries of the batches, a = queries taken, gend in the lanes nG .. K-1 =
+        //      completion time of every new batch, F = the new free times
+        uint32_t K = nG, a = 0, kind = 3;
         uint64_t heads = 0;
         if (sat_skip == 0 && B >= 2 && w >= 2 * B && wv::bcast(rdy, B - 1) <= f0) {
             // Backlog: while the queue holds a full batch whenever a replica frees, the replicas take
@@ -635,7 +638,7 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op) {
                     kind = 4;
                     heads = lanes_below(a) & wv::ballot(lo == kb * B);
                     const uint32_t first = (ln - nG) * B, en = wv::shfl(e, first);
-                    if (ln >= nG && ln < K) { gend = en; vA = first; }
+                    if (ln >= nG && ln < K) gend = en;
                     // the entries not taken, then the last min(nacc, R) batches
                     const uint32_t nn = umin(nacc, R);
                     const uint32_t oe = wv::shfl(F, ln + nn), ne = wv::shfl(e, (nacc - R + ln) * B);
@@ -649,7 +652,9 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op) {
         if (a == 0) {
             // batch by batch; a batch that is not full is decided once a query ready later is in view, or none can follow
             const uint64_t tkl = DIAG ? wv::ticks() : 0;
-            wv::form_batches(rdy, Lrot, B, w, last ? 65u : w, nslots, F, gend, vA, heads, a, K);
+            if (umax(wv::bcast(rdy, w - 1u), wv::bcast(F, R - 1u)) < t_inside)
+                wv::form_batches_inside(rdy, Lrot, B, w, nslots, F, gend, heads, a, K);
+            if (K < nslots) wv::form_batches(rdy, Lrot, B, w, last ? 65u : w, nslots, F, gend, heads, a, K);
             a = umin(a, w);
             if (DIAG) { d_blkl += wv::ticks() - tkl; d_blkk += K - nG; }
             if (a == 0) break;  // undecidable: wait for input
@@ -657,6 +662,8 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op) {
         // ---- the new batches become pending: members to their slots, sizes, everything in order of completion
         {
             const uint32_t kb = nG + wv::rank_below(heads >> 1);  // my batch's lane (query 0 starts the first)
+            const bool head = wv::lane_in(heads);
+            const uint32_t vA = wv::push(head ? ln : 0u, head ? kb : nG);  // first query of the lane's batch (the first of all at query 0)
             const uint32_t pk = wv::shfl((ginfo & 0xFFu) | (vA << 8), kb);
             if (ln < a) lslots[(pk & 0xFFu) * B + (ln - (pk >> 8))] = q;
             const uint32_t anext = wv::shl1(vA);

@@ -22,6 +22,12 @@ EST_DEV uint32_t shfl(uint32_t v, uint32_t src) {
     return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(src << 2), (int)v);
 }
 
+// lane l hands v to lane dst (0..63): the value a lane was handed, 0 where it was handed none.  Lanes that hand to the same lane
+// must hand it the same value.
+EST_DEV uint32_t push(uint32_t v, uint32_t dst) {
+    return (uint32_t)__builtin_amdgcn_ds_permute((int)(dst << 2), (int)v);
+}
+
 // value of v in lane l; l must be the same in every lane
 EST_DEV uint32_t bcast(uint32_t v, uint32_t l) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)__builtin_amdgcn_readfirstlane((int)l));
@@ -129,17 +135,71 @@ EST_DEV uint32_t sat_add_uniform(uint32_t t, uint32_t d) {
 // again, ascending, 2^32-1 beyond the last one; Lrot: lane l holds the latency of a batch of l queries (lane 0 that of 64).
 // A batch starts at T = max(earliest free time, ready time of query a), takes the queries ready by then, up to B, and
 // completes at e = T + latency, at most 2^32-1; e goes into the sorted F in place of the earliest entry (with the right
-// neighbour n of every lane: max(F, min(n, e)), which is n below the place of e, e at it and F above it).  Every batch
-// leaves e and its first query in lane K of gend and vA and a bit at its first query in heads.  The loop ends when the
-// window or the lanes below K_end are used up, or before a batch that is not full while wf or more queries are ready (more
-// members may follow).  Batches that start at 2^32-1 may count lanes beyond the window: a can end up larger than w.
-// What bounds it is the latency of one chain: 23 instructions per batch, one taken branch.  Compiled from C++ the loop had
-// twice the instructions and four taken branches (310 cycles per batch on an idle compute unit).  Wait states: the
-// DPP source F and the lane reads' sources were written at least two instructions earlier, lane selects come from scalar
-// instructions.
+// neighbour n of every lane: the middle one of F, n and e, which is n below the place of e, e at it and F above it).
+// Every batch leaves e in lane K of gend and a bit at its first query in heads.
+//
+// What bounds it is the latency of one chain and, on a full device, the issue slots of both units: per batch 7 vector and 10
+// scalar instructions, one branch.  A stage whose queue forms 2.5 queries per batch spends a third of its instructions
+// here.  (With the first queries written lane by lane as well, the neighbour taken by a minimum and a maximum, the clamp and
+// both ends of the window tested per batch: 9 and 15.)  Wait states: the DPP source F was written three instructions
+// earlier, lane selects come from scalar instructions.
+
+// The loop for a step in which no time can reach 2^32-1 (a < w and K < K_end on entry): it ends, with a < w, before a batch at
+// whose start the whole window is ready or that may need a lane from K_end on.  One test per batch: the queries ready
+// at its start are fewer than the window holds and than the first query plus the lanes left (every batch takes a query at least,
+// so the lanes last as long as that holds); the second bound moves on with the batches formed.
+EST_DEV void form_batches_inside(uint32_t rdy, uint32_t Lrot, uint32_t B, uint32_t w, uint32_t K_end, uint32_t &F, uint32_t &gend,
+                                 uint64_t &heads, uint32_t &a, uint32_t &K) {
+    uint32_t t, u, c, m, z, x = 0xFFFFFFFFu;
+    B = uniform(B); w = uniform(w); K_end = uniform(K_end);
+    asm volatile("s_mov_b32 %[m], m0\n\t"
+                 "s_mov_b32 m0, %[K]\n\t"
+                 "v_readfirstlane_b32 %[t], %[F]\n\t"
+                 "v_readlane_b32 %[u], %[rdy], %[a]\n\t"
+                 "v_mov_b32_dpp %[x], %[F] wave_shl:1 row_mask:0xf bank_mask:0xf\n\t"
+                 "s_max_u32 %[t], %[t], %[u]\n\t"
+                 "v_cmp_ge_u32 vcc, %[t], %[rdy]\n\t"
+                 "s_bcnt1_i32_b64 %[c], vcc\n\t"
+                 "s_branch 2f\n"
+                 "1:\n\t"
+                 "s_sub_u32 %[u], %[c], %[a]\n\t"
+                 "s_min_u32 %[u], %[u], %[B]\n\t"
+                 "v_readlane_b32 %[c], %[L], %[u]\n\t"
+                 "s_bitset1_b64 %[heads], %[a]\n\t"
+                 "s_add_u32 %[a], %[a], %[u]\n\t"
+                 "s_add_u32 %[t], %[t], %[c]\n\t"
+                 "v_med3_u32 %[F], %[F], %[x], %[t]\n\t"
+                 "v_readlane_b32 %[u], %[rdy], %[a]\n\t"
+                 "v_writelane_b32 %[gend], %[t], m0\n\t"
+                 "s_add_u32 m0, m0, 1\n\t"
+                 "v_readfirstlane_b32 %[t], %[F]\n\t"
+                 "v_mov_b32_dpp %[x], %[F] wave_shl:1 row_mask:0xf bank_mask:0xf\n\t"
+                 "s_max_u32 %[t], %[t], %[u]\n\t"
+                 "v_cmp_ge_u32 vcc, %[t], %[rdy]\n\t"
+                 "s_bcnt1_i32_b64 %[c], vcc\n\t"
+                 "s_cmp_lt_u32 %[c], %[z]\n\t"
+                 "s_cbranch_scc1 1b\n"
+                 "2:\n\t"
+                 "s_sub_u32 %[z], %[Ke], m0\n\t"
+                 "s_add_u32 %[z], %[z], %[a]\n\t"
+                 "s_min_u32 %[z], %[z], %[w]\n\t"
+                 "s_cmp_lt_u32 %[c], %[z]\n\t"
+                 "s_cbranch_scc1 1b\n\t"
+                 "s_mov_b32 %[K], m0\n\t"
+                 "s_mov_b32 m0, %[m]\n\t"
+                 "s_nop 1"
+                 : [F] "+v"(F), [gend] "+v"(gend), [heads] "+s"(heads), [a] "+s"(a), [K] "+s"(K), [t] "=&s"(t), [u] "=&s"(u),
+                   [c] "=&s"(c), [x] "+v"(x), [m] "=&s"(m), [z] "=&s"(z)
+                 : [rdy] "v"(rdy), [L] "v"(Lrot), [B] "s"(B), [w] "s"(w), [Ke] "s"(K_end)
+                 : "vcc", "scc");
+}
+
+// The loop without conditions (a < w and K < K_end on entry): it ends when the window or the lanes below K_end are used up, or
+// before a batch that is not full while wf or more queries are ready (more members may follow).  Batches that start at
+// 2^32-1 may count lanes beyond the window: a can end up larger than w.
 EST_DEV void form_batches(uint32_t rdy, uint32_t Lrot, uint32_t B, uint32_t w, uint32_t wf, uint32_t K_end, uint32_t &F, uint32_t &gend,
-                          uint32_t &vA, uint64_t &heads, uint32_t &a, uint32_t &K) {
-    uint32_t t, u, c, x, m;
+                          uint64_t &heads, uint32_t &a, uint32_t &K) {
+    uint32_t t, u, c, m, x = 0xFFFFFFFFu;
     B = uniform(B); w = uniform(w); wf = uniform(wf); K_end = uniform(K_end);
     asm volatile("s_mov_b32 %[m], m0\n\t"
                  "s_mov_b32 m0, %[K]\n\t"
@@ -147,6 +207,7 @@ EST_DEV void form_batches(uint32_t rdy, uint32_t Lrot, uint32_t B, uint32_t w, u
                  "1:\n\t"
                  "v_readfirstlane_b32 %[t], %[F]\n\t"
                  "v_readlane_b32 %[u], %[rdy], %[a]\n\t"
+                 "v_mov_b32_dpp %[x], %[F] wave_shl:1 row_mask:0xf bank_mask:0xf\n\t"
                  "s_max_u32 %[t], %[t], %[u]\n\t"
                  "v_cmp_ge_u32 vcc, %[t], %[rdy]\n\t"
                  "s_bcnt1_i32_b64 %[c], vcc\n\t"
@@ -156,17 +217,14 @@ EST_DEV void form_batches(uint32_t rdy, uint32_t Lrot, uint32_t B, uint32_t w, u
                  "s_cbranch_scc1 3f\n"
                  "2:\n\t"
                  "v_readlane_b32 %[c], %[L], %[u]\n\t"
-                 "v_writelane_b32 %[vA], %[a], m0\n\t"
                  "s_bitset1_b64 %[heads], %[a]\n\t"
                  "s_add_u32 %[t], %[t], %[c]\n\t"
                  "s_cselect_b32 %[t], -1, %[t]\n\t"
-                 "v_mov_b32 %[x], %[t]\n\t"
+                 "s_add_u32 %[a], %[a], %[u]\n\t"
+                 "v_med3_u32 %[F], %[F], %[x], %[t]\n\t"
                  "v_writelane_b32 %[gend], %[t], m0\n\t"
                  "s_add_u32 m0, m0, 1\n\t"
-                 "v_min_u32_dpp %[x], %[F], %[x] wave_shl:1 row_mask:0xf bank_mask:0xf\n\t"
-                 "s_add_u32 %[a], %[a], %[u]\n\t"
                  "s_cmp_lt_u32 %[a], %[w]\n\t"
-                 "v_max_u32 %[F], %[F], %[x]\n\t"
                  "s_cbranch_scc0 4f\n\t"
                  "s_cmp_lt_u32 m0, %[Ke]\n\t"
                  "s_cbranch_scc1 1b\n\t"
@@ -178,8 +236,8 @@ EST_DEV void form_batches(uint32_t rdy, uint32_t Lrot, uint32_t B, uint32_t w, u
                  "s_mov_b32 %[K], m0\n\t"
                  "s_mov_b32 m0, %[m]\n\t"
                  "s_nop 1"
-                 : [F] "+v"(F), [gend] "+v"(gend), [vA] "+v"(vA), [heads] "+s"(heads), [a] "+s"(a), [K] "+s"(K), [t] "=&s"(t), [u] "=&s"(u),
-                   [c] "=&s"(c), [x] "=&v"(x), [m] "=&s"(m)
+                 : [F] "+v"(F), [gend] "+v"(gend), [heads] "+s"(heads), [a] "+s"(a), [K] "+s"(K), [t] "=&s"(t), [u] "=&s"(u),
+                   [c] "=&s"(c), [x] "+v"(x), [m] "=&s"(m)
                  : [rdy] "v"(rdy), [L] "v"(Lrot), [B] "s"(B), [w] "s"(w), [wf] "s"(wf), [Ke] "s"(K_end)
                  : "vcc", "scc");
 }
@@ -192,6 +250,7 @@ EST_DEV uint32_t min_u32(uint32_t v) {
     }
     return uniform(v);
 }
+EST_DEV uint32_t max_u32(uint32_t v) { return ~min_u32(~v); }
 
 // (moves inside the rows of 16 lanes, then one scalar read per row: no trip through the LDS crossbar)
 EST_DEV uint32_t sum_u32(uint32_t v) {

@@ -128,8 +128,45 @@ EST_DEV uint32_t sat_add_uniform(uint32_t t, uint32_t d) {
 
 EST_DEV uint32_t uniform(uint32_t v) { return (uint32_t)emu::exchange(v, 4)[0]; }
 
+// (lanes that hand to the same lane must agree: checked)
+EST_DEV uint32_t push(uint32_t v, uint32_t dst) {
+    EST_CHECK(dst < 64);
+    const uint64_t *x = emu::exchange(((uint64_t)dst << 32) | v, 20);
+    uint32_t got = 0;
+    bool any = false;
+    for (int i = 0; i < 64; ++i)
+        if ((uint32_t)(x[i] >> 32) == emu::lane()) {
+            EST_CHECK(!any || got == (uint32_t)x[i]);
+            got = (uint32_t)x[i];
+            any = true;
+        }
+    return got;
+}
+
+EST_DEV void form_batches_inside(uint32_t rdy, uint32_t Lrot, uint32_t B, uint32_t w, uint32_t K_end, uint32_t &F, uint32_t &gend,
+                                 uint64_t &heads, uint32_t &a, uint32_t &K) {
+    check_uniform2(B, w, "form_batches_inside");
+    check_uniform2(a, K, "form_batches_inside");
+    EST_CHECK(a < w && K < K_end && K_end <= 64);
+    for (;;) {
+        const uint32_t f = bcast(F, 0), r = bcast(rdy, a), T = f > r ? f : r;
+        const uint32_t c = (uint32_t)__builtin_popcountll(ballot(rdy <= T));
+        if (c >= w || c >= a + (K_end - K)) break;
+        const uint32_t b = c - a < B ? c - a : B;
+        const uint32_t L = bcast(Lrot, b & 63u), e = T + L;
+        EST_CHECK(e >= T && e != 0xFFFFFFFFu);
+        gend = set_lane(gend, e, K);
+        heads |= 1ull << a;
+        const uint64_t *x = emu::exchange(F, 21);
+        const uint32_t l = emu::lane(), n = l == 63 ? 0xFFFFFFFFu : (uint32_t)x[l + 1], m = n < e ? n : e;
+        F = F > m ? F : m;
+        a += b;
+        ++K;
+    }
+}
+
 EST_DEV void form_batches(uint32_t rdy, uint32_t Lrot, uint32_t B, uint32_t w, uint32_t wf, uint32_t K_end, uint32_t &F, uint32_t &gend,
-                          uint32_t &vA, uint64_t &heads, uint32_t &a, uint32_t &K) {
+                          uint64_t &heads, uint32_t &a, uint32_t &K) {
     check_uniform2(B, w, "form_batches");
     check_uniform2(wf, K_end, "form_batches");
     check_uniform2(a, K, "form_batches");
@@ -141,7 +178,6 @@ EST_DEV void form_batches(uint32_t rdy, uint32_t Lrot, uint32_t B, uint32_t w, u
         if (c >= wf && b != B) break;
         const uint32_t e = sat_add_uniform(T, bcast(Lrot, b & 63u));
         gend = set_lane(gend, e, K);
-        vA = set_lane(vA, a, K);
         heads |= 1ull << a;
         const uint64_t *x = emu::exchange(F, 19);
         const uint32_t l = emu::lane(), n = l == 63 ? 0xFFFFFFFFu : (uint32_t)x[l + 1], m = n < e ? n : e;
@@ -157,6 +193,8 @@ EST_DEV uint32_t min_u32(uint32_t v) {
     for (int l = 0; l < 64; ++l) m = (uint32_t)x[l] < m ? (uint32_t)x[l] : m;
     return m;
 }
+
+EST_DEV uint32_t max_u32(uint32_t v) { return ~min_u32(~v); }
 
 EST_DEV uint32_t sum_u32(uint32_t v) {
     const uint64_t *x = emu::exchange(v, 6);
