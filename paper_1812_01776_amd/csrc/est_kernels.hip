@@ -62,7 +62,9 @@ __global__ __launch_bounds__(256) void est_prep2_kernel(EstPrepArgs a) {
 }
 
 __global__ __launch_bounds__(256) void est_envelope_kernel(EstEnvArgs a) {
-    estdev::envelope_thread(a, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+    const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4u + (threadIdx.x >> 6));
+    const uint64_t j0 = (uint64_t)(w / a.n_win) * a.per_wave;  // (the widths of the same queries side by side: they read the same arrivals)
+    if (j0 < a.n) estdev::envelope_wave(a, w % a.n_win, (uint32_t)j0, (uint32_t)(j0 + a.per_wave < a.n ? j0 + a.per_wave : a.n));
 }
 
 __global__ __launch_bounds__(256) void est_cfg_kernel(EstCfgArgs a) {
@@ -146,7 +148,8 @@ int launch_prep2(const EstPrepArgs &a, void *stream) {
     return check(hipGetLastError(), "est_prep2_kernel");
 }
 int launch_envelope(const EstEnvArgs &a, void *stream) {
-    est_envelope_kernel<<<blocks_for(a.n, 256 * 16, 8192), 256, 0, (hipStream_t)stream>>>(a);  // 16 queries in a row per thread
+    const uint64_t waves = (a.n + a.per_wave - 1) / a.per_wave * a.n_win;  // (below 2^31 / 64 x 32)
+    est_envelope_kernel<<<(uint32_t)((waves + 3) / 4), 256, 0, (hipStream_t)stream>>>(a);
     return check(hipGetLastError(), "est_envelope_kernel");
 }
 int launch_sim(const EstSimArgs &a, void *stream) {

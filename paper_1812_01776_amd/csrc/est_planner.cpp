@@ -37,6 +37,30 @@ struct DevMem {  // device memory freed on every path out
     DevMem &operator=(const DevMem &) = delete;
 };
 
+// Whether the arrival times never decrease (a thousand at a time: inside, the loop has no way out and is vectorised).
+bool ascending(const uint32_t *arrival, uint64_t n) {
+    for (uint64_t q = 1; q < n;) {
+        const uint64_t e = std::min<uint64_t>(n, q + 1024);
+        uint32_t bad = 0;
+        for (; q < e; ++q) bad |= arrival[q] < arrival[q - 1] ? 1u : 0u;
+        if (bad) return false;
+    }
+    return true;
+}
+
+// Queries that visit each of the S stages, added to visits: 4,096 masks at a time stay in the first-level cache for all
+// stages.
+void count_visits(const uint32_t *mask, uint64_t n, uint32_t S, uint64_t *visits) {
+    for (uint64_t q0 = 0; q0 < n; q0 += 4096) {
+        const uint32_t m = (uint32_t)std::min<uint64_t>(4096, n - q0);
+        for (uint32_t s = 0; s < S; ++s) {
+            uint32_t k = 0;
+            for (uint32_t i = 0; i < m; ++i) k += (mask[q0 + i] >> s) & 1u;
+            visits[s] += k;
+        }
+    }
+}
+
 struct Planner {
     estimator *h;
     uint32_t S, H, Bmax, rmax, slo;
@@ -209,8 +233,7 @@ extern "C" int estimator_plan(estimator_t *h, const est_trace_t *trace, uint32_t
     if (max_replicas < 1 || max_replicas > EST_MAX_REPLICAS) return bad("planner: max_replicas out of range");
     if (steps_cap > 0 && !steps_out) return bad("planner: steps_out is NULL");
     if (trace->n >= (1ull << 31)) return bad("planner: trace too large");
-    for (uint64_t q = 1; q < trace->n; ++q)
-        if (trace->arrival_us[q] < trace->arrival_us[q - 1]) return bad("planner: arrival times decrease");
+    if (!ascending(trace->arrival_us, trace->n)) return bad("planner: arrival times decrease");
     try {
         Planner P;
         P.h = h;
@@ -221,8 +244,7 @@ extern "C" int estimator_plan(estimator_t *h, const est_trace_t *trace, uint32_t
         P.slo = slo_us;
         P.n = trace->n;
         P.visits.assign(P.S, 0);
-        for (uint64_t q = 0; q < trace->n; ++q)
-            for (uint32_t s = 0; s < P.S; ++s) P.visits[s] += (trace->visit_mask[q] >> s) & 1u;
+        count_visits(trace->visit_mask, trace->n, P.S, P.visits.data());
         DevMem m_arr(trace->n * 4), m_mask(trace->n * 4);
         if (trace->n > 0) {
             if (!m_arr.p || !m_mask.p || estbe::h2d(m_arr.p, trace->arrival_us, trace->n * 4, nullptr) ||
@@ -378,47 +400,48 @@ extern "C" int estimator_tuner_handoff(estimator_t *h, const est_trace_t *trace,
     for (uint32_t s = 0; s < S; ++s)
         if (config[s].hw >= H || config[s].batch < 1 || config[s].batch > Bmax || config[s].replicas < 1 || config[s].replicas > EST_MAX_REPLICAS)
             return bad("handoff: configuration entry out of range");
-    for (uint64_t q = 1; q < trace->n; ++q)
-        if (trace->arrival_us[q] < trace->arrival_us[q - 1]) return bad("handoff: arrival times decrease");
+    if (!ascending(trace->arrival_us, trace->n)) return bad("handoff: arrival times decrease");
     est_handoff_t r;
     memset(&r, 0, sizeof r);
     for (uint64_t w = service_time_us; r.n_windows < EST_MAX_WINDOWS && (r.n_windows == 0 || w <= 60000000ull); w *= 2)
         r.window_us[r.n_windows++] = w;
+    uint64_t visits[EST_MAX_STAGES] = {0};
     if (trace->n > 0) {
         EstEnvArgs a;
         memset(&a, 0, sizeof a);
-        DevMem m_arr(trace->n * 4), m_q(EST_MAX_WINDOWS * 4);
-        void *d_arr = m_arr.p, *d_q = m_q.p;
-        int rc = EST_OK;
-        if (!d_arr || !d_q) {
+        DevMem m_arr(trace->n * 4 + EST_MAX_WINDOWS * 4);
+        if (!m_arr.p) {
             h->err = "handoff: device allocation failed";
-            rc = EST_ENOMEM;
-        } else if (estbe::h2d(d_arr, trace->arrival_us, trace->n * 4, nullptr) || estbe::zero(d_q, EST_MAX_WINDOWS * 4, nullptr)) {
-            h->err = std::string("handoff: upload: ") + estbe::last_error();
-            rc = EST_EDEVICE;
-        } else {
-            a.arrival = (const uint32_t *)d_arr;
-            a.n = trace->n;
-            a.n_win = r.n_windows;
-            for (uint32_t i = 0; i < r.n_windows; ++i) a.win_us[i] = r.window_us[i];
-            a.max_queries = (uint32_t *)d_q;
-            if (estbe::launch_envelope(a, nullptr) || estbe::d2h(r.max_queries, d_q, r.n_windows * 4, nullptr) || estbe::sync(nullptr)) {
-                h->err = std::string("handoff: envelope kernel: ") + estbe::last_error();
-                rc = EST_EDEVICE;
-            }
+            return EST_ENOMEM;
         }
-        if (rc != EST_OK) return rc;
+        uint32_t *d_q = (uint32_t *)m_arr.p, *d_arr = d_q + EST_MAX_WINDOWS;
+        if (estbe::zero(d_q, EST_MAX_WINDOWS * 4, nullptr) || estbe::h2d(d_arr, trace->arrival_us, trace->n * 4, nullptr)) {
+            h->err = std::string("handoff: upload: ") + estbe::last_error();
+            (void)estbe::sync(nullptr);
+            return EST_EDEVICE;
+        }
+        a.arrival = d_arr;
+        a.n = trace->n;
+        a.n_win = r.n_windows;
+        // up to eight blocks of 64 windows per wavefront, as long as that leaves twice as many wavefronts as the device holds
+        a.per_wave = 64u * (uint32_t)std::min<uint64_t>(8, std::max<uint64_t>(1, trace->n / 64 * r.n_windows / 16384));
+        for (uint32_t i = 0; i < r.n_windows; ++i) a.win_us[i] = r.window_us[i];
+        a.max_queries = d_q;
+        const bool launched = !estbe::launch_envelope(a, nullptr);
+        count_visits(trace->visit_mask, trace->n, S, visits);  // (beside the kernel)
+        if (!launched || estbe::d2h(r.max_queries, d_q, r.n_windows * 4, nullptr) || estbe::sync(nullptr)) {
+            h->err = std::string("handoff: envelope kernel: ") + estbe::last_error();
+            return EST_EDEVICE;
+        }
     }
     const uint64_t span = trace->n > 0 ? (uint64_t)trace->arrival_us[trace->n - 1] - trace->arrival_us[0] : 0;
     for (uint32_t s = 0; s < S; ++s) {
-        uint64_t visits = 0;
-        for (uint64_t q = 0; q < trace->n; ++q) visits += (trace->visit_mask[q] >> s) & 1u;
         const uint64_t L = h->lat[((size_t)s * H + config[s].hw) * Bmax + (config[s].batch - 1)];
         r.mu_num[s] = (uint64_t)config[s].batch * 1000000ull;
         r.mu_den[s] = L;
         // lambda s_m / (R mu_m) = (n / span) (visits / n) / (R batch / L) = visits L / (span R batch)   (times in us cancel)
         // (a trace that spans no time has no rate: 0 / 0, which the caller must test for before dividing)
-        r.rho_num[s] = span ? visits * L : 0;
+        r.rho_num[s] = span ? visits[s] * L : 0;
         r.rho_den[s] = span * config[s].replicas * config[s].batch;
     }
     *out = r;

@@ -158,6 +158,7 @@ struct EstEnvArgs {
     const uint32_t *arrival;         // [n], non-decreasing
     uint64_t n;
     uint32_t n_win;
+    uint32_t per_wave;               // consecutive queries one wavefront takes, a multiple of 64
     uint64_t win_us[EST_MAX_WINDOWS];
     uint32_t *max_queries;           // [n_win], zero on entry
 };

@@ -111,7 +111,9 @@ int launch_prep2(const EstPrepArgs &a, void *) {
     return 0;
 }
 int launch_envelope(const EstEnvArgs &a, void *) {
-    for (uint32_t t = 0; t < 7; ++t) estdev::envelope_thread(a, t, 7);
+    for (uint64_t j = 0; j < a.n; j += a.per_wave)
+        for (uint32_t i = 0; i < a.n_win; ++i)
+            emu::run_wave([&] { estdev::envelope_wave(a, i, (uint32_t)j, (uint32_t)(j + a.per_wave < a.n ? j + a.per_wave : a.n)); });
     return 0;
 }
 // The wavefronts of all workgroups take turns, one step each, until every one has ended (a full turn in which nobody

@@ -110,3 +110,30 @@ def test_library_handoff_matches(name, n, ts):
     w = workloads.WORKLOADS[name]()
     w = w.subset(cfg_index=[0], n_queries=min(n, w.n_queries))
     _same_as_oracle(binding.Estimator(w.parents, w.lat_us, w.cost_uusd_hr), w, ts)
+
+
+def _edge_trace(n, kind):
+    w = workloads.random_case(48, S=2, n=n, C=1)
+    i = np.arange(n, dtype=np.int64)
+    w.arrival_us = {"one instant": np.full(n, 1_000_000), "even": i * 1000, "late burst": np.where(i < n // 3, i * 7, 100_000_000 + i // 5),
+                    "sparse": i * (4_000_000_000 // n)}[kind].astype(np.uint32)
+    assert np.all(np.diff(w.arrival_us.astype(np.int64)) >= 0)
+    return w
+
+
+EDGES = [(n, kind) for n in (1, 63, 64, 65, 128, 129) for kind in ("one instant", "even", "late burst", "sparse")]
+
+
+@pytest.mark.parametrize("n,kind", EDGES)
+def test_envelope_blocks_and_bursts_emulated(n, kind):
+    """Blocks of 64 windows with remainders; windows that end within their own block, beyond the trace, or behind a burst
+    far ahead of the block before."""
+    w = _edge_trace(n, kind)
+    _same_as_oracle(emu_lib.make(w), w, 4_000_000)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,kind", EDGES + [(n, kind) for n in (4097, 262_145) for kind in ("one instant", "even", "late burst", "sparse")])
+def test_envelope_blocks_and_bursts(n, kind):
+    w = _edge_trace(n, kind)
+    _same_as_oracle(binding.Estimator(w.parents, w.lat_us, w.cost_uusd_hr), w, 4_000_000)
