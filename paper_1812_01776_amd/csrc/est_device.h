@@ -140,11 +140,16 @@ constexpr uint64_t keep_min_mask(uint32_t k, uint32_t j) {
 // every lane; lanes beyond it take part but their result is not used).
 template <uint32_t K, uint32_t J>
 EST_DEV uint32_t cmpx(uint32_t v, uint32_t o) {
-    constexpr uint64_t M = keep_min_mask(K, J);
-    return wv::lane_in(M) ? umin(v, o) : umax(v, o);
+    const uint32_t lo = umin(v, o), hi = umax(v, o);
+    return wv::lane_in_const<keep_min_mask(K, J)>() ? lo : hi;
+}
+template <uint32_t K, uint32_t J>
+EST_DEV uint32_t cmpx_rows(uint32_t v) {  // J = 16 or 32
+    uint32_t a, b;
+    if (J == 16) wv::pair16(v, a, b); else wv::pair32(v, a, b);
+    return cmpx<K, J>(a, b);
 }
 EST_DEV uint32_t sort_lanes(uint32_t v, uint32_t width) {
-    const uint32_t ln = wv::lane();
     v = cmpx<2, 1>(v, wv::xor1(v));
     if (width <= 2) return v;
     v = cmpx<4, 2>(v, wv::xor2(v));
@@ -159,14 +164,14 @@ EST_DEV uint32_t sort_lanes(uint32_t v, uint32_t width) {
     v = cmpx<16, 2>(v, wv::xor2(v));
     v = cmpx<16, 1>(v, wv::xor1(v));
     if (width <= 16) return v;
-    v = cmpx<32, 16>(v, wv::shfl(v, ln ^ 16));
+    v = cmpx_rows<32, 16>(v);
     v = cmpx<32, 8>(v, wv::xor8(v));
     v = cmpx<32, 4>(v, wv::xor4(v));
     v = cmpx<32, 2>(v, wv::xor2(v));
     v = cmpx<32, 1>(v, wv::xor1(v));
     if (width <= 32) return v;
-    v = cmpx<64, 32>(v, wv::shfl(v, ln ^ 32));
-    v = cmpx<64, 16>(v, wv::shfl(v, ln ^ 16));
+    v = cmpx_rows<64, 32>(v);
+    v = cmpx_rows<64, 16>(v);
     v = cmpx<64, 8>(v, wv::xor8(v));
     v = cmpx<64, 4>(v, wv::xor4(v));
     v = cmpx<64, 2>(v, wv::xor2(v));
@@ -177,15 +182,20 @@ EST_DEV uint32_t sort_lanes(uint32_t v, uint32_t width) {
 // Ascending bitonic sort of one 64-bit key per lane over all 64 lanes.
 template <uint32_t K, uint32_t J>
 EST_DEV uint64_t cmpx64(uint64_t v, uint32_t ohi, uint32_t olo) {
-    constexpr uint64_t M = keep_min_mask(K, J);
     const uint64_t o = ((uint64_t)ohi << 32) | olo;
-    return ((o < v) == wv::lane_in(M)) ? o : v;
+    return ((o < v) == wv::lane_in_const<keep_min_mask(K, J)>()) ? o : v;
+}
+template <uint32_t K, uint32_t J>
+EST_DEV uint64_t cmpx64_rows(uint64_t v) {  // J = 16 or 32
+    uint32_t ahi, alo, bhi, blo;
+    if (J == 16) { wv::pair16((uint32_t)(v >> 32), ahi, bhi); wv::pair16((uint32_t)v, alo, blo); }
+    else { wv::pair32((uint32_t)(v >> 32), ahi, bhi); wv::pair32((uint32_t)v, alo, blo); }
+    return cmpx64<K, J>(((uint64_t)ahi << 32) | alo, bhi, blo);
 }
 template <uint32_t K>
 EST_DEV uint64_t sort_merge64(uint64_t v) {  // the compare-exchange steps (K, K/2), ..., (K, 1)
-    const uint32_t ln = wv::lane();
-    if (K >= 64) v = cmpx64<K, 32>(v, wv::shfl((uint32_t)(v >> 32), ln ^ 32), wv::shfl((uint32_t)v, ln ^ 32));
-    if (K >= 32) v = cmpx64<K, 16>(v, wv::shfl((uint32_t)(v >> 32), ln ^ 16), wv::shfl((uint32_t)v, ln ^ 16));
+    if (K >= 64) v = cmpx64_rows<K, 32>(v);
+    if (K >= 32) v = cmpx64_rows<K, 16>(v);
     if (K >= 16) v = cmpx64<K, 8>(v, wv::xor8((uint32_t)(v >> 32)), wv::xor8((uint32_t)v));
     if (K >= 8) v = cmpx64<K, 4>(v, wv::xor4((uint32_t)(v >> 32)), wv::xor4((uint32_t)v));
     if (K >= 4) v = cmpx64<K, 2>(v, wv::xor2((uint32_t)(v >> 32)), wv::xor2((uint32_t)v));
@@ -305,9 +315,7 @@ EST_DEV uint32_t emit_pending(uint32_t B, uint32_t *lslots, uint32_t nE, uint32_
         const uint64_t KM = lanes_below(k1) & ~lanes_below(k0);
         const bool mine = wv::lane_in(KM);
         const uint32_t pos = off - o0;  // first position of my batch in this chunk
-        const uint32_t bit = 1u << (pos & 31u);
-        const uint32_t hlo = wv::sum_u32(mine && pos < 32u ? bit : 0u), hhi = wv::sum_u32(mine && pos >= 32u ? bit : 0u);
-        const uint64_t H = ((uint64_t)hhi << 32) | hlo;
+        const uint64_t H = wv::ballot(wv::push(1u, mine ? pos : 0u) != 0u);
         const uint32_t kl = k0 + wv::rank_below(H >> 1);  // my batch (bit 0 of H is set)
         const uint32_t e = wv::shfl(gend, kl), y = wv::shfl(pk, kl);
         uint32_t q = ln < n ? lslots[(y & 0xFFu) * B + (o0 + ln - (y >> 8))] : 0u;

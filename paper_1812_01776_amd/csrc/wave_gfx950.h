@@ -33,6 +33,22 @@ EST_DEV uint32_t bcast(uint32_t v, uint32_t l) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)__builtin_amdgcn_readfirstlane((int)l));
 }
 
+// is this lane's bit set in m?  (m must be the same in every lane; the mask is used as the lane
+// predicate directly, no vector instruction is spent on it)
+EST_DEV bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// The same for a mask known when compiling, written into scalar registers where it is used: left to itself the compiler
+// makes the masks of all sorting networks before the loop they are in, and they spill: two reads and two writes of a vector lane
+// per use instead of two scalar moves, and a dozen registers gone where they do not (spilled scalar registers of the simulation
+// kernel 247 -> 153; with the rows exchanged by permlane swaps and an emission's batch starts found by one push, sweeps take 4 to 7 % less).
+template <uint64_t M>
+EST_DEV bool lane_in_const() {
+    uint32_t lo, hi;
+    asm volatile("s_mov_b32 %0, %1" : "=s"(lo) : "i"((int32_t)(uint32_t)M));
+    asm volatile("s_mov_b32 %0, %1" : "=s"(hi) : "i"((int32_t)(uint32_t)(M >> 32)));
+    return __builtin_amdgcn_inverse_ballot_w64(((uint64_t)hi << 32) | lo);
+}
+
 // value of lane-1 (lane 0 keeps its own) / of lane+1 (lane 63 keeps its own: shl1)
 EST_DEV uint32_t shr1(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x138, 0xF, 0xF, false); }
 // the same, except that lane 63 gets an unspecified value (no copy of the old value is needed first)
@@ -43,15 +59,22 @@ EST_DEV uint32_t shl1(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp
 EST_DEV uint32_t xor1(uint32_t v) { return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true); }
 EST_DEV uint32_t xor2(uint32_t v) { return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true); }
 EST_DEV uint32_t xor8(uint32_t v) { return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, true); }
+// the values of the two lanes l and l ^ 16 (l ^ 32): a that of the lower one, b that of the upper one, in both lanes
+EST_DEV void pair16(uint32_t v, uint32_t &a, uint32_t &b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    a = r[0];
+    b = r[1];
+}
+EST_DEV void pair32(uint32_t v, uint32_t &a, uint32_t &b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    a = r[0];
+    b = r[1];
+}
 EST_DEV uint32_t xor4(uint32_t v) {
     const uint32_t down = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x124, 0xF, 0xF, true);  // from lane-4 (mod 16)
     const uint32_t up = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x12C, 0xF, 0xF, true);    // from lane+4 (mod 16)
-    return __builtin_amdgcn_inverse_ballot_w64(0xF0F0F0F0F0F0F0F0ull) ? down : up;
+    return lane_in_const<0xF0F0F0F0F0F0F0F0ull>() ? down : up;
 }
-
-// is this lane's bit set in m?  (m must be the same in every lane; the mask is used as the lane
-// predicate directly, no vector instruction is spent on it)
-EST_DEV bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
 // number of set bits of m below this lane's position (m must be the same in every lane)
 EST_DEV uint32_t rank_below(uint64_t m) {

@@ -80,7 +80,12 @@ EST_DEV uint32_t xor2(uint32_t v) { return (uint32_t)emu::exchange(v, 12)[emu::l
 EST_DEV uint32_t xor4(uint32_t v) { return (uint32_t)emu::exchange(v, 13)[emu::lane() ^ 4u]; }
 EST_DEV uint32_t xor8(uint32_t v) { return (uint32_t)emu::exchange(v, 14)[emu::lane() ^ 8u]; }
 
+EST_DEV void pair16(uint32_t v, uint32_t &a, uint32_t &b) { const uint64_t *x = emu::exchange(v, 23); const uint32_t l = emu::lane(); a = (uint32_t)x[l & ~16u]; b = (uint32_t)x[l | 16u]; }
+EST_DEV void pair32(uint32_t v, uint32_t &a, uint32_t &b) { const uint64_t *x = emu::exchange(v, 24); const uint32_t l = emu::lane(); a = (uint32_t)x[l & ~32u]; b = (uint32_t)x[l | 32u]; }
+
 EST_DEV bool lane_in(uint64_t m) { return (m >> emu::lane()) & 1ull; }
+template <uint64_t M>
+EST_DEV bool lane_in_const() { return (M >> emu::lane()) & 1ull; }
 
 // (every lane must pass the same mask: checked like any other wave-uniform argument)
 EST_DEV uint32_t rank_below(uint64_t m) {

@@ -46,7 +46,7 @@ def test_wave_primitive_lane_layout():
     import ctypes
     import torch  # noqa: F401  (PyTorch's copy of the HIP runtime first, so that this library binds to the same instance)
     lib = ctypes.CDLL(os.path.join(os.path.dirname(__file__), "selftest", "libwave_selftest.so"))  # test-only library
-    out = np.zeros((21, 64), np.uint32)
+    out = np.zeros((24, 64), np.uint32)
     assert lib.est_selftest_wave(ctypes.c_void_p(out.ctypes.data)) == 0
     ln = np.arange(64)
     v = 7 * ln + 3
@@ -70,6 +70,9 @@ def test_wave_primitive_lane_layout():
     sq = scr * scr + 1
     assert out[19].tolist() == (np.cumsum(sq) - sq).tolist()
     assert out[20].tolist() == [int(sq.sum())] * 64
+    keys = sorted((int(x) >> 3) << 33 | (int(x) * 5 & 63) << 3 for x in scr)
+    assert [int(h) << 32 | int(l) for h, l in zip(out[21], out[22])] == keys
+    assert out[23].tolist() == [0 if i % 2 else 1000 + i // 2 for i in range(64)]
 
 
 def _hand_examples():
