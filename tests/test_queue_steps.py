@@ -98,3 +98,42 @@ def test_candidate_counts_gpu(C, S):
     est = binding.Estimator(w.parents, w.lat_us, w.cost_uusd_hr)
     _compare(w, est)
     est.close()
+
+
+def _join_case(k, n, start):
+    """A fork of k branches, each taken by some queries, joined again: every query is fed by one to k streams, and what a
+    round of the join passes on is sometimes more and sometimes less than a wavefront has lanes."""
+    rng = np.random.default_rng(8000 + 10 * k + n)
+    parents = [[]] + [[0]] * k + [list(range(1, k + 1))]
+    S = k + 2
+    lat = np.zeros((S, 1, 8), np.uint32)
+    for s in range(S):
+        lat[s, 0] = rng.integers(300, 3000) + rng.integers(20, 300) * np.arange(1, 9)
+    arr = np.cumsum(np.rint(rng.gamma(0.5, 400.0, size=n)).astype(np.int64))
+    if start:  # queueing runs into the horizon
+        arr = arr + (2**32 - 2 - int(arr[-1]) - int(lat.max(axis=2).sum()) - 5000)
+    mask = np.full(n, 1 | 1 << (k + 1), np.uint32)
+    for b in range(1, k + 1):
+        mask |= (rng.random(n) < (0.9 if b == 1 else 0.4)).astype(np.uint32) << b
+    one = np.ones((1, S), np.int64)
+    batch = rng.integers(1, 9, size=(1, S))
+    return workloads.Workload("join%d" % k, parents, lat, np.full((S, 1), 3, np.uint64), arr.astype(np.uint32), mask, (one * 0).astype(np.uint8),
+                              batch.astype(np.uint8), (one * 3).astype(np.uint16), 5000)
+
+
+@pytest.mark.parametrize("k", [2, 3, 4, 7])
+def test_joins_emulated(k):
+    for n, start in ((1, 0), (63, 0), (65, 1), (900, 0)):
+        w = _join_case(k, n, start)
+        _compare(w, emu_lib.make(w))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("start", [0, 1])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 129, 6000])
+@pytest.mark.parametrize("k", [2, 3, 4, 5, 7])
+def test_joins_gpu(k, n, start):
+    w = _join_case(k, n, start)
+    est = binding.Estimator(w.parents, w.lat_us, w.cost_uusd_hr)
+    _compare(w, est)
+    est.close()
