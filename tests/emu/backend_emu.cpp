@@ -1,9 +1,19 @@
 // Host back end for the lock-step wavefront emulation (test infrastructure): "device" memory is
-// host memory, a kernel launch runs every wavefront as 64 fibers, one wavefront after the other.
+// host memory, a wavefront is 64 fibers that meet at every primitive.
+//
+// The wavefronts of a simulation launch are alive together, as on the device, and take turns.  EST_EMU_SCHEDULE unset: a
+// wavefront keeps its turn for one whole step of the driver, so every operation runs from entry to exit undisturbed.
+// EST_EMU_SCHEDULE=<seed>: a turn lasts a random number of primitives, from one to some hundred thousand, so that operations of
+// the same candidate run inside one another and a wavefront may sleep anywhere while the others finish whole candidates.
+// EST_EMU_WAVES: wavefronts of a workgroup at most (4 when unset).
+#include <stdlib.h>
 #include <string.h>
+#include <sys/mman.h>
 #include <ucontext.h>
 
 #include <functional>
+#include <memory>
+#include <random>
 #include <string>
 #include <vector>
 
@@ -14,67 +24,93 @@
 namespace emu {
 
 namespace {
-const size_t STACK = 256 * 1024;
-ucontext_t g_sched, g_ctx[64];
-std::vector<char> g_stacks;
-bool g_done[64];
+const size_t STACK = 128 * 1024;
+const uint32_t TAG_TURN = 100;  // the rendezvous of a wavefront that gives up its turn
+
+struct Wave {
+    ucontext_t ctx[64];
+    char *stacks;
+    bool done[64];
+    uint64_t x[2][64];
+    uint32_t tag[64], nb[64];
+    std::function<void()> body;
+    Wave() {
+        void *p = mmap(nullptr, 64 * STACK, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+        if (p == MAP_FAILED) abort();
+        stacks = (char *)p;
+    }
+    ~Wave() { munmap(stacks, 64 * STACK); }
+    Wave(const Wave &) = delete;
+    Wave &operator=(const Wave &) = delete;
+};
+
+ucontext_t g_sched;
+Wave *g_wave;
 uint32_t g_cur;
-uint64_t g_x[2][64];
-uint32_t g_tag[64];
-uint32_t g_nb[64];
-const std::function<void()> *g_body;
 
 void trampoline() {
-    (*g_body)();
-    g_done[g_cur] = true;
-    swapcontext(&g_ctx[g_cur], &g_sched);
+    g_wave->body();
+    g_wave->done[g_cur] = true;
+    swapcontext(&g_wave->ctx[g_cur], &g_sched);
+}
+
+void start(Wave &w, const std::function<void()> &body) {
+    w.body = body;
+    for (int l = 0; l < 64; ++l) {
+        w.done[l] = false;
+        w.nb[l] = 0;
+        getcontext(&w.ctx[l]);
+        w.ctx[l].uc_stack.ss_sp = w.stacks + (size_t)l * STACK;
+        w.ctx[l].uc_stack.ss_size = STACK;
+        w.ctx[l].uc_link = &g_sched;
+        makecontext(&w.ctx[l], trampoline, 0);
+    }
+}
+
+// All lanes go on to the next primitive: its tag, or 0 when the wavefront has ended.
+uint32_t advance(Wave &w) {
+    g_wave = &w;
+    int ndone = 0;
+    for (int l = 0; l < 64; ++l) {
+        if (w.done[l]) { ++ndone; continue; }
+        g_cur = (uint32_t)l;
+        swapcontext(&g_sched, &w.ctx[l]);
+        if (w.done[l]) ++ndone;
+    }
+    if (ndone == 64) return 0;
+    if (ndone != 0) {
+        fprintf(stderr, "emu: %d lanes left the kernel while others wait in a primitive\n", ndone);
+        abort();
+    }
+    for (int l = 1; l < 64; ++l)
+        if (w.tag[l] != w.tag[0] || w.nb[l] != w.nb[0]) {
+            fprintf(stderr, "emu: lanes 0 and %d are in different primitives (%u vs %u)\n", l, w.tag[0], w.tag[l]);
+            abort();
+        }
+    return w.tag[0];
 }
 }  // namespace
 
 uint32_t lane() { return g_cur; }
 
 const uint64_t *exchange(uint64_t v, uint32_t tag) {
+    Wave &w = *g_wave;
     const uint32_t me = g_cur;
-    const uint32_t ph = g_nb[me] & 1u;
-    g_x[ph][me] = v;
-    g_tag[me] = tag;
-    g_nb[me]++;
-    swapcontext(&g_ctx[me], &g_sched);  // wait for the other lanes
+    const uint32_t ph = w.nb[me] & 1u;
+    w.x[ph][me] = v;
+    w.tag[me] = tag;
+    w.nb[me]++;
+    swapcontext(&w.ctx[me], &g_sched);  // wait for the other lanes
+    g_wave = &w;
     g_cur = me;
-    return g_x[ph];
+    return w.x[ph];
 }
 
+// One wavefront from start to end.
 void run_wave(const std::function<void()> &body) {
-    if (g_stacks.empty()) g_stacks.resize(64 * STACK);
-    g_body = &body;
-    for (int l = 0; l < 64; ++l) {
-        g_done[l] = false;
-        g_nb[l] = 0;
-        getcontext(&g_ctx[l]);
-        g_ctx[l].uc_stack.ss_sp = g_stacks.data() + (size_t)l * STACK;
-        g_ctx[l].uc_stack.ss_size = STACK;
-        g_ctx[l].uc_link = &g_sched;
-        makecontext(&g_ctx[l], trampoline, 0);
-    }
-    for (;;) {
-        int ndone = 0;
-        for (int l = 0; l < 64; ++l) {
-            if (g_done[l]) { ++ndone; continue; }
-            g_cur = (uint32_t)l;
-            swapcontext(&g_sched, &g_ctx[l]);
-            if (g_done[l]) ++ndone;
-        }
-        if (ndone == 64) break;
-        if (ndone != 0) {
-            fprintf(stderr, "emu: %d lanes left the kernel while others wait in a primitive\n", ndone);
-            abort();
-        }
-        for (int l = 1; l < 64; ++l)
-            if (g_tag[l] != g_tag[0] || g_nb[l] != g_nb[0]) {
-                fprintf(stderr, "emu: lanes diverged at a primitive (lane %d tag %u vs lane 0 tag %u)\n", l, g_tag[l], g_tag[0]);
-                abort();
-            }
-    }
+    static Wave w;
+    start(w, body);
+    while (advance(w) != 0) {}
 }
 
 }  // namespace emu
@@ -116,43 +152,67 @@ int launch_envelope(const EstEnvArgs &a, void *) {
             emu::run_wave([&] { estdev::envelope_wave(a, i, (uint32_t)j, (uint32_t)(j + a.per_wave < a.n ? j + a.per_wave : a.n)); });
     return 0;
 }
-// The wavefronts of all workgroups take turns, one step each, until every one has ended (a full turn in which nobody
-// finds anything to do is a stuck candidate).
+// Every wavefront runs the driver's loop until it ends; when all that are left have found nothing to do since anybody last
+// did something, a candidate is stuck.
 int launch_sim(const EstSimArgs &a, void *) {
     const uint32_t groups = (a.n_slots + a.per_group - 1) / a.per_group, total = groups * a.waves;
     const size_t words = (a.shared_bytes + (size_t)a.lds_bytes * a.waves) / 8 + 1;
     std::vector<std::vector<uint64_t>> lds(groups, std::vector<uint64_t>(words, 0x5A5A5A5A5A5A5A5Aull));
-    std::vector<uint32_t> at(total, 0);
-    std::vector<char> ended(total, 0);
     for (uint32_t g = 0; g < groups; ++g)
         emu::run_wave([&] { estdev::pool_setup(estdev::make_pool(a, (uint32_t *)lds[g].data())); });
-    for (uint32_t left = total; left > 0;) {
-        bool worked = false;
-        for (uint32_t i = 0; i < total; ++i) {
-            if (ended[i]) continue;
-            const uint32_t g = i / a.waves, w = i % a.waves;
-            uint64_t *mine = lds[g].data() + a.shared_bytes / 8 + (size_t)w * (a.lds_bytes / 8);
-            uint32_t r = 0, next = at[i];
-            emu::run_wave([&] {
-                uint32_t my_at = at[i];
-                const estdev::Pool p = estdev::make_pool(a, (uint32_t *)lds[g].data());
-                const uint32_t x = a.skip_ops     ? estdev::pool_step<false, true>(p, g, w, my_at, mine)
-                                   : a.dbg_ticks ? estdev::pool_step<true, false>(p, g, w, my_at, mine)
-                                                 : estdev::pool_step<false, false>(p, g, w, my_at, mine);
-                if (wv::lane() == 0) { r = x; next = my_at; }
-            });
-            at[i] = next;
-            if (r == estdev::STEP_END) { ended[i] = 1; --left; }
-            worked = worked || r != estdev::STEP_IDLE;
-        }
-        if (!worked) {
+    static std::vector<std::unique_ptr<emu::Wave>> pool;
+    while (pool.size() < total) pool.emplace_back(new emu::Wave);
+    std::vector<char> quiet(total, 0);  // found nothing to do in a look that began after anybody last did something
+    uint32_t events = 0;
+    for (uint32_t i = 0; i < total; ++i) {
+        const uint32_t g = i / a.waves, w = i % a.waves;
+        uint64_t *mine = lds[g].data() + a.shared_bytes / 8 + (size_t)w * (a.lds_bytes / 8);
+        emu::start(*pool[i], [&a, &lds, &quiet, &events, g, w, i, mine] {
+            const estdev::Pool p = estdev::make_pool(a, (uint32_t *)lds[g].data());
+            uint32_t at = 0;
+            for (;;) {
+                const uint32_t before = events;
+                quiet[i] = 0;
+                const uint32_t r = a.skip_ops     ? estdev::pool_step<false, true>(p, g, w, at, mine)
+                                   : a.dbg_ticks ? estdev::pool_step<true, false>(p, g, w, at, mine)
+                                                 : estdev::pool_step<false, false>(p, g, w, at, mine);
+                if (wv::lane() == 0) {
+                    if (r == estdev::STEP_IDLE) {
+                        quiet[i] = events == before;
+                    } else {
+                        ++events;
+                        quiet.assign(quiet.size(), 0);
+                    }
+                }
+                if (r == estdev::STEP_END) break;
+                (void)emu::exchange(0, emu::TAG_TURN);
+            }
+        });
+    }
+    const char *seed = getenv("EST_EMU_SCHEDULE");
+    std::mt19937_64 rng(seed ? (uint64_t)atoll(seed) : 0);
+    std::vector<char> ended(total, 0);
+    for (uint32_t left = total, turn = 0; left > 0; ++turn) {
+        const uint32_t i = seed ? (uint32_t)(rng() % total) : turn % total;
+        if (ended[i]) continue;
+        uint64_t length = seed ? 1ull << (rng() % 18) : ~0ull;
+        uint32_t tag = 1;
+        while (length-- > 0 && (tag = emu::advance(*pool[i])) != 0 && tag != emu::TAG_TURN) {}
+        if (tag == 0) { ended[i] = 1; --left; }
+        bool stuck = left > 0;
+        for (uint32_t k = 0; k < total && stuck; ++k) stuck = ended[k] || quiet[k];
+        if (stuck) {
             a.status->sim_error = 1;
             break;
         }
     }
     return 0;
 }
-uint32_t max_resident_groups(uint32_t waves, uint32_t, uint32_t) { return waves <= 4 ? 2 : 0; }
+// (two workgroups at a time: what the launches of one call share is in play)
+uint32_t max_resident_groups(uint32_t waves, uint32_t, uint32_t) {
+    const char *most = getenv("EST_EMU_WAVES");
+    return waves <= (most ? (uint32_t)atoi(most) : 4u) ? 2 : 0;
+}
 
 void *stream_create() { return malloc(1); }  // everything runs in program order here
 void stream_destroy(void *s) { free(s); }
