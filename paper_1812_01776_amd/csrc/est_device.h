@@ -1125,10 +1125,11 @@ EST_UNROLL
 // cut beforehand into four runs for a workgroup of four, against this: 16 candidates x 10^6 queries of the ten-stage pipeline
 // 341 -> 130 ms, 4,500 x 50,000 62 -> 49 ms, 12,288 x 100,000 255 -> 217 ms.)
 //
-// Control words in LDS.  Of the workgroup: [0] no candidates are left; then the plan's lists of state words to watch.
+// Control words in LDS.  Of the workgroup: [0] no candidates are left, [1] how many wavefronts are running something (low 8
+// bits) and how often one has finished (above); then the plan's lists of state words to watch.
 // Of a slot: candidate, phase, operations done, memoised rings (two words), spare; then per operation its lock (0 free,
 // 1 running, 2 done) and what it had seen when it was last entered; then the candidate's state words.
-enum { G_DRAINED = 0, G_WORDS = 4, C_T = 0, C_PHASE = 1, C_DONE = 2, C_MEMO = 3, C_T0 = 5, C_LOCK = 6 };
+enum { G_DRAINED = 0, G_WORK = 1, G_WORDS = 4, C_T = 0, C_PHASE = 1, C_DONE = 2, C_MEMO = 3, C_T0 = 5, C_LOCK = 6 };
 enum { PH_EMPTY = 0, PH_INIT = 1, PH_RUN = 2 };
 enum { STEP_IDLE = 0, STEP_WORKED = 1, STEP_END = 2 };
 
@@ -1150,6 +1151,31 @@ EST_DEV Pool make_pool(const EstSimArgs &a, uint32_t *lds) {
 
 EST_DEV uint32_t *slot_ctl(const Pool &p, uint32_t j) { return p.ctl + j * p.a->ctl_words; }
 EST_DEV uint32_t *slot_state(const Pool &p, uint32_t j) { return p.ctl + j * p.a->ctl_words + C_LOCK + 2u * p.a->n_ops; }
+
+// By one lane: something begins, and ends, to run in this workgroup (the start of a candidate, an operation with the selection
+// that may follow it).  It is said before the slot or the operation is taken, so there is no moment at which only the taker
+// knows; a taker that comes too late takes it back.
+EST_DEV void work_begin(const Pool &p) { wv::lds_add(&p.gw[G_WORK], 1u); }
+EST_DEV void work_end(const Pool &p) { wv::lds_add(&p.gw[G_WORK], 0xFFu); }  // (one fewer running, one more finished)
+EST_DEV void work_cancel(const Pool &p) { wv::lds_add(&p.gw[G_WORK], 0xFFFFFFFFu); }
+
+// What a wavefront remembers between two looks that found nothing to do.
+struct Wait {
+    uint32_t idle, still, seen;
+};
+
+// Whether to give up, after a look that found nothing: limit looks in a row during which nobody in the workgroup ran
+// anything or finished anything.  How long a wavefront itself goes without work says nothing: a pipeline of two operations
+// leaves two of four wavefronts idle for as long as its trace lasts.
+EST_DEV bool stuck(const Pool &p, Wait &w, uint32_t limit) {
+    const uint32_t v = wv::uniform(ld_st(&p.gw[G_WORK]));
+    if ((v & 0xFFu) != 0u || v != w.seen) {
+        w.seen = v;
+        w.still = 0;
+        return false;
+    }
+    return ++w.still > limit;
+}
 
 // By one wavefront, before any other starts.
 EST_DEV void pool_setup(const Pool &p) {
@@ -1271,8 +1297,10 @@ EST_DEV uint32_t pick_op(const Pool &p, uint32_t j, uint32_t from) {
             const uint32_t i = ctz64(later ? later : ready);
             uint32_t got = 0;
             if (ln == i) {
+                work_begin(p);
                 got = wv::lds_cas(&ctl[C_LOCK + l], 0u, 1u) == 0u ? 1u : 0u;
                 if (got) st_st(&ctl[C_LOCK + n_ops + l], sum);
+                else work_cancel(p);
             }
             if (wv::bcast(got, i)) return base + i;
             ready &= ~(1ull << i);
@@ -1295,6 +1323,7 @@ EST_DEV uint32_t pool_step(const Pool &p, uint32_t group, uint32_t wave, uint32_
         uint32_t *ctl = slot_ctl(p, home);
         uint32_t t = 0;
         if (ln == 0) {
+            work_begin(p);
             st_st(&ctl[C_PHASE], PH_INIT);
             t = wv::fetch_add_u32(&a.status->next_cfg, 1u);
         }
@@ -1303,13 +1332,17 @@ EST_DEV uint32_t pool_step(const Pool &p, uint32_t group, uint32_t wave, uint32_
             if (ln == 0) {
                 st_st(&ctl[C_PHASE], PH_EMPTY);
                 st_st(&p.gw[G_DRAINED], 1u);
+                work_end(p);
             }
         } else {
             if (MEMO && a.order) t = a.order[t];
             slot_init<MEMO>(p, home, t, (MEMO && a.slot_by_cfg) ? t : group * K + home);
             if (DIAG && a.dbg_ticks && ln == 0) ctl[C_T0] = (uint32_t)wv::ticks();
             wv::sync();
-            if (ln == 0) st_st(&ctl[C_PHASE], PH_RUN);
+            if (ln == 0) {
+                st_st(&ctl[C_PHASE], PH_RUN);
+                work_end(p);
+            }
             at = 0;
             if (n_ops > 0) return STEP_WORKED;
         }
@@ -1366,6 +1399,7 @@ EST_DEV uint32_t pool_step(const Pool &p, uint32_t group, uint32_t wave, uint32_
         wv::sync();
         if (ln == 0) st_st(&ctl[C_PHASE], PH_EMPTY);
     }
+    if (ln == 0 && n_ops > 0) work_end(p);
     return STEP_WORKED;
 }
 

@@ -21,9 +21,9 @@ int check(hipError_t e, const char *what) {
 }
 
 // The simulation kernel (see the driver in est_device.h).  The register budget is pinned per build: WAVES_PER_SIMD
-// resident wavefronts per SIMD, 128 or 80 registers per lane.  Every wait is bounded: a wavefront that finds nothing to
-// do for too long, or sees that another one gave up, sets the error flag and leaves.
-constexpr uint32_t IDLE_LIMIT = 1u << 22;  // (about four microseconds each)
+// resident wavefronts per SIMD, 128 or 80 registers per lane.  Every wait is bounded: a wavefront of a workgroup in which nothing
+// moves any more, or that sees that another one gave up, sets the error flag and leaves.
+constexpr uint32_t STILL_LIMIT = 1u << 18;  // looks of about four microseconds each
 template <bool DIAG, int WAVES_PER_SIMD, bool MEMO>
 __global__ __launch_bounds__(64 * EST_MAX_WAVES) __attribute__((amdgpu_waves_per_eu(WAVES_PER_SIMD, WAVES_PER_SIMD)))
 void est_sim_kernel(EstSimArgs a) {
@@ -34,21 +34,21 @@ void est_sim_kernel(EstSimArgs a) {
     if (wave == 0) estdev::pool_setup(p);
     __syncthreads();
     uint32_t at = 0;
-    for (uint32_t idle = 0;;) {
+    for (estdev::Wait wait = {0, 0, 0};;) {
         const uint32_t r = estdev::pool_step<DIAG, MEMO>(p, blockIdx.x, wave, at, my_lds);
         if (r == estdev::STEP_END) break;
         if (r == estdev::STEP_WORKED) {
-            idle = 0;
+            wait.idle = 0;
             continue;
         }
-        ++idle;
-        if (idle > IDLE_LIMIT || ((idle & 255u) == 0u && wv::load_shared(&a.status->sim_error))) {
+        ++wait.idle;
+        if (estdev::stuck(p, wait, STILL_LIMIT) || ((wait.idle & 255u) == 0u && wv::load_shared(&a.status->sim_error))) {
             if (wv::lane() == 0) a.status->sim_error = 1;
             break;
         }
         // (look again soon at first, then leave the issue slots to those that work)
-        if (idle < 8u) __builtin_amdgcn_s_sleep(8);
-        else if (idle < 32u) __builtin_amdgcn_s_sleep(32);
+        if (wait.idle < 8u) __builtin_amdgcn_s_sleep(8);
+        else if (wait.idle < 32u) __builtin_amdgcn_s_sleep(32);
         else __builtin_amdgcn_s_sleep(127);
     }
 }

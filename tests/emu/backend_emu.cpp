@@ -5,7 +5,9 @@
 // wavefront keeps its turn for one whole step of the driver, so every operation runs from entry to exit undisturbed.
 // EST_EMU_SCHEDULE=<seed>: a turn lasts a random number of primitives, from one to some hundred thousand, so that operations of
 // the same candidate run inside one another and a wavefront may sleep anywhere while the others finish whole candidates.
-// EST_EMU_WAVES: wavefronts of a workgroup at most (4 when unset).
+// EST_EMU_WAVES: wavefronts of a workgroup at most (4 when unset).  EST_EMU_STILL_LIMIT: the driver's own limit on looks that find
+// nothing, instead of the scheduler's knowledge of who is stuck.  EST_EMU_HOLD_LOCK: every candidate's last operation is locked by
+// nobody, so that it never ends.
 #include <stdlib.h>
 #include <string.h>
 #include <sys/mman.h>
@@ -162,14 +164,17 @@ int launch_sim(const EstSimArgs &a, void *) {
         emu::run_wave([&] { estdev::pool_setup(estdev::make_pool(a, (uint32_t *)lds[g].data())); });
     static std::vector<std::unique_ptr<emu::Wave>> pool;
     while (pool.size() < total) pool.emplace_back(new emu::Wave);
+    const char *limit_env = getenv("EST_EMU_STILL_LIMIT");
+    const uint32_t limit = limit_env ? (uint32_t)atol(limit_env) : ~0u;
     std::vector<char> quiet(total, 0);  // found nothing to do in a look that began after anybody last did something
     uint32_t events = 0;
     for (uint32_t i = 0; i < total; ++i) {
         const uint32_t g = i / a.waves, w = i % a.waves;
         uint64_t *mine = lds[g].data() + a.shared_bytes / 8 + (size_t)w * (a.lds_bytes / 8);
-        emu::start(*pool[i], [&a, &lds, &quiet, &events, g, w, i, mine] {
+        emu::start(*pool[i], [&a, &lds, &quiet, &events, limit, g, w, i, mine] {
             const estdev::Pool p = estdev::make_pool(a, (uint32_t *)lds[g].data());
             uint32_t at = 0;
+            estdev::Wait wait = {0, 0, 0};
             for (;;) {
                 const uint32_t before = events;
                 quiet[i] = 0;
@@ -185,6 +190,10 @@ int launch_sim(const EstSimArgs &a, void *) {
                     }
                 }
                 if (r == estdev::STEP_END) break;
+                if (r == estdev::STEP_IDLE && (estdev::stuck(p, wait, limit) || wv::uniform(a.status->sim_error))) {
+                    a.status->sim_error = 1;
+                    break;
+                }
                 (void)emu::exchange(0, emu::TAG_TURN);
             }
         });
@@ -192,14 +201,20 @@ int launch_sim(const EstSimArgs &a, void *) {
     const char *seed = getenv("EST_EMU_SCHEDULE");
     std::mt19937_64 rng(seed ? (uint64_t)atoll(seed) : 0);
     std::vector<char> ended(total, 0);
+    const uint32_t top = 6 + (uint32_t)(rng() % 12);
+    const bool hold = getenv("EST_EMU_HOLD_LOCK") != nullptr;
     for (uint32_t left = total, turn = 0; left > 0; ++turn) {
+        for (uint32_t g = 0; g < groups && hold; ++g) {
+            uint32_t *ctl = estdev::slot_ctl(estdev::make_pool(a, (uint32_t *)lds[g].data()), 0);
+            if (ctl[estdev::C_PHASE] == estdev::PH_RUN && ctl[estdev::C_LOCK + a.n_ops - 1] == 0) ctl[estdev::C_LOCK + a.n_ops - 1] = 1;
+        }
         const uint32_t i = seed ? (uint32_t)(rng() % total) : turn % total;
         if (ended[i]) continue;
-        uint64_t length = seed ? 1ull << (rng() % 18) : ~0ull;
+        uint64_t length = seed ? 1ull << (rng() % top) : ~0ull;
         uint32_t tag = 1;
         while (length-- > 0 && (tag = emu::advance(*pool[i])) != 0 && tag != emu::TAG_TURN) {}
         if (tag == 0) { ended[i] = 1; --left; }
-        bool stuck = left > 0;
+        bool stuck = left > 0 && !limit_env;
         for (uint32_t k = 0; k < total && stuck; ++k) stuck = ended[k] || quiet[k];
         if (stuck) {
             a.status->sim_error = 1;

@@ -49,3 +49,23 @@ def test_shared_stages_inside_one_another_match_oracle(seed, monkeypatch):
     monkeypatch.setenv("EST_EMU_WAVES", "12")
     w, bases, base_of = workloads.neighbourhood_case(seed, S=7)
     check_shared(emu_lib.make(w), w, bases, base_of, "cpu")
+
+
+@pytest.mark.parametrize("schedule", [None, 2, 4, 7])
+def test_a_wavefront_without_work_waits_as_long_as_anything_moves(schedule, monkeypatch):
+    # one stage: two operations, so that at least two of the four wavefronts have nothing to do until the trace ends
+    monkeypatch.setenv("EST_EMU_STILL_LIMIT", "64")
+    if schedule is not None:
+        monkeypatch.setenv("EST_EMU_SCHEDULE", str(schedule))
+    _check(workloads.random_case(2, S=1, n=1500, C=1))
+
+
+@pytest.mark.parametrize("schedule", [None, 8])
+def test_a_candidate_that_cannot_end_ends_the_call(schedule, monkeypatch):
+    monkeypatch.setenv("EST_EMU_STILL_LIMIT", "64")
+    monkeypatch.setenv("EST_EMU_HOLD_LOCK", "1")
+    if schedule is not None:
+        monkeypatch.setenv("EST_EMU_SCHEDULE", str(schedule))
+    with pytest.raises(binding.EstimatorError) as ei:
+        _check(workloads.random_case(2, S=3, n=100, C=2))
+    assert ei.value.code == binding.EST_EINTERNAL
