@@ -1214,7 +1214,7 @@ EST_DEV Ctx make_ctx(const EstSimArgs &a, uint32_t t, uint32_t slot, uint32_t *s
 
 // A candidate's scratch before its first operation: cursors and flags zero, every replica idle at t = 0, every member
 // slot free, no element of any joined stream looked at yet.
-template <bool MEMO>
+template <bool DIAG, bool MEMO>
 EST_DEV void slot_init(const Pool &p, uint32_t j, uint32_t t, uint32_t slot) {
     const uint32_t ln = wv::lane();
     const EstSimArgs &a = *p.a;
@@ -1262,10 +1262,13 @@ EST_DEV void slot_init(const Pool &p, uint32_t j, uint32_t t, uint32_t slot) {
         ctl[C_DONE] = done;
         ctl[C_MEMO] = (uint32_t)mr;
         ctl[C_MEMO + 1] = (uint32_t)(mr >> 32);
+        if (DIAG && a.dbg_ticks) ctl[C_T0] = (uint32_t)wv::ticks();
+        st_st(&ctl[C_PHASE], PH_RUN);
     }
     wv::sync();
     // Last of all the locks, which have stood at "done" since the slot's previous candidate: a wavefront that still takes
-    // the slot for that one's finds either nothing to run or the new candidate complete.
+    // the slot for that one's finds either nothing to run or the new candidate complete.  It may even finish the new one
+    // and empty the slot before this wavefront goes on, so from here on the slot's words are not this wavefront's to write.
     for (uint32_t i = ln; i < a.n_ops; i += 64)
         st_st(&ctl[C_LOCK + i], MEMO && i < 64u && ((a.skip_ops[t] >> i) & 1ull) ? 2u : 0u);
     wv::sync_lds();
@@ -1336,13 +1339,8 @@ EST_DEV uint32_t pool_step(const Pool &p, uint32_t group, uint32_t wave, uint32_
             }
         } else {
             if (MEMO && a.order) t = a.order[t];
-            slot_init<MEMO>(p, home, t, (MEMO && a.slot_by_cfg) ? t : group * K + home);
-            if (DIAG && a.dbg_ticks && ln == 0) ctl[C_T0] = (uint32_t)wv::ticks();
-            wv::sync();
-            if (ln == 0) {
-                st_st(&ctl[C_PHASE], PH_RUN);
-                work_end(p);
-            }
+            slot_init<DIAG, MEMO>(p, home, t, (MEMO && a.slot_by_cfg) ? t : group * K + home);
+            if (ln == 0) work_end(p);
             at = 0;
             if (n_ops > 0) return STEP_WORKED;
         }

@@ -69,3 +69,13 @@ def test_a_candidate_that_cannot_end_ends_the_call(schedule, monkeypatch):
     with pytest.raises(binding.EstimatorError) as ei:
         _check(workloads.random_case(2, S=3, n=100, C=2))
     assert ei.value.code == binding.EST_EINTERNAL
+
+
+@pytest.mark.parametrize("waves,schedule", [(4, 14), (4, 29), (2, 29), (4, 30), (2, 31)])
+def test_a_helper_may_finish_a_candidate_before_its_starter_goes_on(waves, schedule, monkeypatch):
+    # candidates of one query and one stage: a helper that took the slot for the previous candidate's can run both operations of
+    # the next one while the wavefront that started it sleeps
+    monkeypatch.setenv("EST_EMU_SCHEDULE", str(schedule))
+    monkeypatch.setenv("EST_WAVES_PER_CANDIDATE", str(waves))
+    w = workloads.random_case(3, S=1, n=1, C=200)
+    _check(w)
