@@ -23,6 +23,20 @@ int launch_cfg(const EstCfgArgs &a, void *stream);
 int launch_prep1(const EstPrepArgs &a, void *stream);
 int launch_prep2(const EstPrepArgs &a, void *stream);
 int launch_sim(const EstSimArgs &a, void *stream);
+// The envelope's launch, one wavefront per a.per_wave queries and width, four to a workgroup: as many consecutive queries per
+// wavefront as keep twice the wavefronts the device holds (16,384), at most eight blocks of 64, and beyond that as many as keep the
+// launch at 2^25 wavefronts: it would have 2^32 work-items, one more than a launch can have, from queries x widths = 2^35 on.
+inline uint32_t envelope_per_wave(uint64_t n, uint32_t n_win) {
+    const uint64_t blocks = (n + 63) / 64;
+    uint64_t k = n / 64 * n_win / 16384;
+    k = k < 1 ? 1 : k > 8 ? 8 : k;
+    const uint64_t most = (1u << 25) / n_win;  // wavefronts of one width
+    if ((blocks + k - 1) / k > most) k = (blocks + most - 1) / most;
+    return (uint32_t)(64 * k);
+}
+inline uint32_t envelope_groups(uint64_t n, uint32_t n_win, uint32_t per_wave) {
+    return (uint32_t)(((n + per_wave - 1) / per_wave * n_win + 3) / 4);
+}
 int launch_envelope(const EstEnvArgs &a, void *stream);
 // workgroups of the simulation kernel the device holds at once: waves wavefronts and lds_bytes of LDS each, the build for
 // waves_per_simd (4 or 6) wavefronts per SIMD; 0 when it does not fit

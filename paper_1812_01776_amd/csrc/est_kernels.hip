@@ -148,8 +148,7 @@ int launch_prep2(const EstPrepArgs &a, void *stream) {
     return check(hipGetLastError(), "est_prep2_kernel");
 }
 int launch_envelope(const EstEnvArgs &a, void *stream) {
-    const uint64_t waves = (a.n + a.per_wave - 1) / a.per_wave * a.n_win;  // (below 2^31 / 64 x 32)
-    est_envelope_kernel<<<(uint32_t)((waves + 3) / 4), 256, 0, (hipStream_t)stream>>>(a);
+    est_envelope_kernel<<<envelope_groups(a.n, a.n_win, a.per_wave), 256, 0, (hipStream_t)stream>>>(a);
     return check(hipGetLastError(), "est_envelope_kernel");
 }
 int launch_sim(const EstSimArgs &a, void *stream) {

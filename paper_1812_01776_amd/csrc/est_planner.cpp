@@ -423,8 +423,7 @@ extern "C" int estimator_tuner_handoff(estimator_t *h, const est_trace_t *trace,
         a.arrival = d_arr;
         a.n = trace->n;
         a.n_win = r.n_windows;
-        // up to eight blocks of 64 windows per wavefront, as long as that leaves twice as many wavefronts as the device holds
-        a.per_wave = 64u * (uint32_t)std::min<uint64_t>(8, std::max<uint64_t>(1, trace->n / 64 * r.n_windows / 16384));
+        a.per_wave = estbe::envelope_per_wave(trace->n, r.n_windows);
         for (uint32_t i = 0; i < r.n_windows; ++i) a.win_us[i] = r.window_us[i];
         a.max_queries = d_q;
         const bool launched = !estbe::launch_envelope(a, nullptr);

@@ -148,6 +148,11 @@ int launch_prep2(const EstPrepArgs &a, void *) {
     for (uint32_t t = 0; t < 7; ++t) estdev::prep2_thread(a, t, 7);
     return 0;
 }
+// what the launch would be, for a test of its size
+extern "C" uint32_t emu_envelope_launch(uint64_t n, uint32_t n_win, uint32_t *per_wave) {
+    *per_wave = envelope_per_wave(n, n_win);
+    return envelope_groups(n, n_win, *per_wave);
+}
 int launch_envelope(const EstEnvArgs &a, void *) {
     for (uint64_t j = 0; j < a.n; j += a.per_wave)
         for (uint32_t i = 0; i < a.n_win; ++i)

@@ -4,6 +4,7 @@ oracle/envelope_oracle.py is the definition written out; it is pinned by a brute
 integer window start on tiny traces and by the closed form for evenly spaced arrivals.  The library
 (estimator_tuner_handoff: one kernel over the trace plus exact integer ratios) must agree with it
 exactly."""
+import ctypes
 from fractions import Fraction
 
 import numpy as np
@@ -130,6 +131,19 @@ def test_envelope_blocks_and_bursts_emulated(n, kind):
     far ahead of the block before."""
     w = _edge_trace(n, kind)
     _same_as_oracle(emu_lib.make(w), w, 4_000_000)
+
+
+@pytest.mark.parametrize("n_win", [1, 10, 16, 26, 32])
+@pytest.mark.parametrize("n", [1, 64, 65, 2_000_000, 2**30 + 1, 2**31 - 1])
+def test_envelope_launch_covers_the_trace_and_is_a_legal_one(n, n_win):
+    lib = emu_lib.lib()
+    per_wave = ctypes.c_uint32()
+    lib.emu_envelope_launch.restype = ctypes.c_uint32
+    groups = lib.emu_envelope_launch(ctypes.c_uint64(n), ctypes.c_uint32(n_win), ctypes.byref(per_wave))
+    assert per_wave.value >= 64 and per_wave.value % 64 == 0
+    waves = -(-n // per_wave.value) * n_win
+    assert 0 <= 4 * groups - waves < 4
+    assert groups * 256 < 2**32  # work-items of a launch
 
 
 @pytest.mark.gpu
