@@ -126,7 +126,8 @@ int estimator_run(estimator_t *h, const est_trace_t *trace, const est_stage_cfg_
  * configs and the three arrays of out are DEVICE pointers (the structs themselves live on the
  * host).  workspace is a device scratch buffer of workspace_bytes bytes owned by the caller, or
  * NULL to let the library allocate (and cache in the handle) what it needs; a smaller workspace
- * means fewer wavefronts share the candidates (scratch is per wavefront, not per candidate).  hip_stream is a hipStream_t
+ * means shorter streams between the operations of a candidate and fewer candidates in flight at a time (scratch is
+ * per candidate in flight, not per candidate).  hip_stream is a hipStream_t
  * (NULL = the default stream); all work is enqueued on it and the call returns after that work
  * has completed.  Same errors as estimator_run; EST_ENOMEM if the workspace cannot hold one
  * candidate.

@@ -98,16 +98,28 @@ struct PlanOut {
     uint8_t acc_slot_of_src[EST_MAX_STAGES + 1][EST_TRACE_BIT + 1];
 };
 
+// The streams between operations: how long their rings are at least.  Longer rings let an operation run longer before it has to
+// hand over to its neighbour: 8,192 elements (64 KB) instead of 1,024 take 4 % off a sweep of the ten-stage pipeline (11.0 -> 10.5 s;
+// 32,768 and more: 10.5 s).  Short ones are for scratch that holds a quarter more candidates with them: ten stages, 512 candidates x
+// 20,011 in 400 MB 5.5 ms with long rings (347 in flight), 4.0 ms with short ones (512); 4,500 candidates 35.5 / 25.7 ms; three
+// stages, 1,024 x 2,000 in 64 MB 1.09 / 0.59 ms; scratch that is mostly per-query arrays holds about as many either way (ten stages,
+// 4,500 x 100,003 in 4 GB: 1,419) and keeps the long ones.  Tight ones (what each ring needs; as few member slots and staged keys as a
+// scan can do with) are for scratch that holds no candidate otherwise.
+enum Rings { RINGS_LONG, RINGS_SHORT, RINGS_TIGHT };
+
 // Build the operation list for one run from the DAG and what the trace scan found.
 //
 // For stage c (and for the virtual sink, index S) the trace scan gives the union over visiting
 // queries of the query's nearest visited ancestors.  Those are the streams the stage's input has to
 // be merged from.  A stage fed by exactly one stream, every element of which visits the stage, reads
 // that stream directly.
-int build_plan(estimator *h, const EstStatus &st, uint64_t n, PlanOut &po, bool small_rings = false) {
+int build_plan(estimator *h, const EstStatus &st, uint64_t n, PlanOut &po, Rings rings = RINGS_LONG) {
     const uint32_t S = h->dag.S;
     EstPlan &P = po.plan;
     memset(&P, 0, sizeof P);
+    po.sz = Sizes();
+    po.shape = Shape();
+    po.n_acc = 0;
     memset(po.acc_slot_of_src, 0xFF, sizeof po.acc_slot_of_src);
 
     auto count_of = [&](uint32_t src) -> uint64_t { return src == EST_TRACE_BIT ? n : st.n_visit[src]; };
@@ -116,19 +128,17 @@ int build_plan(estimator *h, const EstStatus &st, uint64_t n, PlanOut &po, bool 
     for (uint32_t s = 0; s < S; ++s) max_rb = std::max(max_rb, st.r_max[s] * st.b_max[s]);
     // a scan's member slots: room for a full batch per replica, and not so little that a step over small batches runs
     // out of slots (64 slots of 8)
-    const uint32_t slot_words = (uint32_t)align_up(std::max(max_rb, 512u), 64);
+    const uint32_t slot_words = (uint32_t)align_up(std::max(max_rb, rings == RINGS_TIGHT ? 1u : 512u), 64);
     P.slot_words = slot_words;
-    // A bounded ring must take a whole group of batches that complete together (<= R*B members)
-    // while its consumer still holds back a look-ahead window, and a merge wants 64 x sources free.
-    // Beyond that need, longer rings let an operation run longer before it has to hand over to its neighbour:
-    // 8,192 elements (64 KB) instead of the 1,024 the need alone gives take 4 % off a sweep of the ten-stage
-    // pipeline (11.0 -> 10.5 s; 32,768 and more: 10.5 s).  A run inside a fixed scratch keeps the short ones (more
-    // candidates in flight matter more there), and so does a call that gives each candidate several wavefronts.  EST_RING_ELEMS sets another floor (tests use a small one, so that
-    // short traces wrap the rings).
-    uint64_t ring_floor = small_rings ? 1024 : 8192;
-    if (const char *e = getenv("EST_RING_ELEMS"))
+    const uint32_t key_words = rings == RINGS_TIGHT ? 2 * 128 : 2 * 256;  // the keys staged in the in-ring
+    // A scan passes on no less than a whole group of batches that complete together (R x B members), and wants room for a window of
+    // 64; a merge wants 64 x sources free.  A reader that waits for this stream holds nothing of it back.
+    uint64_t ring_floor = rings == RINGS_LONG ? 8192 : 1024;
+    if (const char *e = getenv("EST_RING_ELEMS"))  // another floor, for tests: short traces then wrap the rings
         if (atol(e) >= 64 && atol(e) <= (1l << 24)) ring_floor = (uint64_t)atol(e);
     const uint64_t cap_bounded = pow2ceil(std::max<uint64_t>(ring_floor, (uint64_t)max_rb + 64 * EST_KMAX + 65));
+    auto out_cap = [&](uint32_t s) -> uint64_t { return rings == RINGS_TIGHT ? pow2ceil(std::max(256u, st.r_max[s] * st.b_max[s])) : cap_bounded; };
+    auto in_cap = [&](uint32_t n_src) -> uint64_t { return rings == RINGS_TIGHT ? pow2ceil(std::max(256u, 64u * n_src)) : cap_bounded; };
 
     std::vector<int32_t> out_ring(S, -1), in_ring(S, -1);
     struct Src { uint32_t n; int32_t ring_src[EST_KMAX]; };  // ring_src: stage index or EST_TRACE_BIT
@@ -221,7 +231,7 @@ int build_plan(estimator *h, const EstStatus &st, uint64_t n, PlanOut &po, bool 
             op.rep_off = (uint32_t)po.sz.rep_words;
             po.sz.rep_words += EST_REP_WORDS;
             op.slot_off = po.sz.slot_words;
-            po.sz.slot_words += slot_words + 2 * 256;  // (and the keys staged in the in-ring)
+            po.sz.slot_words += slot_words + key_words;
         }
     }
     P.n_ops = no;
@@ -241,7 +251,7 @@ int build_plan(estimator *h, const EstStatus &st, uint64_t n, PlanOut &po, bool 
         if (!live[s]) continue;
         {
             EstRing &R = P.rings[out_ring[s]];
-            uint64_t cap = R.n_cons >= 2 ? std::max<uint64_t>(cap_bounded, pow2ceil(st.n_visit[s])) : cap_bounded;
+            uint64_t cap = R.n_cons >= 2 ? std::max<uint64_t>(out_cap(s), pow2ceil(st.n_visit[s])) : out_cap(s);
             R.off = off;
             R.cap_mask = (uint32_t)(cap - 1);
             off += cap;
@@ -249,8 +259,8 @@ int build_plan(estimator *h, const EstStatus &st, uint64_t n, PlanOut &po, bool 
         if (in_ring[s] >= 0) {
             EstRing &R = P.rings[in_ring[s]];
             R.off = off;
-            R.cap_mask = (uint32_t)(cap_bounded - 1);
-            off += cap_bounded;
+            R.cap_mask = (uint32_t)(in_cap(srcs[s].n) - 1);
+            off += in_cap(srcs[s].n);
         }
     }
     po.sz.ring_elems = off;
@@ -279,19 +289,25 @@ int build_plan(estimator *h, const EstStatus &st, uint64_t n, PlanOut &po, bool 
         P.watch_off[i + 1] = (uint16_t)P.n_watch;
         P.max_watch = std::max(P.max_watch, P.n_watch - (uint32_t)P.watch_off[i]);
     }
-    po.shape = pick_shape(P, lds256);
-    const Shape small = pick_shape(P, lds128);
-    if (small.waves * small.groups > po.shape.waves * po.shape.groups) {
+    if (rings == RINGS_TIGHT) {
         P.scan_ring = 128u;
         po.lds_bytes = lds128;
-        po.shape = small;
-    }
-    if (const char *e = getenv("EST_SCAN_RING"))  // for tests: 128 or 256
-        if (atoi(e) == 128 || atoi(e) == 256) {
-            P.scan_ring = (uint32_t)atoi(e);
-            po.lds_bytes = P.scan_ring == 128u ? lds128 : lds256;
-            po.shape = pick_shape(P, po.lds_bytes);
+        po.shape = pick_shape(P, lds128);
+    } else {
+        po.shape = pick_shape(P, lds256);
+        const Shape small = pick_shape(P, lds128);
+        if (small.slots() > po.shape.slots()) {
+            P.scan_ring = 128u;
+            po.lds_bytes = lds128;
+            po.shape = small;
         }
+        if (const char *e = getenv("EST_SCAN_RING"))  // for tests: 128 or 256
+            if (atoi(e) == 128 || atoi(e) == 256) {
+                P.scan_ring = (uint32_t)atoi(e);
+                po.lds_bytes = P.scan_ring == 128u ? lds128 : lds256;
+                po.shape = pick_shape(P, po.lds_bytes);
+            }
+    }
     if (po.shape.groups == 0) return fail(h, EST_EDEVICE, "the simulation kernel does not fit a compute unit: %s", estbe::last_error());
     po.sz.state_words = P.state_words;
     po.sz.rep_words = align_up(po.sz.rep_words, 4);
@@ -386,12 +402,39 @@ int run_core(estimator *h, uint64_t n, const uint32_t *d_arrival, const uint32_t
                     st.last_arrival, (unsigned long long)h->sum_max_lat, slo_us);
     st.n_visit[S] = (uint32_t)n;
 
+    const bool with_lat = mode == MODE_P99 && n > 0;
+
+    // ---- the per-query tables and the results' staging, the same for every plan's layout
+    uint64_t fixed = 0;
+    auto take = [&](uint64_t bytes) {
+        uint64_t at = fixed;
+        fixed = align_up(fixed + bytes, 256);
+        return at;
+    };
+    const uint64_t n_pad = align_up(std::max<uint64_t>(n, 1), 256);
+    const uint64_t o_p99 = take(n_cfg * 4);
+    const uint64_t o_miss = take(n_cfg * 4);
+    const uint64_t o_cost = take(n_cfg * 8);
+    const uint64_t o_keys = take(n_pad * 8);
+
+    // ---- the plan, and how many candidates the scratch holds with it (h->ws, when the caller passes no scratch, can grow to avail)
+    const uint64_t avail = workspace ? 0 : (uint64_t)estbe::mem_free() + h->ws_bytes;
+    const uint64_t scratch = workspace ? workspace_bytes : avail / 100 * 92;  // (an allocation that fails is tried again smaller, below)
     PlanOut po;
-    po.sz = Sizes();
-    po.n_acc = 0;
+    auto per_candidate = [&](const PlanOut &p) { return p.sz.per_cfg_bytes(n, with_lat) + 64; };  // + alignment slack per area
+    auto holds = [&](const PlanOut &p) -> uint64_t {
+        const uint64_t tables = fixed + align_up((uint64_t)std::max<uint32_t>(p.n_acc, 1) * n_pad, 256) + 8 * 256;
+        return scratch > tables ? (scratch - tables) / per_candidate(p) : 0;
+    };
     if (n > 0) {
-        int rc = build_plan(h, st, n, po, no_alloc);
+        int rc = build_plan(h, st, n, po, no_alloc ? RINGS_SHORT : RINGS_LONG);
         if (rc != EST_OK) return rc;
+        if (!no_alloc && holds(po) < std::min<uint64_t>(n_cfg, po.shape.slots())) {
+            PlanOut shorter;
+            if ((rc = build_plan(h, st, n, shorter, RINGS_SHORT)) != EST_OK) return rc;
+            if (holds(shorter) * 4 >= holds(po) * 5) po = shorter;
+        }
+        if (holds(po) == 0 && (rc = build_plan(h, st, n, po, RINGS_TIGHT)) != EST_OK) return rc;
     } else {
         memset(&po.plan, 0, sizeof po.plan);
         po.plan.state_words = 4;
@@ -401,30 +444,15 @@ int run_core(estimator *h, uint64_t n, const uint32_t *d_arrival, const uint32_t
         po.shape.waves_per_simd = 4;
         po.shape.groups = 256;
     }
-    const bool with_lat = mode == MODE_P99 && n > 0;
-
-    // ---- lay out the scratch
-    const uint64_t n_pad = align_up(std::max<uint64_t>(n, 1), 256);
-    uint64_t fixed = 0;
-    auto take = [&](uint64_t bytes) {
-        uint64_t at = fixed;
-        fixed = align_up(fixed + bytes, 256);
-        return at;
-    };
-    const uint64_t o_keys = take(n_pad * 8);
     const uint64_t o_acc = take((uint64_t)std::max<uint32_t>(po.n_acc, 1) * n_pad);
-    const uint64_t o_p99 = take(n_cfg * 4);
-    const uint64_t o_miss = take(n_cfg * 4);
-    const uint64_t o_cost = take(n_cfg * 8);
-    const uint64_t per_cfg = po.sz.per_cfg_bytes(n, with_lat) + 64;  // + alignment slack per area
+    const uint64_t per_cfg = per_candidate(po);
 
     uint8_t *ws = (uint8_t *)workspace;
     uint64_t ws_bytes = workspace_bytes;
     if (!ws) {
         const uint64_t max_slots = std::min<uint64_t>(n_cfg, po.shape.slots());
         uint64_t want = fixed + per_cfg * max_slots + 8 * 256;
-        uint64_t avail = (uint64_t)estbe::mem_free() + h->ws_bytes;
-        uint64_t budget = std::min<uint64_t>(want, avail / 100 * 92);  // (an allocation that fails is tried again smaller, below)
+        uint64_t budget = std::min<uint64_t>(want, scratch);
         // (when the free memory is what limits the scratch, the budget moves a little from call to call with whatever
         // else the process allocates: a cached workspace within a sixteenth of it is kept, since freeing and
         // allocating a few hundred GB costs seconds)
@@ -657,8 +685,6 @@ int run_shared_core(estimator *h, uint64_t n, const uint32_t *d_arrival, const u
     st.n_visit[S] = (uint32_t)n;
 
     PlanOut po;
-    po.sz = Sizes();
-    po.n_acc = 0;
     int rc = build_plan(h, st, n, po);
     if (rc != EST_OK) return rc;
     const EstPlan &P = po.plan;

@@ -28,7 +28,7 @@
     do {                                                                                               \
         wv::sync();                                                                                    \
         if (ln == 0)                                                                                   \
-            for (uint32_t i_ = chk_wr > 0 ? chk_wr : 1; i_ < wr; ++i_) {                               \
+            for (uint32_t i_ = chk_wr > 0 && wr - chk_wr <= omask ? chk_wr : chk_wr + 1; i_ < wr; ++i_) { \
                 const uint64_t a_ = out[(i_ - 1) & omask], b_ = out[i_ & omask];                       \
                 if ((uint32_t)(b_ >> 32) != 0xFFFFFFFFu && !(a_ < b_)) {                               \
                     fprintf(stderr, "order violated by path %d at out[%u]: %llx then %llx (stage %u)\n", tag, i_, (unsigned long long)a_, (unsigned long long)b_, s); \
