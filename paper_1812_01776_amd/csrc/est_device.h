@@ -74,7 +74,9 @@ EST_DEV uint64_t *est_dbg_rec(const EstSimArgs *a, uint32_t t, uint32_t s) {
 
 // Ring cursors and the other state words of a candidate, in LDS, are written by the operation that owns them and read
 // by its neighbours, which may run in another wavefront of the workgroup at the same time: they are read and written
-// through these (the value is the same in every lane).
+// through these (the value is the same in every lane).  Where the order matters it is kept: an end flag before the
+// cursor that then is final, a cursor before the elements it says are there or the room it says is free.
+EST_DEV uint32_t ld_ord(const uint32_t *p) { return wv::load_ordered(p); }
 EST_DEV uint32_t ld_st(const uint32_t *p) { return wv::load_shared(p); }
 EST_DEV void st_st(uint32_t *p, uint32_t v) { wv::store_shared(p, v); }
 
@@ -101,8 +103,8 @@ EST_DEV View view_of(const Ctx &c, int32_t ring) {
         const EstRing &R = c.P->rings[ring];
         v.base = c.rings + R.off;
         v.mask = R.cap_mask;
-        v.fin = ld_st(&c.st[c.P->fin_off + ring]) != 0u;  // (before the cursor: a stream seen as ended is seen whole)
-        v.wr = ld_st(&c.st[c.P->wr_off + ring]);
+        v.fin = ld_ord(&c.st[c.P->fin_off + ring]) != 0u;  // (before the cursor: a stream seen as ended is seen whole)
+        v.wr = ld_ord(&c.st[c.P->wr_off + ring]);
     }
     return v;
 }
@@ -123,6 +125,7 @@ EST_DEV uint32_t ring_space(const Ctx &c, int32_t ring, uint32_t wr) {
     const EstRing &R = c.P->rings[ring];
     uint32_t used = 0;
     for (uint32_t i = 0; i < R.n_cons; ++i) used = umax(used, wr - ld_st(&c.st[c.P->rd_off + R.cons_edge[i]]));
+    wv::ordered();  // (the readers are through with what is written next)
     EST_CHECK(used <= R.cap_mask + 1u);
     return R.cap_mask + 1u - used;
 }
@@ -445,7 +448,7 @@ EST_DEV bool scan_run(const Ctx &c, const EstOp &op) {
         }
         if (staged < 64 && !in.fin) {
             // the producer may have gone on meanwhile
-            const uint32_t fin2 = wv::uniform(ld_st(&c.st[P.fin_off + op.src_ring[0]])), wr2 = wv::uniform(ld_st(&c.st[P.wr_off + op.src_ring[0]]));
+            const uint32_t fin2 = wv::uniform(ld_ord(&c.st[P.fin_off + op.src_ring[0]])), wr2 = wv::uniform(ld_ord(&c.st[P.wr_off + op.src_ring[0]]));
             if (fin2 || wr2 != in.wr) {
                 in.fin = fin2 ? 1u : 0u;
                 in.wr = wr2;
