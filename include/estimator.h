@@ -98,7 +98,8 @@ typedef struct {
     uint64_t workspace_bytes; /* device scratch used                                                  */
     float capture_ms;         /* estimator_run_shared_dev: the launch that simulates the bases (part of sim_ms) */
     float ops_run_fraction;   /* estimator_run_shared_dev: operations run / (candidates x operations); else 0    */
-    uint32_t waves_per_candidate; /* wavefronts there were for every candidate in flight: 1, 2 (to 3) or 4 (or more) */
+    uint32_t waves_per_candidate; /* wavefronts there were for every candidate in flight: 1, 2 (to 3) or 4 (or more); in
+                                     rounds, those of the round that had the fewest */
     uint32_t reserved;
 } est_stats_t;
 

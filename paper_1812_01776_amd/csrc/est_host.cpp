@@ -345,6 +345,9 @@ void set_shape(EstSimArgs &sa, const PlanOut &po, const Shape &shape, uint32_t p
     sa.quantum = 256;
 }
 
+// est_stats_t::waves_per_candidate of a launch
+uint32_t waves_each(uint32_t waves, uint32_t per_group) { return waves >= 4 * per_group ? 4 : waves >= 2 * per_group ? 2 : 1; }
+
 struct DevBuf {
     void *p = nullptr;
     ~DevBuf() {
@@ -617,7 +620,7 @@ int run_core(estimator *h, uint64_t n, const uint32_t *d_arrival, const uint32_t
     memset(&ss, 0, sizeof ss);
     ss.n_launches = 1;
     ss.n_slots = (uint32_t)n_slots;
-    ss.waves_per_candidate = shape.waves >= 4 * per_group ? 4 : shape.waves >= 2 * per_group ? 2 : 1;
+    ss.waves_per_candidate = waves_each(shape.waves, per_group);
     ss.sim_ms = estbe::event_ms(e0, e1);
     ss.prep_ms = estbe::event_ms(ev_p0, ev_p1) + estbe::event_ms(ev_p2, ev_p3);
     for (uint32_t s = 0; s < S; ++s) ss.stage_visits += st.n_visit[s];
@@ -965,6 +968,7 @@ int run_shared_core(estimator *h, uint64_t n, const uint32_t *d_arrival, const u
         estbe::event_record(cap_done[k], cap_stream);
         return 0;
     };
+    uint32_t each = 4;  // wavefronts per candidate, in the launch of candidates that has the fewest
     auto launch_candidates = [&](uint64_t k) -> int {
         const uint64_t lo = round_lo[k], hi = round_lo[k + 1];
         const uint32_t ar = (uint32_t)(k % n_areas);
@@ -983,6 +987,7 @@ int run_shared_core(estimator *h, uint64_t n, const uint32_t *d_arrival, const u
                 mine = std::max<uint64_t>(n_slots > next ? n_slots - next : 0, std::min<uint64_t>(n_slots, 64));  // never more than exist
             }
             set_shape(cb, po, po.shape, share(std::min<uint64_t>(mine, hi - lo)), (uint32_t)std::min<uint64_t>(mine, hi - lo));
+            each = std::min(each, waves_each(cb.waves, cb.per_group));
             cb.have_lat = 1;
             cb.state = (uint32_t *)(ws + o_state);  cb.state_stride = po.sz.state_words;
             cb.rings = (uint64_t *)(ws + o_rings);  cb.ring_stride = po.sz.ring_elems;
@@ -1025,7 +1030,7 @@ int run_shared_core(estimator *h, uint64_t n, const uint32_t *d_arrival, const u
     est_stats_t &ss = h->stats;
     memset(&ss, 0, sizeof ss);
     ss.n_launches = (uint32_t)((capture ? 2 : 1) * n_rounds);
-    ss.waves_per_candidate = 1;
+    ss.waves_per_candidate = each;
     ss.n_slots = (uint32_t)n_slots;
     ss.capture_ms = capture_ms;
     ss.sim_ms = estbe::event_ms(e0, e2);

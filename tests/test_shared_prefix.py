@@ -67,6 +67,13 @@ def test_bases_taken_a_group_at_a_time_emulated(per_round, monkeypatch):
         assert stats["n_launches"] in (-(-5 // per_round), 2 * -(-5 // per_round))
 
 
+@pytest.mark.parametrize("per_base,waves", [(2, 4), (4, 2), (8, 1)])
+def test_stats_tell_the_wavefronts_per_candidate_emulated(per_base, waves):
+    # (the emulation holds two workgroups of four wavefronts)
+    w, bases, base_of = workloads.neighbourhood_case(3, n=60, n_bases=1, per_base=per_base, S=4)
+    assert _check(emu_lib.make(w), w, bases, base_of, "cpu")["waves_per_candidate"] == waves
+
+
 def test_no_bases_or_no_queries_fall_back_to_the_plain_run():
     import torch
     w, bases, base_of = workloads.neighbourhood_case(7, n=60)
