@@ -57,6 +57,36 @@ def _cases(i, n):
     yield _queue_case(200 + i, R, B, 1.3 * load, quantum, n + 1, start=1)
 
 
+def _horizon_case(i, n):
+    """Queues that run into the horizon at every size: four times the load, and a trace that ends as close to the horizon as is
+    accepted."""
+    R, B, load, quantum = SIZES[i]
+    w = _queue_case(300 + i, R, B, 4.0 * load, quantum, n)
+    w.slo_us = 1
+    w.arrival_us = (w.arrival_us.astype(np.int64) + (2**32 - 3 - int(w.arrival_us[-1]) - int(w.lat_us.max(axis=(1, 2)).sum()))).astype(np.uint32)
+    ref = oracle.run(w.parents, w.lat_us, w.cost_uusd_hr, w.arrival_us, w.visit_mask, w.cfg_hw, w.cfg_batch,
+                     w.cfg_replicas, w.slo_us, want_latencies=True)
+    clamped = int((ref["latency"][0] + w.arrival_us.astype(np.uint64) == 2**32 - 1).sum())
+    assert 0 < clamped < n
+    return w
+
+
+@pytest.mark.parametrize("i", range(len(SIZES)))
+def test_queues_at_the_horizon_emulated(i):
+    w = _horizon_case(i, 8000 if SIZES[i][0] * SIZES[i][1] == 4096 else 1500)
+    _compare(w, emu_lib.make(w))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [8000, 20001])
+@pytest.mark.parametrize("i", range(len(SIZES)))
+def test_queues_at_the_horizon_gpu(i, n):
+    w = _horizon_case(i, n)
+    est = binding.Estimator(w.parents, w.lat_us, w.cost_uusd_hr)
+    _compare(w, est)
+    est.close()
+
+
 @pytest.mark.parametrize("i", range(len(SIZES)))
 def test_steps_at_the_edges_emulated(i):
     for w in _cases(i, 421):
