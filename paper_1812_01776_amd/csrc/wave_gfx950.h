@@ -51,8 +51,6 @@ EST_DEV bool lane_in_const() {
 
 // value of lane-1 (lane 0 keeps its own) / of lane+1 (lane 63 keeps its own: shl1)
 EST_DEV uint32_t shr1(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x138, 0xF, 0xF, false); }
-// the same, except that lane 63 gets an unspecified value (no copy of the old value is needed first)
-EST_DEV uint32_t shl1_any(uint32_t v) { return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x130, 0xF, 0xF, true); }
 EST_DEV uint32_t shl1(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x130, 0xF, 0xF, false); }
 // value of lane ^ 1, ^ 2, ^ 4, ^ 8 (data-parallel-primitive moves inside a row of 16 lanes; every
 // lane has a source, so no previous value is carried)
@@ -96,15 +94,7 @@ EST_DEV uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfir
 // through uniform() first: where the compiler keeps such a value in a vector register (it does when it cannot
 // prove the value uniform), the scalar-register operand of the instruction text would otherwise not assemble.
 
-// v (the same in every lane), hidden from the optimiser and kept in a scalar register: a test of the result stays a
-// scalar compare and branch of its own instead of being merged with its neighbours into lane-mask arithmetic
-EST_DEV uint32_t opaque_uniform(uint32_t v) {
-    v = uniform(v);
-    asm volatile("" : "+s"(v));
-    return v;
-}
-
-// 1 when a >= b (a != b), else 0, for operands that are the same in every lane: a scalar compare whose result is an
+// 1 when a >= b (a == b), else 0, for operands that are the same in every lane: a scalar compare whose result is an
 // integer in a scalar register (several tests combined with & and | then cost one branch, and no lane masks)
 EST_DEV uint32_t flag_ge(uint32_t a, uint32_t b) {
     uint32_t r;
@@ -116,26 +106,6 @@ EST_DEV uint32_t flag_eq(uint32_t a, uint32_t b) {
     uint32_t r;
     a = uniform(a); b = uniform(b);
     asm("s_cmp_eq_u32 %1, %2\n\ts_cselect_b32 %0, 1, 0" : "=s"(r) : "s"(a), "s"(b) : "scc");
-    return r;
-}
-EST_DEV uint32_t flag_lt(uint32_t a, uint32_t b) {
-    uint32_t r;
-    a = uniform(a); b = uniform(b);
-    asm("s_cmp_lt_u32 %1, %2\n\ts_cselect_b32 %0, 1, 0" : "=s"(r) : "s"(a), "s"(b) : "scc");
-    return r;
-}
-// 1 when a != b and c >= d (d at least 1), else 0
-EST_DEV uint32_t flag_ne_and_ge(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
-    uint32_t r;
-    a = uniform(a); b = uniform(b); c = uniform(c); d = uniform(d);
-    asm("s_cmp_lg_u32 %1, %2\n\ts_cselect_b32 %0, %3, 0\n\ts_cmp_ge_u32 %0, %4\n\ts_cselect_b32 %0, 1, 0"
-        : "=&s"(r) : "s"(a), "s"(b), "s"(c), "s"(d) : "scc");
-    return r;
-}
-EST_DEV uint32_t flag_ne(uint32_t a, uint32_t b) {
-    uint32_t r;
-    a = uniform(a); b = uniform(b);
-    asm("s_cmp_lg_u32 %1, %2\n\ts_cselect_b32 %0, 1, 0" : "=s"(r) : "s"(a), "s"(b) : "scc");
     return r;
 }
 

@@ -59,14 +59,14 @@ def test_wave_primitive_lane_layout():
         assert out[6 + i][:width].tolist() == sorted(scr[:width].tolist()), width
     m = 0xF0F0A5A5C3C3FF01
     assert out[12].tolist() == [bin(m & ((1 << i) - 1)).count("1") for i in range(64)]
+    for row, j in ((13, 16), (18, 32)):
+        assert out[row].tolist() == (v[ln & ~j] | v[ln | j] << 16).tolist(), j
     # the scalar-unit helpers
-    assert out[13][:63].tolist() == v[1:].tolist()
     want = v.copy(); want[17] = 1000; want[41] = 1001
     assert out[14].tolist() == want.tolist()
     assert out[15].tolist() == [1000 + 0x200] * 64
     assert out[16].tolist() == [0xFFFFFFFF] * 64
-    assert out[17].tolist() == [0b001010101] * 64
-    assert out[18].tolist() == (1000 + ln).tolist()
+    assert out[17].tolist() == [0b0101] * 64
     sq = scr * scr + 1
     assert out[19].tolist() == (np.cumsum(sq) - sq).tolist()
     assert out[20].tolist() == [int(sq.sum())] * 64
