@@ -914,7 +914,7 @@ EST_UNROLL
                 wr_pub = wr;
             }
             if (any) wv::sync();  // (tables and staged elements: written above, read below by other lanes)
-            // ---- the window of every source: its first 64 staged elements
+            // ---- the window of every source: its first MERGE_WIN staged elements
             uint32_t more = 0, total = 0;  // more, bit j: source j may hold elements beyond its window
             bool blocked = false, clamped = false;
             uint64_t bound = ~0ull;  // everything up to the smallest last key of a source that may hold more is final
@@ -1086,7 +1086,7 @@ EST_UNROLL
                 }
             }
             wr += n_out;
-            if (!is_lat) space -= n_out;  // (nobody consumes while this operation runs)
+            if (!is_lat) space -= n_out;  // (a reader may have made more room since: looked up again when this runs short)
             for (uint32_t j = 0; j < K; ++j) va = wv::set_lane(va, wv::bcast(va, F_HEAD + j) + wv::bcast(vb, F_CONS + j), F_HEAD + j);
             wv::sync_lds();
         }
@@ -1126,7 +1126,7 @@ EST_UNROLL
 // finished by everybody.  (What bounds a call with few candidates is its slowest single simulation, and what a sweep loses
 // at its end are the wavefronts without a candidate.  With one wavefront per candidate, or the operations of a candidate
 // cut beforehand into four runs for a workgroup of four, against this: 16 candidates x 10^6 queries of the ten-stage pipeline
-// 341 -> 130 ms, 4,500 x 50,000 62 -> 49 ms, 12,288 x 100,000 255 -> 217 ms.)
+// 341 -> 130 ms, 4,500 x 50,000 62 -> 49 ms, 12,288 x 100,000 255 -> 206 ms.)
 //
 // Control words in LDS.  Of the workgroup: [0] no candidates are left, [1] how many wavefronts are running something (low 8
 // bits) and how often one has finished (above); then the plan's lists of state words to watch.

@@ -64,9 +64,13 @@ uint32_t shared_bytes_of(const EstPlan &P, uint32_t per_group) {
 
 // As many wavefronts per compute unit as LDS and registers allow, in workgroups of twelve for pipelines of more than eight
 // operations and of four for shorter ones.  An operation is run by one wavefront at a time and the slowest sets the pace of a
-// candidate that has a workgroup to itself, so a short pipeline has no use for more wavefronts.  Measured with 4 / 8 / 12: ten
-// stages, 16 candidates x 10^6 queries 212 / 126 / 127 ms, 12,288 x 100,000 230 / 221 / 217 ms; fork and join of five stages,
-// 97 x 100,000 16.6 / 16.7 ms, 8,192 x 100,000 141 / 153 ms.
+// candidate that has a workgroup to itself, so the shortest pipelines have no use for more wavefronts.  Measured with at most 4 / 8 / 12,
+// ms: ten stages (12 operations), 16 candidates x 300,000 52.8 / 34.1 / 33.6, 6,144 x 50,000 58.3 / 53.7 / 50.6; chains of stages, 16
+// candidates x 100,000 and 4,096 x 20,000: nine (10 operations) 15.2 / 9.7 / 10.4 and 15.3 / 14.4 / 12.9, twenty 30.7 / 17.4 / 13.2 and
+// 32.8 / 31.6 / 27.1; four (5 operations) 8.6 / 9.0 / 9.3 and 7.2 / 7.4 / 7.0; three, 1,024 x 10,000 2.52 / 2.46 / 2.64; fork and join of five
+// (7 operations), 97 x 100,000 13.6 / 13.5 / 14.2.  Between the two sweeps already favour twelve: fork and join, 4,096 x 50,000
+// 36.8 / 38.4 / 33.6, chain of seven (8 operations) 11.4 / 9.9 / 9.8 and 11.8 / 11.3 / 9.8.  With 64 replicas of batches of 64
+// (18 KB of LDS per wavefront) the size of the workgroup makes no difference to a sweep (ten stages 95.8 / 92.6 / 93.7).
 Shape pick_shape(const EstPlan &P, uint32_t lds_per_wave) {
     Shape best;
     const uint32_t top = P.n_ops <= 8 ? 4u : 12u;
@@ -486,8 +490,7 @@ int run_core(estimator *h, uint64_t n, const uint32_t *d_arrival, const uint32_t
     if (ws_bytes < fixed + per_cfg + 8 * 256)
         return fail(h, EST_ENOMEM, "workspace of %llu bytes cannot hold one candidate (%llu + %llu bytes needed)",
                     (unsigned long long)ws_bytes, (unsigned long long)fixed, (unsigned long long)per_cfg);
-    // scratch slots: one per wavefront that works on this launch; more than the device can hold at once
-    // would only wait
+    // scratch slots: as many candidates in flight as the scratch holds and the device has wavefronts; more would only wait
     uint64_t n_slots = std::min<uint64_t>((ws_bytes - fixed - 8 * 256) / per_cfg, n_cfg);
     Shape shape = po.shape;
     uint32_t per_group = 0;  // candidates a workgroup works on at a time

@@ -124,7 +124,7 @@ struct EstSimArgs {
     uint8_t *tabs;      uint64_t tab_stride;     // bytes: the time tables of the merges that join several streams
     uint32_t *lat;      uint64_t lat_stride;     // words
     EstStatus *status;
-    uint64_t *dbg_ticks;           // optional: [n_cfg] 100 MHz ticks each candidate took, then [n_cfg][EST_MAX_STAGES][8] counters (diagnostics)
+    uint64_t *dbg_ticks;           // optional: [n_cfg] 100 MHz ticks each candidate took, then [n_cfg][EST_MAX_STAGES][EST_DBG_WORDS] counters (diagnostics)
     uint32_t *p99; uint32_t *miss; uint64_t *cost;   // [n_cfg] results
     // Shared upstream stages (Section 4.3: the candidates of one planner step differ from a common base
     // in one model, so everything upstream of the change is simulated once).  Only read by the kernel
