@@ -285,15 +285,15 @@ EST_DEV void sync_lds() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// A word that another wavefront of the workgroup may write or read (the same address and value in every lane).  load_ordered: what
-// follows it in the text follows it in memory, so that whoever stored the word after a sync() shows what it wrote before.  A
-// wavefront issues its memory operations in the order of the code, LDS answers them in that order, and one compute unit's loads and
-// stores of global memory reach its cache in it; what is left is to keep the compiler from moving any.  (An acquire at
-// workgroup scope also waits for the wavefront's own stores under way: 1 % on calls with few candidates.)
-EST_DEV void ordered() { asm volatile("" ::: "memory"); }
-EST_DEV uint32_t load_ordered(const uint32_t *p) {
-    const uint32_t v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    ordered();
+// A word that another wavefront of the workgroup may write or read (the same address and value in every lane).  Whoever stores such
+// a word after a sync() shows with it what it wrote before: a wavefront issues its memory operations in the order of the code,
+// LDS answers them in that order, and one compute unit's loads and stores of global memory reach its cache in it.  What is used or
+// overwritten only where the loaded word allows it comes after the load by itself; where two such words have to be read in a
+// certain order, the second one's index goes through after().  (Acquires at workgroup scope instead also wait for the wavefront's own
+// stores under way, 1 % on calls with few candidates; a barrier for all of the compiler's memory operations makes it load the plan's fields
+// again, 1 to 2 % on shared runs.)
+EST_DEV uint32_t after(uint32_t v, uint32_t first) {  // v, known only once first is
+    asm volatile("" : "+v"(v) : "v"(first));
     return v;
 }
 EST_DEV uint32_t load_shared(const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
