@@ -27,7 +27,12 @@ SALU_PEAK_GINST_S = 256 * 2.4            # 614.4 G scalar instructions / s: one 
 # (FETCH_SIZE + WRITE_SIZE scaled by a copy kernel of known size; SQ_INSTS_VALU; SQ_INSTS_SALU), keyed by
 # (workload, candidates per call).  Each entry names the SHA-256 (first 16 hex digits) of the kernel sources it
 # was taken on; the line below prints it only while the sources in the tree still hash to that, else null.
-PROFILED = {}
+PROFILED = {
+    ("W4", 65536): {"csrc_sha16": "127c0305e97c29b3", "traffic_bytes": 1.6527e13, "valu_insts": 3.76661e12, "salu_insts": 4.5787e12,
+                    "source": "profiles/est_sim_kernel_W4.md"},
+    ("W5", 262144): {"csrc_sha16": "127c0305e97c29b3", "traffic_bytes": 1.3639e14, "valu_insts": 2.74328e13, "salu_insts": 3.33388e13,
+                     "source": "profiles/est_sim_kernel_W5.md"},
+}
 
 
 def csrc_sha16():
@@ -249,7 +254,7 @@ def main():
         prof = PROFILED.get((wl.name, chunk_of(wl)))
         if prof is not None and per_launch == chunk_of(wl):  # (one launch per library call of that many candidates)
             if prof["csrc_sha16"] == csrc_sha16():
-                r["traffic"] = prof["traffic_bytes"]
+                r["traffic"] = prof.get("traffic_bytes")
                 for key, peak, unit in (("valu", VALU_PEAK_GINST_S, "G wave64 vector instructions/s"), ("salu", SALU_PEAK_GINST_S, "G scalar instructions/s")):
                     g = prof[key + "_insts"] / avg_s / 1e9
                     r[key + "_issue"] = {"insts_per_launch": prof[key + "_insts"], "achieved": g, "peak": peak,
@@ -313,18 +318,16 @@ def main():
             d = np.fromfile(os.path.join(td, "ticks.bin"), dtype=np.uint64)
         rec = d[len(sel):].reshape(len(sel), 32, 16).astype(np.float64)
         stg, oth = rec[:, :S, :], rec[:, 31, :]
-        fast, gen = stg[:, :, 3].sum(), oth[:, 7].sum()
-        tot = fast + gen
-        named = stg[:, :, 4:8].sum(axis=(0, 1))
+        tot, by4, one, by = (stg[:, :, i].sum() for i in (3, 4, 6, 7))
         lsel = sel[:: max(len(sel) // 8, 1)][:8]
         lcfg_t = torch.from_numpy(np.ascontiguousarray(cfg[lsel]).view(np.uint8).reshape(-1)).to(dev)
         lat = est.run_latencies_dev(arr_t, msk_t, lcfg_t, len(lsel)).cpu().numpy().view(np.uint32)
         clamped = float((lat.astype(np.uint64) + w.arrival_us.astype(np.uint64)[None, :] == 2**32 - 1).mean())
         ticks = stg[:, :, 1].sum() + oth[:, 0].sum() + oth[:, 1].sum() + oth[:, 2].sum()
         regime = {"sample": "%d seeded random candidates of the sweep (step counters), %d of them for the clamped share" % (len(sel), len(lsel)),
-                  "stage_visits_by_step": {"light_load_large_groups": named[0] / tot, "light_load": named[1] / tot, "one_query_per_batch": named[2] / tot,
-                                           "block_of_batches": named[3] / tot, "backlog_and_horizon": (fast - named.sum()) / tot, "general_one_batch": gen / tot},
-                  "queries_per_step": tot / (stg[:, :, 2].sum() + stg[:, :, 0].sum()),
+                  "stage_visits_by_step": {"batch_by_batch": by / tot, "batch_by_batch_four_or_more_queries_each": by4 / tot,
+                                           "one_query_per_batch": one / tot, "backlog_and_horizon": (tot - by - by4 - one) / tot},
+                  "queries_per_step": tot / stg[:, :, 2].sum(),
                   "wavefront_time_share": {"scans": stg[:, :, 1].sum() / ticks, "merges": oth[:, 0].sum() / ticks, "latency_sink": oth[:, 1].sum() / ticks,
                                            "p99_selection": oth[:, 2].sum() / ticks},
                   "queries_clamped_at_horizon": clamped}
@@ -348,7 +351,7 @@ def main():
                "matches_gpu": bool(ok)}
 
     # the largest sweep (W5): one pass of it after the timed steps when that fits the time this run may take;
-    # a pass of W5 does about 8.9 x the work of a pass of W4 (8 x the simulations, a few more visits per query)
+    # a pass of W5 does 8.5 x the stage visits of a pass of W4 (8 x the simulations, a few more visits per query)
     largest = None
     # the regime a planner's search visits (W4's pipeline and trace, candidates provisioned around the SLO boundary):
     # one call, timed like the sweep, reported beside it
@@ -380,7 +383,7 @@ def main():
             a5 = torch.from_numpy(w5.arrival_us.view(np.int32)).to(dev); m5 = torch.from_numpy(w5.visit_mask.view(np.int32)).to(dev)
             c5 = torch.from_numpy(cfg5.view(np.uint8).reshape(-1)).to(dev)
             acc5 = {"sim_ms": 0.0, "launches": 0}
-            # (untimed: one candidate per resident wavefront, so that the handle allocates its scratch, 233 GB, before the pass)
+            # (untimed: one candidate per resident wavefront, so that the handle allocates its scratch, 255 GB, before the pass)
             est5.run_dev(a5, m5, c5[:6144 * w5.n_stages * 4], 6144, w5.slo_us)
             torch.cuda.synchronize()
             q0 = time.perf_counter()
