@@ -49,8 +49,9 @@ bool ascending(const uint32_t *arrival, uint64_t n) {
 }
 
 // Queries that visit each of the S stages, added to visits: 4,096 masks at a time stay in the first-level cache for all
-// stages.
-void count_visits(const uint32_t *mask, uint64_t n, uint32_t S, uint64_t *visits) {
+// stages.  (Its loop is what the hand-off waits for beside the kernel; where it begins in the middle of a cache line, 2 x 10^6 queries of
+// ten stages take 1.42 ms instead of 1.39.)
+__attribute__((aligned(64))) void count_visits(const uint32_t *mask, uint64_t n, uint32_t S, uint64_t *visits) {
     for (uint64_t q0 = 0; q0 < n; q0 += 4096) {
         const uint32_t m = (uint32_t)std::min<uint64_t>(4096, n - q0);
         for (uint32_t s = 0; s < S; ++s) {
