@@ -17,8 +17,9 @@ GOLD = os.path.join(os.path.dirname(__file__), "golden")
 
 @pytest.fixture(params=["1", "4", "2"], ids=["wave_per_candidate", "workgroup_per_candidate", "two_wavefronts_per_candidate"])
 def waves(request, monkeypatch):
-    """The ways a candidate is run: by one wavefront, or (what calls with few candidates get by default) by a
-    workgroup of four, or of two, wavefronts that share its operations as a pipeline."""
+    """The ways a candidate is run: in a workgroup of four wavefronts with as many candidates, or (what calls with few
+    candidates get by default, in workgroups of four or twelve) alone in a workgroup of four, or of two, wavefronts that share
+    its operations as a pipeline."""
     monkeypatch.setenv("EST_WAVES_PER_CANDIDATE", request.param)
     return int(request.param)
 
@@ -117,15 +118,15 @@ def test_wide_batches_many_replicas_ties(seed, waves):
 @pytest.mark.parametrize("seed", range(20))
 def test_bursts_of_large_groups(seed, waves):
     """Queries that become ready in groups of 4..48, large batches whose service time is several times the
-    gap between groups, many batches in flight at once (the light-load step for large groups), with ties
+    gap between groups, many batches in flight at once (batch by batch, four and more queries per batch), with ties
     on a 100-us grid, the fork-join shape, and stages that are short of replicas for part of the trace."""
     _compare(workloads.grouped_case(seed))
 
 
 @pytest.mark.parametrize("seed", range(16))
 def test_small_in_ring(seed, monkeypatch):
-    """The scans' LDS in-ring at 128 keys instead of 256 (what the host picks when that lets a sixth wavefront
-    share a SIMD, as on W4 and W5): refills of uneven length, with and without a filter."""
+    """The scans' LDS in-ring at 128 keys instead of 256 (what the host picks when that lets more wavefronts
+    share a compute unit): refills of uneven length, with and without a filter."""
     monkeypatch.setenv("EST_SCAN_RING", "128")
     _compare([workloads.random_case, workloads.backlog_case, workloads.grouped_case, workloads.provisioned_case][seed % 4](seed + 100))
 

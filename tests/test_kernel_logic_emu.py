@@ -66,7 +66,7 @@ def test_backlog_lockstep_and_horizon_cases_match_oracle(seed):
 @pytest.mark.parametrize("seed", range(10))
 def test_bursts_of_large_groups_match_oracle(seed, tmp_path, monkeypatch):
     # groups of queries that become ready together, large batches, many of them in flight at once; the
-    # step counters confirm that the light-load step for large groups is the one that ran
+    # step counters confirm that batches of four and more queries were formed batch by batch
     w = workloads.grouped_case(seed, n=1200)
     dump = tmp_path / "ticks.bin"
     monkeypatch.setenv("EST_DEBUG_TICKS", str(dump))
@@ -84,7 +84,7 @@ def test_provisioned_small_batches_with_tied_completions_match_oracle(seed):
 
 @pytest.mark.parametrize("seed,nw", [(s, 4) for s in range(12)] + [(s, 2) for s in range(0, 12, 2)])
 def test_several_wavefronts_per_candidate_match_oracle(seed, nw, monkeypatch):
-    # the candidate's operations dealt out to four (or two) wavefronts that run as a pipeline through the rings
+    # a candidate alone in a workgroup of four (or two) wavefronts that run its operations as a pipeline through the rings
     monkeypatch.setenv("EST_WAVES_PER_CANDIDATE", str(nw))
     w = [workloads.random_case, workloads.backlog_case, workloads.grouped_case, workloads.provisioned_case][seed % 4](seed)
     if w.n_queries > 1500:
@@ -96,7 +96,7 @@ def test_several_wavefronts_per_candidate_match_oracle(seed, nw, monkeypatch):
 
 @pytest.mark.parametrize("seed", range(12))
 def test_small_in_ring_matches_oracle(seed, monkeypatch):
-    # the scans' LDS in-ring at 128 keys (what the host picks when that lets a sixth wavefront share a SIMD):
+    # the scans' LDS in-ring at 128 keys (what the host picks when that lets more wavefronts share a compute unit):
     # refills of uneven length, with and without a filter
     monkeypatch.setenv("EST_SCAN_RING", "128")
     w = [workloads.random_case, workloads.backlog_case, workloads.grouped_case, workloads.provisioned_case][seed % 4](seed + 100)
